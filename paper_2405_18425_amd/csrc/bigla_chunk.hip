@@ -1118,6 +1118,7 @@ __global__ __launch_bounds__(kThreads, 2) void bigla_slab_kernel(
 }  // namespace vig
 
 #include "bigla_chunk_ws.hpp"
+#include "bigla_short.hpp"
 
 namespace vig {
 
@@ -1140,7 +1141,8 @@ size_t four_wave_bytes(long BH, int L)
 size_t bigla_chunk_workspace_bytes(long BH, int L)
 {
     const size_t a = four_wave_bytes(BH, L), b = bigla_chunk_ws_workspace_bytes(BH, L);
-    return a > b ? a : b;
+    const size_t c = bigla_short_applicable(L) ? bigla_short_workspace_bytes(BH) : 0;
+    return a > b ? (a > c ? a : c) : (b > c ? b : c);
 }
 
 namespace {
@@ -1188,6 +1190,8 @@ hipError_t chunk_launch(const void *q, const void *k, const void *v, const void 
             hipLaunchKernelGGL((bigla_segment_out_kernel<true, kDk, kTm, kLoc>), dim3((unsigned)blocks),
                                dim3(kThreads), 0, stream, qq, kk, vv, gf, gb, oo, seg_in, flags, stash, L, p.n_chunks,
                                p.seg_chunks, p.n_seg, heads_token_major, lf);
+        else if constexpr (kLoc)
+            return hipErrorInvalidValue;  // (sequences of a single chunk are blended by the locality kernel)
         else  // a single chunk per sequence: no state kernel has run, no flags exist
             hipLaunchKernelGGL((bigla_segment_out_kernel<false, kDk, kTm, kLoc>), dim3((unsigned)blocks),
                                dim3(kThreads), 0, stream, qq, kk, vv, gf, gb, oo, seg_in, flags, stash, L, p.n_chunks,
@@ -1207,15 +1211,19 @@ hipError_t bigla_chunk_set_alias(int on)
     return hipMemcpyToSymbol(HIP_SYMBOL(g_alias_inputs), &on, sizeof(int));
 }
 
-bool bigla_chunk_gated_selectable(long BH, int L, int dk) { return !g_alias_on && bigla_chunk_ws_applicable(BH, L, dk); }
+bool bigla_chunk_gated_selectable(long BH, int L, int dk)
+{
+    return !g_alias_on && (bigla_short_applicable(L) ? (dk == kD || dk == kD / 2) : bigla_chunk_ws_applicable(BH, L, dk));
+}
 
-// bigla_chunk_launch with the eight-wave kernels, the state pass making the gates from the gate producer's
-// low-rank half (and writing them to g_fwd, g_bwd, which the output pass then reads).
+// bigla_chunk_launch with the first pass over the keys (the state pass of the eight-wave kernels, or the one pass of
+// the kernel for short sequences) making the gates from the gate producer's low-rank half, and writing them to g_fwd
+// and g_bwd.
 hipError_t bigla_chunk_gated_launch(const void *q, const void *k, const void *v, void *g_fwd, void *g_bwd, void *out,
                                     long BH, int L, int dk, int n_heads, int heads_token_major, const void *lowrank,
                                     const void *w2, const void *bias, float tau, void *workspace, hipStream_t stream)
 {
-    if (!bigla_chunk_ws_applicable(BH, L, dk) || n_heads <= 0 || BH % n_heads != 0) return hipErrorInvalidValue;
+    if (!bigla_chunk_gated_selectable(BH, L, dk) || n_heads <= 0 || BH % n_heads != 0) return hipErrorInvalidValue;
     if (g_alias_on) return hipErrorInvalidValue;  // aliased slabs would all write the first slab's gates
     GateSource gs;
     gs.lowrank = static_cast<const uint16_t *>(lowrank);
@@ -1223,6 +1231,8 @@ hipError_t bigla_chunk_gated_launch(const void *q, const void *k, const void *v,
     gs.bias = static_cast<const uint16_t *>(bias);
     gs.inv_tau = 1.f / tau;
     gs.n_heads = n_heads;
+    if (bigla_short_applicable(L))
+        return bigla_short_launch(q, k, v, g_fwd, g_bwd, out, BH, L, dk, heads_token_major, workspace, stream, &gs);
     return bigla_chunk_ws_launch(q, k, v, g_fwd, g_bwd, out, BH, L, dk, heads_token_major, workspace, stream, &gs);
 }
 
@@ -1240,6 +1250,8 @@ hipError_t bigla_chunk_launch(const void *q, const void *k, const void *v, const
     // kernels: 0 = the faster set for the shape (the eight-wave kernels where they apply), 1 = four-wave,
     // 2 = eight-wave (an error where they do not apply), 3 = four-wave with one workgroup per slab
     // (with a fusion: grids narrow enough for the eight-wave epilogue's ring of conv-input rows)
+    if (kernels == 0 && !fusion && bigla_short_applicable(L))
+        return bigla_short_launch(q, k, v, g_fwd, g_bwd, out, BH, L, dk, heads_token_major, workspace, stream);
     const bool ws_ok = bigla_chunk_ws_applicable(BH, L, dk) && (!fusion || (fusion->Wg < kXHalo && L < (1 << 22)));
     if (kernels == 2 && !ws_ok) return hipErrorInvalidValue;
     if (kernels == 2 || (kernels == 0 && ws_ok)) {

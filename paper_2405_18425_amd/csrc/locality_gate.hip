@@ -76,7 +76,7 @@ constexpr unsigned kOffGrid = 0xfffffff0u;
 template <typename T, int DV, int RS, bool kTm /* [B,L,H,dv] instead of [B,H,L,dv] */>
 __global__ __launch_bounds__(kThreads) void locality_gate_kernel(
     const T *__restrict__ x, const T *__restrict__ w, const T *__restrict__ bias, const T *__restrict__ z,
-    const T *__restrict__ og, T *__restrict__ out, int H, int Hg, int Wg, unsigned threads_per_slab,
+    const T *og, T *out /* may be og */, int H, int Hg, int Wg, unsigned threads_per_slab,
     unsigned blocks_per_slab)
 {
     using V = vec4<T>;

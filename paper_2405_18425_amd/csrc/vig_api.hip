@@ -300,6 +300,13 @@ int bigla_locality_fwd(const void *q, const void *k, const void *v, const void *
         return VIG_ERR_ALIGN;
     const size_t need = vig::bigla_chunk_workspace_bytes(long(B) * H, L);
     if (need > 0 && (!workspace || workspace_bytes < need)) return VIG_ERR_WORKSPACE;
+    if (vig::bigla_short_applicable(L)) {
+        // one launch takes the whole sequence as one chunk; the locality kernel then blends its output in place (a thread
+        // reads the o_global of the pixels that it writes, before it writes them)
+        const int st = bigla_fwd_layout(q, k, v, g_fwd, g_bwd, out, B, H, L, dk, dv, dtype, layout, workspace, workspace_bytes, stream);
+        if (st != VIG_OK) return st;
+        return locality_gate_fwd_layout(x, w, bias, gate_logits, out, out, B, H, Hg, Wg, dv, dtype, layout, stream);
+    }
     const vig::LocalityFusion fusion = {x, w, bias, gate_logits, H, Hg, Wg};
     clear_stale_hip_error();
     return hip_status(vig::bigla_chunk_launch(q, k, v, g_fwd, g_bwd, out, long(B) * H, L, dk,
@@ -357,7 +364,8 @@ int gated_bigla_fwd(const void *x, const void *w1, const void *w2, const void *b
     const long BH = long(B) * H;
     const bool fusable = chunkwise_fwd(L, dk, dv, bf16) && vig::bigla_chunk_gated_selectable(BH, L, dk) &&
                          chunk_offsets_ok(L, H, layout);
-    if (plan == VIG_GATES_IN_STATE_PASS && !fusable) return VIG_ERR_UNSUPPORTED;
+    // (asked for by name the plan keeps to the shapes of the eight-wave kernels; short sequences beyond those get it from AUTO)
+    if (plan == VIG_GATES_IN_STATE_PASS && !(fusable && vig::bigla_chunk_ws_selectable(BH, L, dk))) return VIG_ERR_UNSUPPORTED;
     const size_t mixer_bytes = round256(bigla_workspace_bytes(B, H, L, dk, dv, dtype));
     if (plan == VIG_GATES_SEPARATE || !fusable) {
         const int st = gate_producer_fwd(x, w1, w2, bias, g_fwd, g_bwd, B, H, L, D, dk, tau, dtype, layout, stream);

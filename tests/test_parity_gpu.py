@@ -1094,3 +1094,62 @@ def test_bigla_bwd_is_the_gradient_of_the_forward_kernels():
     rhs = (loss(+1.0) - loss(-1.0)) / (2 * h)
     _say(f"<grad, u> = {lhs:.6f}, central difference of the forward = {rhs:.6f}")
     assert abs(lhs - rhs) <= 2e-3 * max(1.0, abs(rhs))
+
+
+# --------------------------------------------------------------------------- #
+# sequences taken as one chunk (32 to 256 tokens)
+# --------------------------------------------------------------------------- #
+@pytest.mark.parametrize("layout,dk", (("bhld", 64), ("blhd", 64), ("bhld", 32), ("blhd", 32)))
+@pytest.mark.parametrize("L", (32, 33, 48, 49, 64, 65, 97, 129, 196, 209, 241, 256))
+def test_bigla_one_chunk_sequences(L, layout, dk):
+    """The kernel that takes a whole sequence as one chunk: lengths around its tiles of 16 tokens, waves of 32 and the
+    two and four slabs that share a workgroup, five slabs (the last workgroup is not full); in one call slabs of mild
+    gates, slabs just inside and just beyond the limit of bf16 operands, hard resets, and a slab that leaves the fast
+    form by a few channels of one stretch."""
+    import torch
+    from paper_2405_18425_amd import binding as vb
+
+    w = wl.Workload("one_chunk", B=5, H=1, Hg=1, Wg=L, dk=dk, dv=64, dtype="bf16", gate_mu=-1.0)
+    _say(f"bigla one chunk L{L} {layout} dk{dk}")
+    s = wl.generate(w, seed=L + dk, tensors=("q", "k", "v", "g_fwd", "g_bwd"))
+    r = np.random.default_rng(L)
+    for name in ("g_fwd", "g_bwd"):
+        g = wl.widen(s[name], "bf16")
+        g[1] = -0.24
+        g[2] = -0.3
+        g[3] = np.where(r.random(g[3].shape) < 0.02, -30.0, -0.01)
+        g[4, :, L // 2:, ::5] = -2.0
+        s[name] = wl.store(g, "bf16")
+    t = {n: wl.to_torch(a, "bf16", "cuda:0") for n, a in s.items()}
+    if layout == "blhd":
+        t = {n: a.transpose(1, 2).contiguous() for n, a in t.items()}
+    out = vb.bigla_fwd(t["q"], t["k"], t["v"], t["g_fwd"], t["g_bwd"], layout=layout, out=torch.full_like(t["v"], float("nan")))
+    torch.cuda.synchronize()
+    if layout == "blhd":
+        out = out.transpose(1, 2).contiguous()
+    assert_close(wl.widen(wl.from_torch(out, "bf16"), "bf16"), run_bigla_oracle(s, "bf16"), TOL["bf16"], f"L{L}")
+
+
+@pytest.mark.parametrize("layout,dk,bias_mu", (("bhld", 64, 0.0), ("blhd", 64, -9.0), ("blhd", 32, 0.0)))
+@pytest.mark.parametrize("L", (40, 49, 196, 250))
+def test_gated_bigla_one_chunk_sequences(L, layout, dk, bias_mu):
+    """gated_bigla_fwd where one launch makes the gates and takes the sequence as one chunk: bit for bit what the gate
+    producer followed by the token mixer returns (which the oracle checks elsewhere), in and beyond the fast form."""
+    import torch
+    from paper_2405_18425_amd import binding as vb
+
+    B, H, D = 3, 3, 192
+    _say(f"gated one chunk L{L} {layout} dk{dk}")
+    st = wl.generate_gate_inputs(B, L, D, H, dk, "bf16", seed=L, bias_mu=bias_mu)
+    s = wl.generate(wl.Workload("gated", B=B, H=H, Hg=1, Wg=L, dk=dk, dv=64, dtype="bf16", gate_mu=0.0), seed=L,
+                    tensors=("q", "k", "v"))
+    t = {n: wl.to_torch(a, "bf16", "cuda:0") for n, a in {**st, **s}.items()}
+    if layout == "blhd":
+        for n in ("q", "k", "v"):
+            t[n] = t[n].transpose(1, 2).contiguous()
+    w1, w2 = t["w1"].t().contiguous(), t["w2"].t().contiguous()
+    got, want = (vb.gated_bigla_fwd(t["x"], w1, w2, t["q"], t["k"], t["v"], bias=t["bias"], layout=layout, plan=plan)
+                 for plan in ("auto", "separate"))
+    torch.cuda.synchronize()
+    for a, b, name in zip(got, want, ("out", "g_fwd", "g_bwd")):
+        assert torch.equal(a, b), name
