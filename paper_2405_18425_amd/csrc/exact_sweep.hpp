@@ -1,0 +1,497 @@
+// Building blocks of the exact (token by token, fp32 arithmetic) kernels of the token mixer and its
+// gradient (Section 4.2.1, Eq. (BiGLA)).
+//
+// Every quantity they produce is a readout of a dk x dv matrix that follows a recurrence over the
+// tokens: M_t = diag(decay_t) M_prev + (outer product), then a contraction of M_t with a vector over
+// one of its dimensions.  The chain from token to token is one fused multiply-add per element, so
+// what bounds these kernels is the instructions and the latencies around it.  The mapping keeps both
+// out of the chain: a WAVE owns a strip of the matrix, its lanes lie along the contracted dimension
+// (64 lanes, or 64 / W strips side by side where that dimension is W = 32 or 16), and a lane holds
+// kStrip = 4 elements of the other dimension.  Operands along the lanes are then plain coalesced
+// loads into registers, kDepth tiles ahead, with no trip through LDS and no barrier; the products of
+// kTile tokens x 4 elements are summed over the lanes together, in a tree that halves the values a lane
+// keeps at every level (70 instructions for 32 values over 64 lanes).
+// The two directions are walked at the same time by two waves, from the two ends: each parks its
+// results for the first half of its way (split at a tile boundary), one barrier, then each adds what the
+// other has parked to its own.  For 12 slabs of 196 tokens, 64 x 64, fp32 (a workgroup per slab and one
+// direction after the other, tokens through LDS, took 236 us for the forward; a workgroup per 16 rows,
+// tokens through LDS, 54 + 61 us for the gradient) see the measurements at the kernels.
+#pragma once
+
+#include <type_traits>
+
+#include "vig_common.hpp"
+
+namespace vig {
+
+namespace {
+
+constexpr int kStrip = 4;   // matrix elements per lane
+constexpr int kTile = 8;    // tokens whose readouts are summed over the lanes together
+constexpr int kDepth = 3;   // tiles whose operands are in registers or on their way there
+constexpr int kVals = kTile * kStrip;
+
+// the partner's value under a DPP permutation that exchanges the two halves of a lane group
+template <int CTRL>
+__device__ __forceinline__ float dpp_swap(float x)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+
+template <int CTRL, int N>
+__device__ __forceinline__ void halve_dpp(float (&x)[kVals], bool upper)
+{
+#pragma unroll
+    for (int n = 0; n < N / 2; ++n) {
+        const float keep = upper ? x[n + N / 2] : x[n];
+        const float send = upper ? x[n] : x[n + N / 2];
+        x[n] = keep + dpp_swap<CTRL>(send);
+    }
+}
+
+// Sums of kVals values over groups of W lanes.  Afterwards lane l holds in x[0] (x[0], x[1] for W = 16)
+// the totals of value number lane_value<W>(l) (and the next).
+template <int W>
+__device__ __forceinline__ void sum_over_lanes(float (&x)[kVals], int lane)
+{
+    static_assert(kVals == 32 && (W == 64 || W == 32 || W == 16), "levels of the tree");
+    if constexpr (W == 64) {
+        // v_permlane32_swap: the upper half of the first register against the lower half of the second
+#pragma unroll
+        for (int n = 0; n < 16; ++n) {
+            const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[n]), __float_as_uint(x[n + 16]), false, false);
+            x[n] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+        }
+    }
+    constexpr int kA = W == 64 ? 16 : 32;
+    if constexpr (W >= 32) {
+        // v_permlane16_swap: odd rows of 16 lanes of the first against even rows of the second
+#pragma unroll
+        for (int n = 0; n < kA / 2; ++n) {
+            const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[n]), __float_as_uint(x[n + kA / 2]), false, false);
+            x[n] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+        }
+    }
+    constexpr int kB = W >= 32 ? kA / 2 : kA;
+    halve_dpp<0x140, kB>(x, (lane & 8) != 0);      // row_mirror
+    halve_dpp<0x141, kB / 2>(x, (lane & 4) != 0);  // row_half_mirror
+    halve_dpp<0x4e, kB / 4>(x, (lane & 2) != 0);   // quad_perm [2,3,0,1]
+    if constexpr (kB / 8 >= 2)
+        halve_dpp<0xb1, kB / 8>(x, (lane & 1) != 0);  // quad_perm [1,0,3,2]
+    else
+        x[0] += dpp_swap<0xb1>(x[0]);  // (both lanes of a pair end up with the total)
+}
+
+// first value whose total a lane holds, values it holds, and whether it is the one that stores them
+template <int W>
+__device__ __forceinline__ int lane_value(int lane)
+{
+    return W == 64 ? lane >> 1 : W == 32 ? (lane & 31) : 2 * (lane & 15);
+}
+template <int W>
+constexpr int kHeld = W == 16 ? 2 : 1;
+template <int W>
+__device__ __forceinline__ bool lane_stores(int lane)
+{
+    return W != 64 || (lane & 1) == 0;
+}
+
+template <typename T>
+__device__ __forceinline__ void load_strip(const T *p, float (&f)[kStrip])
+{
+    if constexpr (sizeof(T) == 2) {
+        const uint2 u = *reinterpret_cast<const uint2 *>(p);
+        f[0] = bf16_lo_to_f32(u.x); f[1] = bf16_hi_to_f32(u.x);
+        f[2] = bf16_lo_to_f32(u.y); f[3] = bf16_hi_to_f32(u.y);
+    } else {
+        const float4 u = *reinterpret_cast<const float4 *>(p);
+        f[0] = u.x; f[1] = u.y; f[2] = u.z; f[3] = u.w;
+    }
+}
+
+// element `n` (32 bits: inside a tile) of a row tensor
+template <typename T>
+__device__ __forceinline__ const T *at(const T *base, unsigned n)
+{
+    return reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + n * unsigned(sizeof(T)));
+}
+
+// Orders this wave's LDS writes before its later LDS reads of what other lanes of the wave wrote (the LDS
+// executes one wave's accesses in order; this keeps the compiler from moving them across each other)
+__device__ __forceinline__ void lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// alpha = e^g to within an ulp in nine instructions (expf: fifteen): 2^(g log2 e) on the hardware's instruction, with
+// the rounding of the product put back to first order.  A log-gate is <= 0; below -150 alpha is zero in fp32.
+__device__ __forceinline__ float gate_factor(float g)
+{
+    const float kHi = 1.44269502162933349609375f, kLo = 1.92596299112661746887e-8f;  // log2 e in two parts
+    g = g < -150.f ? -150.f : g;  // (NaN stays)
+    const float x = g * kHi;
+    const float rest = fmaf(g, kLo, fmaf(g, kHi, -x));
+    const float e = __builtin_amdgcn_exp2f(x);
+    return fmaf(e, 0.693147182464599609375f * rest, e);
+}
+
+// The way of one direction over the tokens: tile number n of it covers the tokens token(n, 0..kTile-1) in
+// visiting order.  Both directions share the tile boundaries; a ragged last tile belongs to the
+// sequence's end.
+struct Way {
+    int L, tiles;
+    bool descending;
+    __device__ __forceinline__ int token(int n, int i) const
+    {
+        return descending ? (tiles - 1 - n) * kTile + (kTile - 1 - i) : n * kTile + i;
+    }
+    __device__ __forceinline__ int low(int n) const { return (descending ? tiles - 1 - n : n) * kTile; }
+    __device__ __forceinline__ bool ragged(int n) const { return low(n) + kTile > L; }
+    // token(n, i) - low(n), clamped to the sequence (always a valid address)
+    __device__ __forceinline__ unsigned offset(int n, int i) const
+    {
+        return unsigned(min(descending ? kTile - 1 - i : i, L - 1 - low(n)));
+    }
+    // tiles of the first half: what the other direction meets in its second half
+    __device__ __forceinline__ int first_half() const { return descending ? tiles - tiles / 2 : tiles / 2; }
+};
+
+__device__ __forceinline__ Way make_way(int L, bool descending)
+{
+    Way w;
+    w.L = L;
+    w.tiles = (L + kTile - 1) / kTile;
+    w.descending = descending;
+    return w;
+}
+
+// Readouts over the rows of the matrix: M_t = diag(alpha) M_prev + u_t^T (b_scale * b_t), result_t = r_t M_t, for the
+// strip of columns col0 .. (64 / DK strips of four side by side in a wave).  kDelayed false: alpha is the gate of
+// the token itself (a state: u = k, b = v, r = q); true: the gate of the token visited before (an adjoint: u = q,
+// b = d_out, r = k).  `park`: fp32, dense or strided like the result; result = result_scale * (own + parked).
+// One barrier, executed by every wave that calls this.  `park` and `result` may be one buffer (fp32).
+template <typename T, int DK, int DV, bool kDelayed>
+__device__ __forceinline__ void column_sweep(const T *u_rows, const T *r_rows, const T *g_rows, const T *b_rows,
+                                             float *park, T *result, size_t step, size_t park_step, int L,
+                                             bool descending, int col_block, float b_scale, float result_scale, int lane)
+{
+    constexpr int kGroups = 64 / DK;
+    constexpr int kH = kHeld<DK>;
+    const Way way = make_way(L, descending);
+    const int ch = lane % DK;
+    int col0 = (col_block * kGroups + lane / DK) * kStrip;
+    // kept out of the scalar unit where a wave has one strip: scalar loads of the strip's operands, three
+    // tiles of them, overflow the scalar registers
+    asm("" : "+v"(col0));
+    const int held = lane_value<DK>(lane);
+    const int held_i = held / kStrip, held_col = col0 + held % kStrip;
+    const bool storing = lane_stores<DK>(lane);
+
+    struct Operands {
+        float u[kTile], r[kTile], g[kTile], b[kTile][kStrip], other[kH];
+    };
+    float M[kStrip] = {0.f, 0.f, 0.f, 0.f}, before = 0.f;
+    // a whole tile's offsets, the same in every tile (a wave alone on its SIMD pays for scalar address
+    // arithmetic as much as for any other instruction)
+    unsigned off_k[kTile], off_v[kTile];
+#pragma unroll
+    for (int i = 0; i < kTile; ++i) {
+        const unsigned t = unsigned(descending ? kTile - 1 - i : i) * unsigned(step);
+        off_k[i] = t * DK + unsigned(ch);
+        off_v[i] = t * DV + unsigned(col0);
+    }
+
+    auto half = [&](int first, int last, bool second) __attribute__((always_inline)) {
+        auto fetch = [&](Operands &o, int n) __attribute__((always_inline)) {
+            n = min(n, last - 1);  // (past the end: loaded, never used; a branch would make every wait a full one)
+            const size_t low = size_t(way.low(n));
+            const T *u = u_rows + low * step * DK, *r = r_rows + low * step * DK, *g = g_rows + low * step * DK;
+            const T *b = b_rows + low * step * DV;
+            auto load = [&](auto clamped) __attribute__((always_inline)) {
+#pragma unroll
+                for (int i = 0; i < kTile; ++i) {
+                    const unsigned tk = clamped ? way.offset(n, i) * unsigned(step) * DK + unsigned(ch) : off_k[i];
+                    const unsigned tv = clamped ? way.offset(n, i) * unsigned(step) * DV + unsigned(col0) : off_v[i];
+                    o.u[i] = io<T>::load(at(u, tk));
+                    o.r[i] = io<T>::load(at(r, tk));
+                    o.g[i] = io<T>::load(at(g, tk));
+                    load_strip(at(b, tv), o.b[i]);
+                }
+            };
+            if (way.ragged(n)) load(std::true_type{});
+            else load(std::false_type{});
+            if (second) {
+                const size_t t = size_t(min(way.token(n, held_i), L - 1));
+#pragma unroll
+                for (int h = 0; h < kH; ++h) o.other[h] = park[t * park_step * DV + held_col + h];
+            }
+        };
+        auto walk = [&](Operands &o, int n) __attribute__((always_inline)) {
+            // tokens past the sequence: nothing enters the matrix (ascending they come last, descending
+            // first, when it is still zero)
+            if (way.ragged(n)) {
+#pragma unroll
+                for (int i = 0; i < kTile; ++i) {
+                    if (way.token(n, i) < L) continue;
+                    o.u[i] = 0.f;
+                    o.g[i] = 0.f;
+#pragma unroll
+                    for (int c = 0; c < kStrip; ++c) o.b[i][c] = 0.f;
+                }
+            }
+            float x[kVals];
+#pragma unroll
+            for (int i = 0; i < kTile; ++i) {
+                const float alpha = gate_factor(o.g[i]);
+                const float decay = kDelayed ? before : alpha;
+#pragma unroll
+                for (int c = 0; c < kStrip; ++c) {
+                    M[c] = fmaf(decay, M[c], o.u[i] * (kDelayed ? b_scale * o.b[i][c] : o.b[i][c]));
+                    x[kStrip * i + c] = o.r[i] * M[c];
+                }
+                before = alpha;
+            }
+            sum_over_lanes<DK>(x, lane);
+            const int t = way.token(n, held_i);
+            if (storing && t < L) {
+#pragma unroll
+                for (int h = 0; h < kH; ++h) {
+                    if (second)
+                        io<T>::store(result + size_t(t) * step * DV + held_col + h, result_scale * (o.other[h] + x[h]));
+                    else
+                        park[size_t(t) * park_step * DV + held_col + h] = x[h];
+                }
+            }
+        };
+        if (first >= last) return;
+        Operands o[kDepth];
+#pragma unroll
+        for (int d = 0; d < kDepth; ++d) fetch(o[d], first + d);
+        int n = first;
+        for (; n + kDepth <= last; n += kDepth) {
+#pragma unroll
+            for (int d = 0; d < kDepth; ++d) {
+                walk(o[d], n + d);
+                fetch(o[d], n + d + kDepth);
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < kDepth - 1; ++d)
+            if (n + d < last) walk(o[d], n + d);
+    };
+    half(0, way.first_half(), false);
+    __threadfence_block();
+    __syncthreads();
+    half(way.first_half(), way.tiles, true);
+}
+
+// Inclusive prefix sum over the wave's 64 lanes
+__device__ __forceinline__ float wave_scan(float x, int lane)
+{
+    x = row_scan<0>(x);
+#pragma unroll
+    for (int row = 1; row < 4; ++row) {
+        const float total = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 16 * row - 1));
+        x += lane >> 4 == row ? total : 0.f;
+    }
+    return x;
+}
+
+// Gradients that are readouts over the columns: for the strip of rows row0 .. (64 / DV strips of four in a wave) the state
+// S of the wave's own direction (dq_t = S_t do_t^T) and the adjoint A that runs the same way, the other
+// direction's (dk_t = A_t v_t^T), together: they share every operand.  The ascending wave of a pair has S of the
+// forward direction and A of the backward one, the descending wave the other two; where they have
+// met, dq and dk are sums of both, and
+//   e^f = q * dq^f - k * dk^f ,  e^b = q * dq^b - k * dk^b
+// take the place of the parked partial results (part_f, part_b: dense fp32 [L][DK]); their running sums over
+// the tokens, descending and ascending, are dg_fwd and dg_bwd.
+// Two barriers, executed by every wave that calls this.  `stage` is the wave's own LDS.
+template <int DV>
+struct RowStage {
+    // per token of the tile: both gates' factors, k and q of the wave's rows
+    float x[kTile][4][kStrip * (64 / DV)];
+};
+
+template <typename T, int DK, int DV>
+__device__ __forceinline__ void row_sweep(const T *q_rows, const T *k_rows, const T *v_rows, const T *gf_rows,
+                                          const T *gb_rows, const T *do_rows, T *dq_rows, T *dk_rows, T *dgf_rows,
+                                          T *dgb_rows, float *part_f, float *part_b, RowStage<DV> &stage, size_t step,
+                                          int L, bool descending, int row_block, int lane)
+{
+    constexpr int kGroups = 64 / DV;
+    constexpr int kRows = kStrip * kGroups;   // rows of the wave
+    constexpr int kLoads = 2 * kGroups;       // staged values a lane loads per tile
+    constexpr int kH = kHeld<DV>;
+    const Way way = make_way(L, descending);
+    const int col = lane % DV, grp = lane / DV, first_row = row_block * kRows;
+    const int held = lane_value<DV>(lane);
+    const int held_i = held / kStrip, held_c = kStrip * grp + held % kStrip;  // token and row (of the wave's) of the totals held
+    const bool storing = lane_stores<DV>(lane);
+    // the lane's staged values: array (0: gate of S, 1: gate of A, 2: k, 3: q), token and row
+    auto staged = [&](int j, int &array, int &i, int &row) __attribute__((always_inline)) {
+        const int n = lane + 64 * j;
+        array = n / (kTile * kRows);
+        i = n / kRows % kTile;
+        row = n % kRows;
+    };
+    const T *staged_rows[kLoads];  // where a lane's staged values come from (row included)
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) {
+        int array, i, row;
+        staged(j, array, i, row);
+        const T *rows = descending ? gb_rows : gf_rows;
+        if (array == 1) rows = descending ? gf_rows : gb_rows;
+        if (array == 2) rows = k_rows;
+        if (array == 3) rows = q_rows;
+        staged_rows[j] = rows + first_row + row;
+    }
+
+    struct Operands {
+        float v[kTile], d[kTile], s[kLoads], other_f[kH], other_b[kH];
+    };
+    unsigned off_v[kTile];  // a whole tile's offsets
+#pragma unroll
+    for (int i = 0; i < kTile; ++i)
+        off_v[i] = unsigned(descending ? kTile - 1 - i : i) * unsigned(step) * DV + unsigned(col);
+    float S[kStrip] = {0.f, 0.f, 0.f, 0.f}, A[kStrip] = {0.f, 0.f, 0.f, 0.f}, before[kStrip] = {0.f, 0.f, 0.f, 0.f};
+
+    auto half = [&](int first, int last, bool second) __attribute__((always_inline)) {
+        auto fetch = [&](Operands &o, int n) __attribute__((always_inline)) {
+            n = min(n, last - 1);  // (past the end: loaded, never used; a branch would make every wait a full one)
+            const size_t low = size_t(way.low(n));
+            const T *v = v_rows + low * step * DV, *d = do_rows + low * step * DV;
+            auto load = [&](auto clamped) __attribute__((always_inline)) {
+#pragma unroll
+                for (int i = 0; i < kTile; ++i) {
+                    const unsigned t = clamped ? way.offset(n, i) * unsigned(step) * DV + unsigned(col) : off_v[i];
+                    o.v[i] = io<T>::load(at(v, t));
+                    o.d[i] = io<T>::load(at(d, t));
+                }
+            };
+            if (way.ragged(n)) load(std::true_type{});
+            else load(std::false_type{});
+#pragma unroll
+            for (int j = 0; j < kLoads; ++j) {
+                int array, i, row;
+                staged(j, array, i, row);
+                o.s[j] = io<T>::load(staged_rows[j] + (low + way.offset(n, i)) * step * DK);
+            }
+            if (second) {
+                const size_t t = low + way.offset(n, held_i);
+#pragma unroll
+                for (int h = 0; h < kH; ++h) {
+                    o.other_f[h] = part_f[t * DK + first_row + held_c + h];
+                    o.other_b[h] = part_b[t * DK + first_row + held_c + h];
+                }
+            }
+        };
+        auto walk = [&](Operands &o, int n) __attribute__((always_inline)) {
+            const bool ragged = way.ragged(n);
+#pragma unroll
+            for (int j = 0; j < kLoads; ++j) {
+                int array, i, row;
+                staged(j, array, i, row);
+                float x = array < 2 ? gate_factor(o.s[j]) : o.s[j];
+                // tokens past the sequence: nothing enters the matrices
+                if (ragged && way.token(n, i) >= L) x = array < 2 ? 1.f : 0.f;
+                stage.x[i][array][row] = x;
+            }
+            if (ragged) {
+#pragma unroll
+                for (int i = 0; i < kTile; ++i)
+                    if (way.token(n, i) >= L) o.v[i] = o.d[i] = 0.f;
+            }
+            lds_order();
+            float xq[kVals], xk[kVals];
+#pragma unroll
+            for (int i = 0; i < kTile; ++i) {
+                const float d = 0.5f * o.d[i], v = o.v[i];
+                float gs[kStrip], ga[kStrip], kr[kStrip], qr[kStrip];
+                load_strip(&stage.x[i][0][kStrip * grp], gs);
+                load_strip(&stage.x[i][1][kStrip * grp], ga);
+                load_strip(&stage.x[i][2][kStrip * grp], kr);
+                load_strip(&stage.x[i][3][kStrip * grp], qr);
+#pragma unroll
+                for (int c = 0; c < kStrip; ++c) {
+                    S[c] = fmaf(gs[c], S[c], kr[c] * v);
+                    A[c] = fmaf(before[c], A[c], qr[c] * d);
+                    before[c] = ga[c];
+                    xq[kStrip * i + c] = S[c] * d;
+                    xk[kStrip * i + c] = A[c] * v;
+                }
+            }
+            sum_over_lanes<DV>(xq, lane);
+            sum_over_lanes<DV>(xk, lane);
+            const int t = way.token(n, held_i);
+            if (storing && t < L) {
+#pragma unroll
+                for (int h = 0; h < kH; ++h) {
+                    const size_t dense = size_t(t) * DK + first_row + held_c + h;
+                    // the parked halves lie where the other wave finds them by direction: the state's in
+                    // part_f, the adjoint's in part_b
+                    if (!second) {
+                        part_f[dense] = xq[h];
+                        part_b[dense] = xk[h];
+                        continue;
+                    }
+                    const float kk = stage.x[held_i][2][held_c + h], qq = stage.x[held_i][3][held_c + h];
+                    const size_t o_row = size_t(t) * step * DK + first_row + held_c + h;
+                    io<T>::store(dq_rows + o_row, o.other_f[h] + xq[h]);
+                    io<T>::store(dk_rows + o_row, o.other_b[h] + xk[h]);
+                    // own state with the other wave's adjoint: the own state's direction, and the reverse
+                    const float e_state = qq * xq[h] - kk * o.other_b[h];
+                    const float e_adjoint = qq * o.other_f[h] - kk * xk[h];
+                    part_f[dense] = descending ? e_adjoint : e_state;
+                    part_b[dense] = descending ? e_state : e_adjoint;
+                }
+            }
+            lds_order();  // the totals' reads of the stage before the next tile's writes
+        };
+        if (first >= last) return;
+        Operands o[kDepth];
+#pragma unroll
+        for (int d = 0; d < kDepth; ++d) fetch(o[d], first + d);
+        int n = first;
+        for (; n + kDepth <= last; n += kDepth) {
+#pragma unroll
+            for (int d = 0; d < kDepth; ++d) {
+                walk(o[d], n + d);
+                fetch(o[d], n + d + kDepth);
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < kDepth - 1; ++d)
+            if (n + d < last) walk(o[d], n + d);
+    };
+    half(0, way.first_half(), false);
+    __threadfence_block();
+    __syncthreads();
+    half(way.first_half(), way.tiles, true);
+    __threadfence_block();
+    __syncthreads();
+
+    // running sums, a lane per token: dg_fwd from the last token on (descending wave), dg_bwd from the first
+    const float *part = descending ? part_f : part_b;
+    T *dg = descending ? dgf_rows : dgb_rows;
+    for (int r0 = 0; r0 < kRows; r0 += kStrip) {
+        float run[kStrip] = {0.f, 0.f, 0.f, 0.f};
+        for (int n = 0; n < L; n += 64) {
+            const int t = descending ? L - 1 - n - lane : n + lane;
+            const bool live = n + lane < L;
+            float e[kStrip] = {0.f, 0.f, 0.f, 0.f};
+            if (live) load_strip(part + size_t(t) * DK + first_row + r0, e);
+#pragma unroll
+            for (int c = 0; c < kStrip; ++c) {
+                e[c] = run[c] + wave_scan(e[c], lane);
+                run[c] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(e[c]), 63));
+                if (live) io<T>::store(dg + size_t(t) * step * DK + first_row + r0 + c, e[c]);
+            }
+        }
+    }
+}
+
+}  // namespace
+
+}  // namespace vig

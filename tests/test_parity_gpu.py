@@ -1153,3 +1153,48 @@ def test_gated_bigla_one_chunk_sequences(L, layout, dk, bias_mu):
     torch.cuda.synchronize()
     for a, b, name in zip(got, want, ("out", "g_fwd", "g_bwd")):
         assert torch.equal(a, b), name
+
+
+# --------------------------------------------------------------------------- #
+# exact kernels (two directions at a time, strips of four rows or columns per lane)
+# --------------------------------------------------------------------------- #
+@pytest.mark.parametrize("dk,dv,layout", ((16, 16, "bhld"), (16, 64, "blhd"), (64, 16, "bhld"), (32, 64, "blhd"),
+                                          (64, 32, "bhld"), (64, 64, "blhd")))
+@pytest.mark.parametrize("L", (1, 7, 8, 9, 16, 17, 24, 25, 49, 64, 65, 130))
+def test_exact_kernels_tile_edges(L, dk, dv, layout):
+    """fp32 forward and gradient around the edges of the tiles of 8 tokens, the meeting point of the two directions
+    and the 64-token steps of the gate gradients' running sums.
+
+    Bound: a term of a sum passes through at most L products with a gate (each gate within 2 ulp), L updates and a tree
+    of L + 64 additions; with u = 2^-24 that is (5 L + 64) u of the sum of the terms' magnitudes, which is what the
+    oracle gives for |q|, |k|, |v|, |d_out|.  The gate gradients are running sums of q dq - k dk over the sequence: the same
+    of |q| |dq| + |k| |dk|, summed, and once more L additions."""
+    import oracle
+    import torch
+    from paper_2405_18425_amd import binding as vb
+
+    B, H = (2, 3) if L > 16 else (3, 43)  # the many short slabs: two pairs of waves per workgroup
+    _say(f"exact kernels L{L} dk{dk} dv{dv} {layout}")
+    w = wl.Workload("exact", B=B, H=H, Hg=1, Wg=L, dk=dk, dv=dv, dtype="f32", gate_mu=-1.0)
+    s = wl.generate(w, seed=L + dk + 3 * dv, tensors=("q", "k", "v", "g_fwd", "g_bwd"))
+    s["d_out"] = np.random.default_rng(L).standard_normal(s["v"].shape).astype(np.float32)
+    s["g_fwd"][0, 0, L // 2:] = -40.0
+    t = {n: wl.to_torch(a, "f32", "cuda:0") for n, a in s.items()}
+    if layout == "blhd":
+        t = {n: a.transpose(1, 2).contiguous() for n, a in t.items()}
+    names = ("q", "k", "v", "g_fwd", "g_bwd", "d_out")
+    got = [vb.bigla_fwd(*(t[n] for n in names[:5]), layout=layout, out=torch.full_like(t["v"], float("nan")))]
+    got += vb.bigla_bwd(*(t[n] for n in names), layout=layout)
+    torch.cuda.synchronize()
+    if layout == "blhd":
+        got = [a.transpose(1, 2) for a in got]
+    d = {n: a.astype(np.float64) for n, a in s.items()}
+    m = {n: a if n.startswith("g_") else np.abs(a) for n, a in d.items()}
+    ref = [oracle.bigla(*(d[n] for n in names[:5])), *oracle.bigla_bwd(*(d[n] for n in names))]
+    size = [oracle.bigla(*(m[n] for n in names[:5])), *oracle.bigla_bwd(*(m[n] for n in names))]
+    running = np.sum(m["q"] * size[1] + m["k"] * size[2], axis=2, keepdims=True)
+    u = 2.0 ** -24
+    for i, name in enumerate(("out", "dq", "dk", "dv", "dg_fwd", "dg_bwd")):
+        bound = (5 * L + 64) * u * size[i] if i < 4 else (6 * L + 64) * u * running
+        err = np.abs(got[i].cpu().numpy().astype(np.float64) - ref[i])
+        assert np.all(err <= bound + 1e-37), f"{name}: {np.max(err / (bound + 1e-37)):.2f} of the bound"
