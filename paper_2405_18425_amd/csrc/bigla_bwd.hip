@@ -39,23 +39,21 @@ __global__ __launch_bounds__(128 * kPairs, 1) void bigla_bwd_exact_kernel(
 {
     constexpr int kRowWork = DK / (kStrip * (64 / DV)) / kPairs;  // workgroups of a slab that take rows
     __shared__ RowStage<DV> stage[2 * kPairs];
-    const size_t slab = blockIdx.x % n_slabs;
+    const unsigned slab = blockIdx.x % n_slabs;
     if (only_marked && only_marked[slab] == 0) return;  // the chunkwise kernels have taken this slab
     const int work = int(blockIdx.x / n_slabs);
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x)) >> 6, lane = int(threadIdx.x) & 63;
     const bool descending = (wave & 1) != 0;
-    const size_t row0 = heads_token_major
-                            ? (slab / heads_token_major) * size_t(L) * heads_token_major + slab % heads_token_major
-                            : slab * size_t(L);
+    const size_t row0 = slab_first_row(slab, L, heads_token_major);
     const size_t step = heads_token_major ? heads_token_major : 1;
     if (work < kRowWork)
         row_sweep<T, DK, DV>(q + row0 * DK, k + row0 * DK, v + row0 * DV, gf + row0 * DK, gb + row0 * DK, d_out + row0 * DV,
-                             dq + row0 * DK, dk + row0 * DK, dgf + row0 * DK, dgb + row0 * DK, part_f + slab * L * DK,
-                             part_b + slab * L * DK, stage[wave], step, L, descending, work * kPairs + (wave >> 1), lane);
+                             dq + row0 * DK, dk + row0 * DK, dgf + row0 * DK, dgb + row0 * DK, part_f + size_t(slab) * L * DK,
+                             part_b + size_t(slab) * L * DK, stage[wave], step, L, descending, work * kPairs + (wave >> 1), lane);
     else
         // the adjoint that runs with the wave belongs to the other direction
         column_sweep<T, DK, DV, true>(q + row0 * DK, k + row0 * DK, (descending ? gf : gb) + row0 * DK, d_out + row0 * DV,
-                                      part_v + slab * L * DV, dv + row0 * DV, step, 1, L, descending,
+                                      part_v + size_t(slab) * L * DV, dv + row0 * DV, step, 1, L, descending,
                                       (work - kRowWork) * kPairs + (wave >> 1), 0.5f, 1.f, lane);
 }
 

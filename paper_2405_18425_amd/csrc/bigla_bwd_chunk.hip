@@ -123,11 +123,8 @@ struct SlabRows {
 };
 constexpr unsigned kBeyond = 0xfffffff0u;
 
-__device__ __forceinline__ SlabRows slab_rows(const void *base, long slab, int L, int heads_token_major, int width = kD)
+__device__ __forceinline__ SlabRows slab_rows(const void *base, size_t first, int L, int heads_token_major, int width = kD)
 {
-    const size_t first = heads_token_major
-                             ? size_t(slab / heads_token_major) * size_t(L) * heads_token_major + slab % heads_token_major
-                             : size_t(slab) * L;
     const unsigned pitch = 2u * unsigned(width) * unsigned(heads_token_major ? heads_token_major : 1);
     const unsigned extent = unsigned(L - 1) * pitch + 2u * unsigned(width);
     SlabRows s;
@@ -266,15 +263,14 @@ __global__ __launch_bounds__(kThreads, 2) void bigla_bwd_chunk_local_kernel(
     uint16_t *__restrict__ states, float *__restrict__ logdec, int L, int heads_token_major, int n_chunks, int dk)
 {
     __shared__ __align__(16) LocalLds sm;
-    const long unit = blockIdx.x;
-    const long slab = unit / n_chunks;
-    const int chunk = int(unit % n_chunks);
-    const unsigned t0 = unsigned(chunk) * kC;
+    const unsigned unit = blockIdx.x, slab = unit / unsigned(n_chunks);
+    const unsigned t0 = (unit - slab * unsigned(n_chunks)) * kC;
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r = lane & 15, g = lane >> 4;
 
-    const SlabRows q = slab_rows(q_all, slab, L, heads_token_major, dk), k = slab_rows(k_all, slab, L, heads_token_major, dk);
-    const SlabRows v = slab_rows(v_all, slab, L, heads_token_major), dout = slab_rows(do_all, slab, L, heads_token_major);
-    const SlabRows gf = slab_rows(gf_all, slab, L, heads_token_major, dk), gb = slab_rows(gb_all, slab, L, heads_token_major, dk);
+    const size_t first = slab_first_row(slab, L, heads_token_major);
+    const SlabRows q = slab_rows(q_all, first, L, heads_token_major, dk), k = slab_rows(k_all, first, L, heads_token_major, dk);
+    const SlabRows v = slab_rows(v_all, first, L, heads_token_major), dout = slab_rows(do_all, first, L, heads_token_major);
+    const SlabRows gf = slab_rows(gf_all, first, L, heads_token_major, dk), gb = slab_rows(gb_all, first, L, heads_token_major, dk);
 
     uint2 qr[4], kr[4];
     {
@@ -358,7 +354,7 @@ __global__ __launch_bounds__(kScanThreads) void bigla_bwd_chunk_scan_kernel(uint
                                                                        int *__restrict__ marks, int n_chunks)
 {
     constexpr int kScanParts = kCt * 256 / kScanThreads;  // workgroups per matrix: 16 * kCt rows of 16 pieces
-    const long slab = blockIdx.x / (4 * kScanParts);
+    const unsigned slab = blockIdx.x / (4 * kScanParts);
     const int kind = (blockIdx.x / kScanParts) & 3, part = blockIdx.x % kScanParts;
     const int tid = threadIdx.x;
     const int piece = part * kScanThreads + tid;  // 0 .. 256 * kCt - 1
@@ -689,17 +685,16 @@ __global__ __launch_bounds__(kThreads, 2) void bigla_bwd_chunk_main_kernel(
     int heads_token_major, int n_chunks, int dk)
 {
     __shared__ __align__(16) MainLds sm;
-    const long unit = blockIdx.x;
-    const long slab = unit / n_chunks;
+    const unsigned unit = blockIdx.x, slab = unit / unsigned(n_chunks);
     if (marks[slab] != 0) return;  // left to the exact kernels
-    const int chunk = int(unit % n_chunks);
-    const unsigned t0 = unsigned(chunk) * kC;
+    const unsigned t0 = (unit - slab * unsigned(n_chunks)) * kC;
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r = lane & 15, g = lane >> 4;
 
-    const SlabRows q = slab_rows(q_all, slab, L, heads_token_major, dk), k = slab_rows(k_all, slab, L, heads_token_major, dk);
-    const SlabRows v = slab_rows(v_all, slab, L, heads_token_major), dout = slab_rows(do_all, slab, L, heads_token_major);
-    const SlabRows gf = slab_rows(gf_all, slab, L, heads_token_major, dk), gb = slab_rows(gb_all, slab, L, heads_token_major, dk);
-    const SlabRows dgf = slab_rows(dgf_all, slab, L, heads_token_major, dk), dgb = slab_rows(dgb_all, slab, L, heads_token_major, dk);
+    const size_t first = slab_first_row(slab, L, heads_token_major);
+    const SlabRows q = slab_rows(q_all, first, L, heads_token_major, dk), k = slab_rows(k_all, first, L, heads_token_major, dk);
+    const SlabRows v = slab_rows(v_all, first, L, heads_token_major), dout = slab_rows(do_all, first, L, heads_token_major);
+    const SlabRows gf = slab_rows(gf_all, first, L, heads_token_major, dk), gb = slab_rows(gb_all, first, L, heads_token_major, dk);
+    const SlabRows dgf = slab_rows(dgf_all, first, L, heads_token_major, dk), dgb = slab_rows(dgb_all, first, L, heads_token_major, dk);
 
     uint2 qr[4], kr[4];
     const uint16_t *mats = states + size_t(unit) * 4 * kMat;
@@ -723,9 +718,9 @@ __global__ __launch_bounds__(kThreads, 2) void bigla_bwd_chunk_main_kernel(
                             [&]() { in_b = fetch_dir<1, kCt>(gb, mats, t0, tid, w, lane); });
     chunk_direction<1, kCt>(sm, in_b, dgb, t0, tid, w, lane, r, g, qr, kr, acc, []() {});
 
-    store_own(sm.st, slab_rows(dq_all, slab, L, heads_token_major, dk), t0, w, lane, r, g, acc.dq);
-    store_own(sm.ad, slab_rows(dk_all, slab, L, heads_token_major, dk), t0, w, lane, r, g, acc.dk);
-    store_own(sm.v, slab_rows(dv_all, slab, L, heads_token_major), t0, w, lane, r, g, acc.dv);
+    store_own(sm.st, slab_rows(dq_all, first, L, heads_token_major, dk), t0, w, lane, r, g, acc.dq);
+    store_own(sm.ad, slab_rows(dk_all, first, L, heads_token_major, dk), t0, w, lane, r, g, acc.dk);
+    store_own(sm.v, slab_rows(dv_all, first, L, heads_token_major), t0, w, lane, r, g, acc.dv);
 }
 
 }  // namespace

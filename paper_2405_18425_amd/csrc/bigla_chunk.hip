@@ -582,7 +582,7 @@ __device__ __forceinline__ void out_unit(
     int seg;
     unit_slab_segment(unit, n_seg, slab, seg);
     // first row of the slab and distance between its tokens, in rows of the tensor
-    const long row0 = kTm ? (slab / heads) * L * heads + slab % heads : slab * L;
+    const long row0 = long(slab_first_row(unsigned(slab), L, kTm ? heads : 0));
     const long row0_in = g_alias_inputs ? 0 : row0;
     const long base = row0 * kD, in_base = row0_in * kD, key_base = row0_in * kDk;
     // bytes between consecutive tokens of the slab, and the slab's extent from its first row
@@ -604,7 +604,7 @@ __device__ __forceinline__ void out_unit(
     LocalitySlab ls;
     if (kLoc) {
         // the head's taps and bias as fp32 in LDS (read after the first barrier of the first step)
-        const int head = int(slab % lf.H);
+        const int head = int(unsigned(slab) % unsigned(lf.H));
         const uint16_t *taps = static_cast<const uint16_t *>(lf.w) + size_t(head) * kD * 9;
         for (int i = tid; i < kD * 9; i += kThreads) sm.cw[i % 9][i / 9] = bf16_lo_to_f32(taps[i]);
         if (tid < kD)
@@ -838,7 +838,7 @@ __device__ __forceinline__ bool state_unit(
     long slab;
     int seg;
     unit_slab_segment(unit, n_seg, slab, seg);
-    const long row0 = g_alias_inputs ? 0 : (kTm ? (slab / heads) * L * heads + slab % heads : slab * L);
+    const long row0 = g_alias_inputs ? 0 : (long(slab_first_row(unsigned(slab), L, kTm ? heads : 0)));
     // bytes between consecutive tokens of the slab, and the slab's extent from its first row
     const unsigned key_pitch = unsigned(heads) * kDk * 2u, val_pitch = unsigned(heads) * kD * 2u;
     const unsigned key_extent = unsigned(L - 1) * key_pitch + kDk * 2u, val_extent = unsigned(L - 1) * val_pitch + kD * 2u;

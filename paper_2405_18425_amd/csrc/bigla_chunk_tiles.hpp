@@ -504,14 +504,14 @@ __device__ __forceinline__ bf16x8 operand(const uint2 &a, const uint2 &b)
 // written in either case: both passes use the same mapping).
 __device__ __forceinline__ void unit_slab_segment(long unit, int n_seg, long &slab, int &seg)
 {
-    const long n_slabs = gridDim.x / unsigned(n_seg);
-    if (n_slabs % 8 == 0) {
-        const long j = unit / 8;
-        slab = unit % 8 + 8 * (j / n_seg);
-        seg = int(j % n_seg);
+    const unsigned u = unsigned(unit), ns = unsigned(n_seg);  // 32 bits: see slab_first_row
+    if (gridDim.x / ns % 8 == 0) {
+        const unsigned j = u / 8;
+        slab = long(u % 8 + 8 * (j / ns));
+        seg = int(j % ns);
     } else {
-        slab = unit / n_seg;
-        seg = int(unit % n_seg);
+        slab = long(u / ns);
+        seg = int(u % ns);
     }
 }
 

@@ -131,7 +131,7 @@ struct SlabIo {
                                       const uint16_t *gf_all, const uint16_t *gb_all, uint16_t *out_all, long slab,
                                       int L, int heads)
     {
-        const long row0 = kTm ? (slab / heads) * L * heads + slab % heads : slab * L;
+        const long row0 = long(slab_first_row(unsigned(slab), L, kTm ? heads : 0));
         const long in0 = g_alias_inputs ? 0 : row0;
         pitch = unsigned(kTm ? heads : 1) * kD * 2u;
         key_pitch = unsigned(kTm ? heads : 1) * kDk * 2u;
@@ -205,8 +205,8 @@ __global__ __launch_bounds__(kWsThreads) void bigla_ws_state_kernel(
     f32x4 gate_bias[4];  // element e of tile i: channel 16g + 4i + e (the accumulators' initial value)
     const uint16_t *lowrank_rows = nullptr;
     if (kGates) {
-        const int head = int(slab % gs.n_heads);
-        lowrank_rows = gs.lowrank + size_t(slab / gs.n_heads) * L * 16;
+        const int head = int(unsigned(slab) % unsigned(gs.n_heads));
+        lowrank_rows = gs.lowrank + size_t(unsigned(slab) / unsigned(gs.n_heads)) * L * 16;
         // (a 32-wide head has channels for the lanes g = 0, 1 only; the others repeat those rows and make zeros)
         const int arow = (16 * (r >> 2)) % kDk + (r & 3);
         const int base = (gdir * gs.n_heads + head) * kDk;
@@ -506,7 +506,7 @@ __device__ __forceinline__ void ws_out_unit(
     const float inv_wg = 1.f / float(lf.Wg > 0 ? lf.Wg : 1);
     auto ring_slot = [&](int tok) { return tok & (kXRing - 1); };
     if (kLoc) {
-        const int head = int(slab % lf.H);
+        const int head = int(unsigned(slab) % unsigned(lf.H));
         // taps [channel][9] bf16: the lane's 8 channels are 72 consecutive values.  Kept as bf16 pairs of
         // taps (0,1) (2,3) (4,5) (6,7) (8,-): a pair meets the same two taps of the input in one
         // v_dot2c_f32_bf16 (exact products, fp32 sum).
@@ -528,7 +528,7 @@ __device__ __forceinline__ void ws_out_unit(
 #pragma unroll
             for (int e = 0; e < 8; ++e) cbias[e] = 0.f;
         }
-        const long row0 = kTm ? (slab / heads) * long(L) * heads + slab % heads : slab * long(L);
+        const long row0 = long(slab_first_row(unsigned(slab), L, kTm ? heads : 0));
         rz = slab_resource(static_cast<const uint16_t *>(lf.gate_logits) + row0 * kD, unsigned(L - 1) * io.pitch + kD * 2u);
     }
     // the lane's gate logits of row t (of its two) of chunk c of the segment
@@ -830,7 +830,7 @@ __device__ __forceinline__ void ws_out_unit(
         StagedRows rxg;
         uint4 rz0 = make_uint4(0u, 0u, 0u, 0u);
         if (kLoc) {
-            const long row0 = kTm ? (slab / heads) * long(L) * heads + slab % heads : slab * long(L);
+            const long row0 = long(slab_first_row(unsigned(slab), L, kTm ? heads : 0));
             const unsigned extent = unsigned(L - 1) * io.pitch + kD * 2u;
             rx = slab_resource(static_cast<const uint16_t *>(lf.x) + row0 * kD, extent);
             if (tid4 < 8) *reinterpret_cast<uint4 *>(&g_ws_xr[kXRing][8 * tid4]) = make_uint4(0u, 0u, 0u, 0u);

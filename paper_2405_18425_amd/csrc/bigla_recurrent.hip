@@ -24,16 +24,14 @@ __global__ __launch_bounds__(128 * kPairs, 1) void bigla_recurrent_kernel(
     int heads_token_major /* 0: [B,H,L,d]; H: [B,L,H,d] */, unsigned n_slabs, bool part_in_out)
 {
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x)) >> 6, lane = int(threadIdx.x) & 63;
-    const size_t slab = blockIdx.x % n_slabs;
+    const unsigned slab = blockIdx.x % n_slabs;
     const int col_block = int(blockIdx.x / n_slabs) * kPairs + (wave >> 1);
     const bool descending = (wave & 1) != 0;
     // first row of the slab and distance between its tokens, in rows of the tensor
-    const size_t row0 = heads_token_major
-                            ? (slab / heads_token_major) * size_t(L) * heads_token_major + slab % heads_token_major
-                            : slab * size_t(L);
+    const size_t row0 = slab_first_row(slab, L, heads_token_major);
     const size_t step = heads_token_major ? heads_token_major : 1;
     // the fp32 side buffer is dense [slab][L][DV]; when the partial sums live in `out` they follow it
-    float *park = o_part + (part_in_out ? row0 : slab * size_t(L)) * DV;
+    float *park = o_part + (part_in_out ? row0 : size_t(slab) * L) * DV;
     column_sweep<T, DK, DV, false>(k + row0 * DK, q + row0 * DK, (descending ? g_bwd : g_fwd) + row0 * DK, v + row0 * DV,
                                    park, out + row0 * DV, step, part_in_out ? step : 1, L, descending, col_block, 1.f,
                                    0.5f, lane);

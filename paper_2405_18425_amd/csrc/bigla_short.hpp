@@ -278,8 +278,8 @@ __global__ __launch_bounds__(64 * kShortWaves, 4) void bigla_short_kernel(
                 }
         }
     } else {
-        const int head = int(slab % gs.n_heads);
-        const uint16_t *lowrank = gs.lowrank + size_t(slab / gs.n_heads) * L * 16;
+        const int head = int(unsigned(slab) % unsigned(gs.n_heads));
+        const uint16_t *lowrank = gs.lowrank + size_t(unsigned(slab) / unsigned(gs.n_heads)) * L * 16;
         uint2 low[2];
 #pragma unroll
         for (int T = 0; T < 2; ++T) {

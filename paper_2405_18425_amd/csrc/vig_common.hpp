@@ -113,6 +113,16 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t slab_resource(const void *p, u
                                              int(kRawDwords));
 }
 
+// First row of slab number `slab` (batch element, head) of a row tensor: head-major (heads = 0) or token-major with
+// `heads` heads.  Slab and workgroup numbers fit 32 bits, and are divided as such: a 64-bit division is about 200
+// dependent scalar instructions, and a workgroup cannot request anything before it.
+__device__ __forceinline__ size_t slab_first_row(unsigned slab, int L, int heads)
+{
+    if (heads == 0) return size_t(slab) * unsigned(L);
+    const unsigned b = slab / unsigned(heads);
+    return size_t(b) * unsigned(L) * unsigned(heads) + (slab - b * unsigned(heads));
+}
+
 // log(sigmoid(z)) = min(z, 0) - log(1 + exp(-|z|)), finite for every finite z.  The bare hardware
 // exp2 / log2 serve: the exponential's argument is <= 0 (an underflow to 0 is the right limit) and
 // the logarithm's lies in [1, 2], so neither needs the range handling of the library functions,
