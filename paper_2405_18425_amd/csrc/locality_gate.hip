@@ -218,13 +218,15 @@ hipError_t launch(const void *x, const void *w, const void *bias, const void *z,
 {
     constexpr int CG = DV / vec4<T>::N;
     // Taller strips re-read less (a strip of RS rows reads RS + 2 input rows) but mean fewer threads and
-    // more registers per thread: 8 rows while that still leaves about four workgroups per compute
-    // unit (measured at 48 slabs of 64 x 64: 21.9 us against 22.5 us with 4 rows, 27.4 us with 2),
-    // then 4 rows, and 2 rows for small problems.
+    // more registers per thread.  8 rows while that still leaves about four workgroups per compute unit (48 slabs of
+    // 64 x 64: 20.2 us against 21.1 with 4 rows and 23.7 with 2; 384 of 14 x 14: 12.6 / 13.1 / 13.3) and the grid is taller
+    // than one strip (1024 slabs of 7 x 7: 11.3 / 10.6 / 11.6); then 4 rows while every compute unit has a workgroup
+    // (32 slabs of 56 x 56: 14.7 / 14.6 / 15.2; 80 of 28 x 28: 12.7 / 11.6 / 12.5; 15 of 37 x 53: 10.1 / 7.7 / 7.9), and 2 rows
+    // for small problems (6 slabs of 14 x 14: 6.8 / 6.9 / 6.5; event times, about 3 us above the kernel's own).
     const long slabs = long(B) * H;
     auto blocks = [&](int rs) { return slabs * ((long((Hg + rs - 1) / rs) * Wg * CG + kThreads - 1) / kThreads); };
-    if (blocks(8) >= 1024) return launch_rs<T, DV, 8>(x, w, bias, z, og, out, slabs, H, Hg, Wg, token_major, stream);
-    if (blocks(4) >= 2048) return launch_rs<T, DV, 4>(x, w, bias, z, og, out, slabs, H, Hg, Wg, token_major, stream);
+    if (Hg > 8 && blocks(8) >= 1024) return launch_rs<T, DV, 8>(x, w, bias, z, og, out, slabs, H, Hg, Wg, token_major, stream);
+    if (blocks(4) >= 256) return launch_rs<T, DV, 4>(x, w, bias, z, og, out, slabs, H, Hg, Wg, token_major, stream);
     return launch_rs<T, DV, 2>(x, w, bias, z, og, out, slabs, H, Hg, Wg, token_major, stream);
 }
 
