@@ -14,8 +14,8 @@
 //                run the same way, and the gate gradients are running sums of what the pair leaves behind;
 //   dv         : a strip of columns of the adjoint.
 // This is the exact-arithmetic path for every head shape and both dtypes (bf16 storage, fp32
-// arithmetic).  For bf16 with 64-wide heads the chunkwise matrix-core kernels run first and these
-// kernels then take only the slabs marked for them (gates beyond the chunkwise range).
+// arithmetic).  For bf16 with 64-wide values the chunkwise matrix-core kernels run instead, and evaluate the slabs
+// whose gates are beyond their range with the same sweeps.
 #include "exact_sweep.hpp"
 #include "vig_common.hpp"
 #include "vig_kernels.hpp"
@@ -34,13 +34,11 @@ __global__ __launch_bounds__(128 * kPairs, 1) void bigla_bwd_exact_kernel(
     const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, const T *__restrict__ gf,
     const T *__restrict__ gb, const T *__restrict__ d_out, T *__restrict__ dq, T *__restrict__ dk, T *__restrict__ dv,
     T *__restrict__ dgf, T *__restrict__ dgb, float *part_f /* [slabs][L][DK] */, float *part_b /* same */,
-    float *part_v /* [slabs][L][DV] */, int L, int heads_token_major /* 0: [B,H,L,d]; H: [B,L,H,d] */, unsigned n_slabs,
-    const int *__restrict__ only_marked /* null: every slab; else only slabs whose entry is non-zero */)
+    float *part_v /* [slabs][L][DV] */, int L, int heads_token_major /* 0: [B,H,L,d]; H: [B,L,H,d] */, unsigned n_slabs)
 {
     constexpr int kRowWork = DK / (kStrip * (64 / DV)) / kPairs;  // workgroups of a slab that take rows
     __shared__ RowStage<DV> stage[2 * kPairs];
     const unsigned slab = blockIdx.x % n_slabs;
-    if (only_marked && only_marked[slab] == 0) return;  // the chunkwise kernels have taken this slab
     const int work = int(blockIdx.x / n_slabs);
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x)) >> 6, lane = int(threadIdx.x) & 63;
     const bool descending = (wave & 1) != 0;
@@ -60,7 +58,7 @@ __global__ __launch_bounds__(128 * kPairs, 1) void bigla_bwd_exact_kernel(
 template <typename T, int DK, int DV>
 hipError_t launch(const void *q, const void *k, const void *v, const void *gf, const void *gb, const void *d_out,
                   void *dq, void *dk, void *dv, void *dgf, void *dgb, long BH, int L, int heads_token_major,
-                  float *ws, const int *only_marked, hipStream_t stream)
+                  float *ws, hipStream_t stream)
 {
     constexpr int kRowStrips = DK / (kStrip * (64 / DV)), kColStrips = DV / (kStrip * (64 / DK));
     float *part_f = ws, *part_b = ws + size_t(BH) * L * DK, *part_v = part_b + size_t(BH) * L * DK;
@@ -72,7 +70,7 @@ hipError_t launch(const void *q, const void *k, const void *v, const void *gf, c
                            static_cast<const T *>(q), static_cast<const T *>(k), static_cast<const T *>(v),
                            static_cast<const T *>(gf), static_cast<const T *>(gb), static_cast<const T *>(d_out),
                            static_cast<T *>(dq), static_cast<T *>(dk), static_cast<T *>(dv), static_cast<T *>(dgf),
-                           static_cast<T *>(dgb), part_f, part_b, part_v, L, heads_token_major, unsigned(BH), only_marked);
+                           static_cast<T *>(dgb), part_f, part_b, part_v, L, heads_token_major, unsigned(BH));
         return hipGetLastError();
     };
     // as in the forward: one pair per workgroup until every compute unit has one
@@ -84,12 +82,12 @@ hipError_t launch(const void *q, const void *k, const void *v, const void *gf, c
 template <typename T, int DK>
 hipError_t launch_dv(int dv_, const void *q, const void *k, const void *v, const void *gf, const void *gb,
                      const void *d_out, void *dq, void *dk, void *dv, void *dgf, void *dgb, long BH, int L,
-                     int heads_token_major, float *ws, const int *only_marked, hipStream_t stream)
+                     int heads_token_major, float *ws, hipStream_t stream)
 {
     switch (dv_) {
-        case 16: return launch<T, DK, 16>(q, k, v, gf, gb, d_out, dq, dk, dv, dgf, dgb, BH, L, heads_token_major, ws, only_marked, stream);
-        case 32: return launch<T, DK, 32>(q, k, v, gf, gb, d_out, dq, dk, dv, dgf, dgb, BH, L, heads_token_major, ws, only_marked, stream);
-        case 64: return launch<T, DK, 64>(q, k, v, gf, gb, d_out, dq, dk, dv, dgf, dgb, BH, L, heads_token_major, ws, only_marked, stream);
+        case 16: return launch<T, DK, 16>(q, k, v, gf, gb, d_out, dq, dk, dv, dgf, dgb, BH, L, heads_token_major, ws, stream);
+        case 32: return launch<T, DK, 32>(q, k, v, gf, gb, d_out, dq, dk, dv, dgf, dgb, BH, L, heads_token_major, ws, stream);
+        case 64: return launch<T, DK, 64>(q, k, v, gf, gb, d_out, dq, dk, dv, dgf, dgb, BH, L, heads_token_major, ws, stream);
     }
     return hipErrorInvalidValue;
 }
@@ -97,12 +95,12 @@ hipError_t launch_dv(int dv_, const void *q, const void *k, const void *v, const
 template <typename T>
 hipError_t launch_dk(int dk_, int dv_, const void *q, const void *k, const void *v, const void *gf, const void *gb,
                      const void *d_out, void *dq, void *dk, void *dv, void *dgf, void *dgb, long BH, int L,
-                     int heads_token_major, float *ws, const int *only_marked, hipStream_t stream)
+                     int heads_token_major, float *ws, hipStream_t stream)
 {
     switch (dk_) {
-        case 16: return launch_dv<T, 16>(dv_, q, k, v, gf, gb, d_out, dq, dk, dv, dgf, dgb, BH, L, heads_token_major, ws, only_marked, stream);
-        case 32: return launch_dv<T, 32>(dv_, q, k, v, gf, gb, d_out, dq, dk, dv, dgf, dgb, BH, L, heads_token_major, ws, only_marked, stream);
-        case 64: return launch_dv<T, 64>(dv_, q, k, v, gf, gb, d_out, dq, dk, dv, dgf, dgb, BH, L, heads_token_major, ws, only_marked, stream);
+        case 16: return launch_dv<T, 16>(dv_, q, k, v, gf, gb, d_out, dq, dk, dv, dgf, dgb, BH, L, heads_token_major, ws, stream);
+        case 32: return launch_dv<T, 32>(dv_, q, k, v, gf, gb, d_out, dq, dk, dv, dgf, dgb, BH, L, heads_token_major, ws, stream);
+        case 64: return launch_dv<T, 64>(dv_, q, k, v, gf, gb, d_out, dq, dk, dv, dgf, dgb, BH, L, heads_token_major, ws, stream);
     }
     return hipErrorInvalidValue;
 }
@@ -124,27 +122,24 @@ hipError_t bigla_bwd_launch(const void *q, const void *k, const void *v, const v
 {
     LaunchTimer timer(kKernelBackward, stream);
     char *base = static_cast<char *>(workspace);
-    const int *only_marked = nullptr;
     if (bigla_bwd_chunk_supported(dk_, dv_, is_bf16)) {
-        // The chunkwise kernels take every slab whose gates they can carry and mark the others.  Sequences
+        float *exact = reinterpret_cast<float *>(base + bigla_bwd_chunk_workspace_bytes(BH, L));
+        // The chunkwise kernels evaluate a slab whose gates they cannot carry with the exact form themselves.  Sequences
         // shorter than half a chunk go to the exact kernels altogether: a slab of a few tokens has only a
         // handful of score entries, all of which can be small at once, and the bf16 rounding of the scaled
         // queries and keys (relative to the summands of those entries) is then large against the slab's own
         // gradients -- reproduced on the CPU from the operand roundings alone.
-        if (!recurrent_only && L >= kChunkwiseMinTokens) {
-            const hipError_t e = bigla_bwd_chunk_launch(q, k, v, g_fwd, g_bwd, d_out, dq, dk, dv, dg_fwd, dg_bwd, BH, L,
-                                                        dk_, heads_token_major, base, stream);
-            if (e != hipSuccess) return e;
-            only_marked = bigla_bwd_chunk_marks(base, BH, L);
-        }
-        base += bigla_bwd_chunk_workspace_bytes(BH, L);
+        if (!recurrent_only && L >= kChunkwiseMinTokens)
+            return bigla_bwd_chunk_launch(q, k, v, g_fwd, g_bwd, d_out, dq, dk, dv, dg_fwd, dg_bwd, BH, L, dk_,
+                                          heads_token_major, base, exact, stream);
+        base = reinterpret_cast<char *>(exact);
     }
     float *ws = reinterpret_cast<float *>(base);
     if (is_bf16)
         return launch_dk<bf16_t>(dk_, dv_, q, k, v, g_fwd, g_bwd, d_out, dq, dk, dv, dg_fwd, dg_bwd, BH, L,
-                                 heads_token_major, ws, only_marked, stream);
+                                 heads_token_major, ws, stream);
     return launch_dk<float>(dk_, dv_, q, k, v, g_fwd, g_bwd, d_out, dq, dk, dv, dg_fwd, dg_bwd, BH, L,
-                            heads_token_major, ws, only_marked, stream);
+                            heads_token_major, ws, stream);
 }
 
 }  // namespace vig

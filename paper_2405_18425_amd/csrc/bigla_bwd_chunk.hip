@@ -28,8 +28,8 @@
 //      total log-decay exceeds 60 nats in some channel;
 //   3. bigla_bwd_chunk_main_kernel (workgroup per chunk): everything above for both directions,
 //      dq, dk, dv accumulated in registers and written once.
-// exp(-b) grows with the decay accumulated over a chunk, so marked slabs are left to the exact
-// token-by-token kernels (which skip every other slab); gates of the paper's form,
+// exp(-b) grows with the decay accumulated over a chunk, so marked slabs are evaluated token by token (exact_sweep.hpp) by
+// the workgroups of the main launch; gates of the paper's form,
 // sigmoid(z)^(1/16), reach 60 nats in 64 steps only for z < -15 throughout.
 //
 // Wavefront mapping (256 threads = 4 waves): wave w owns tokens 16w..16w+15 of the chunk; results
@@ -41,6 +41,7 @@
 // resource that spans the slab.
 #include <type_traits>
 
+#include "exact_sweep.hpp"
 #include "vig_common.hpp"
 #include "vig_kernels.hpp"
 #include "vig_timing.hpp"
@@ -234,7 +235,7 @@ __device__ __forceinline__ void gate_scan(const Tile &gates, int w, int r, int g
 //     2: backward state entering the chunk from the right
 //     3: backward A' of the chunk (decayed adjoint from the left)
 //   log-decays, per (slab, chunk, direction): the chunk's total log-gate per channel, fp32
-//   slab marks: one int per slab, non-zero when the slab is left to the exact kernels
+//   slab marks: one int per slab, non-zero when the slab takes the exact form
 struct Workspace {
     uint16_t *states;
     float *logdec;
@@ -676,17 +677,55 @@ __device__ __forceinline__ void chunk_direction(MainLds &sm, const DirInputs &in
     }
 }
 
+// A slab that is marked: the workgroups of its chunks share out the strips of the exact form, two pairs of waves at a
+// time.  Inside this launch and not in one of its own: a launch that finds no marked slab still took 4.7 us (and
+// two of them, 9.5 us, were 7 % of a call at 384 slabs of 196 tokens).  Not inlined, so that its registers stay out of
+// the chunkwise code's allocation; its LDS is a namespace-scope object, which such a function can address as LDS.
+__shared__ RowStage<kD> g_exact_stage[4];
+
+template <int DK>
+__device__ __attribute__((noinline)) void exact_slab_share(
+    const void *q_all, const void *k_all, const void *v_all, const void *gf_all, const void *gb_all, const void *do_all,
+    void *dq_all, void *dk_all, void *dv_all, void *dgf_all, void *dgb_all, float *exact_ws, int L, int heads_token_major,
+    unsigned n_slabs, unsigned slab, unsigned first_item, int n_chunks)
+{
+    constexpr int kRowItems = DK / kStrip / 2, kColItems = kD / (kStrip * (kD / DK)) / 2;
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x)) >> 6, lane = int(threadIdx.x) & 63;
+    const bool descending = (wave & 1) != 0;
+    const size_t row0 = slab_first_row(slab, L, heads_token_major), step = heads_token_major ? heads_token_major : 1;
+    const size_t keys = size_t(L) * DK, all_keys = keys * n_slabs;
+    auto in = [&](const void *p, int width) { return static_cast<const bf16_t *>(p) + row0 * width; };
+    auto out = [&](void *p, int width) { return static_cast<bf16_t *>(p) + row0 * width; };
+#pragma unroll 1
+    for (int item = int(first_item); item < kRowItems + kColItems; item += n_chunks) {
+        if (item < kRowItems)
+            row_sweep<bf16_t, DK, kD>(in(q_all, DK), in(k_all, DK), in(v_all, kD), in(gf_all, DK), in(gb_all, DK), in(do_all, kD),
+                                      out(dq_all, DK), out(dk_all, DK), out(dgf_all, DK), out(dgb_all, DK),
+                                      exact_ws + slab * keys, exact_ws + all_keys + slab * keys, g_exact_stage[wave], step, L,
+                                      descending, 2 * item + (wave >> 1), lane);
+        else
+            column_sweep<bf16_t, DK, kD, true>(in(q_all, DK), in(k_all, DK), in(descending ? gf_all : gb_all, DK), in(do_all, kD),
+                                               exact_ws + 2 * all_keys + size_t(slab) * L * kD, out(dv_all, kD), step, 1, L,
+                                               descending, 2 * (item - kRowItems) + (wave >> 1), 0.5f, 1.f, lane);
+    }
+}
+
 template <int kCt>
 __global__ __launch_bounds__(kThreads, 2) void bigla_bwd_chunk_main_kernel(
     const void *__restrict__ q_all, const void *__restrict__ k_all, const void *__restrict__ v_all,
     const void *__restrict__ gf_all, const void *__restrict__ gb_all, const void *__restrict__ do_all,
     void *__restrict__ dq_all, void *__restrict__ dk_all, void *__restrict__ dv_all, void *__restrict__ dgf_all,
-    void *__restrict__ dgb_all, const uint16_t *__restrict__ states, const int *__restrict__ marks, int L,
-    int heads_token_major, int n_chunks, int dk)
+    void *__restrict__ dgb_all, const uint16_t *__restrict__ states, const int *__restrict__ marks, float *exact_ws, int L,
+    int heads_token_major, int n_chunks, unsigned n_slabs)
 {
+    constexpr int dk = 16 * kCt;
     __shared__ __align__(16) MainLds sm;
     const unsigned unit = blockIdx.x, slab = unit / unsigned(n_chunks);
-    if (marks[slab] != 0) return;  // left to the exact kernels
+    if (marks[slab] != 0) {  // gates beyond the range of this form
+        exact_slab_share<16 * kCt>(q_all, k_all, v_all, gf_all, gb_all, do_all, dq_all, dk_all, dv_all, dgf_all, dgb_all, exact_ws,
+                                   L, heads_token_major, n_slabs, slab, unit - slab * unsigned(n_chunks), n_chunks);
+        return;
+    }
     const unsigned t0 = (unit - slab * unsigned(n_chunks)) * kC;
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r = lane & 15, g = lane >> 4;
 
@@ -732,14 +771,10 @@ size_t bigla_bwd_chunk_workspace_bytes(long BH, int L)
     return states_bytes(BH, L) + logdec_bytes(BH, L) + marks_bytes(BH);
 }
 
-const int *bigla_bwd_chunk_marks(void *workspace, long BH, int L)
-{
-    return reinterpret_cast<const int *>(static_cast<char *>(workspace) + states_bytes(BH, L) + logdec_bytes(BH, L));
-}
-
 hipError_t bigla_bwd_chunk_launch(const void *q, const void *k, const void *v, const void *g_fwd, const void *g_bwd,
                                   const void *d_out, void *dq, void *dk, void *dv, void *dg_fwd, void *dg_bwd, long BH,
-                                  int L, int dk_, int heads_token_major, void *workspace, hipStream_t stream)
+                                  int L, int dk_, int heads_token_major, void *workspace,
+                                  float *exact_workspace, hipStream_t stream)
 {
     const int n_chunks = chunks_of(L);
     const long units = BH * n_chunks;
@@ -749,7 +784,7 @@ hipError_t bigla_bwd_chunk_launch(const void *q, const void *k, const void *v, c
     ws.states = reinterpret_cast<uint16_t *>(base);
     ws.logdec = reinterpret_cast<float *>(base + states_bytes(BH, L));
     ws.marks = reinterpret_cast<int *>(base + states_bytes(BH, L) + logdec_bytes(BH, L));
-    auto launch = [&](auto ct) {
+    auto launch = [&](auto ct) -> hipError_t {
         constexpr int kCt = decltype(ct)::value;
         const dim3 scan_grid((unsigned)(BH * 4 * (kCt * 256 / kScanThreads)));
         hipLaunchKernelGGL(bigla_bwd_chunk_local_kernel<kCt>, dim3((unsigned)units), dim3(kThreads), 0, stream, q, k, v,
@@ -761,14 +796,11 @@ hipError_t bigla_bwd_chunk_launch(const void *q, const void *k, const void *v, c
             hipLaunchKernelGGL((bigla_bwd_chunk_scan_kernel<8, kCt>), scan_grid, dim3(kScanThreads), 0, stream, ws.states,
                                ws.logdec, ws.marks, n_chunks);
         hipLaunchKernelGGL(bigla_bwd_chunk_main_kernel<kCt>, dim3((unsigned)units), dim3(kThreads), 0, stream, q, k, v,
-                           g_fwd, g_bwd, d_out, dq, dk, dv, dg_fwd, dg_bwd, ws.states, ws.marks, L, heads_token_major,
-                           n_chunks, dk_);
+                           g_fwd, g_bwd, d_out, dq, dk, dv, dg_fwd, dg_bwd, ws.states, ws.marks, exact_workspace, L,
+                           heads_token_major, n_chunks, unsigned(BH));
+        return hipGetLastError();
     };
-    if (dk_ == kD)
-        launch(std::integral_constant<int, 4>{});
-    else
-        launch(std::integral_constant<int, 2>{});
-    return hipGetLastError();
+    return dk_ == kD ? launch(std::integral_constant<int, 4>{}) : launch(std::integral_constant<int, 2>{});
 }
 
 }  // namespace vig

@@ -1198,3 +1198,19 @@ def test_exact_kernels_tile_edges(L, dk, dv, layout):
         bound = (5 * L + 64) * u * size[i] if i < 4 else (6 * L + 64) * u * running
         err = np.abs(got[i].cpu().numpy().astype(np.float64) - ref[i])
         assert np.all(err <= bound + 1e-37), f"{name}: {np.max(err / (bound + 1e-37)):.2f} of the bound"
+
+
+@pytest.mark.parametrize("layout,dk", (("bhld", 64), ("blhd", 64), ("blhd", 32)))
+@pytest.mark.parametrize("L", (32, 64, 65, 128, 129, 192, 193, 256, 257))
+def test_bigla_bwd_slabs_of_both_forms(L, layout, dk):
+    """Lengths of one to five chunks; in the same call a slab that decays by more than the chunkwise form carries in its last chunk only, and one in a
+    single channel of its first, which the workgroups of the main launch evaluate token by token."""
+    w = wl.Workload("bwdslab", B=2, H=3, Hg=1, Wg=L, dk=dk, dv=64, dtype="bf16", gate_mu=0.0)
+    s = _bwd_inputs(w, seed=5 * L + dk)
+    gf, gb = wl.widen(s["g_fwd"], "bf16"), wl.widen(s["g_bwd"], "bf16")
+    gf[0, 1, L - 20:] = -4.0
+    gb[1, 0, :30, dk - 1] = -3.0
+    s["g_fwd"], s["g_bwd"] = wl.store(gf, "bf16"), wl.store(gb, "bf16")
+    _say(f"bigla_bwd both forms L={L} dk={dk} {layout}")
+    worst = _check_bwd(s, "bf16", layout, "auto")
+    _say(f"  worst error / bound = {worst:.3f}")
