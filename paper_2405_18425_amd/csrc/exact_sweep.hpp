@@ -18,8 +18,6 @@
 // tokens through LDS, 54 + 61 us for the gradient) see the measurements at the kernels.
 #pragma once
 
-#include <type_traits>
-
 #include "vig_common.hpp"
 
 namespace vig {
@@ -109,11 +107,16 @@ __device__ __forceinline__ void load_strip(const T *p, float (&f)[kStrip])
     }
 }
 
-// element `n` (32 bits: inside a tile) of a row tensor
+// byte offset (32 bits: inside a tile) of element `n` of a row tensor, and what lies there
 template <typename T>
-__device__ __forceinline__ const T *at(const T *base, unsigned n)
+__device__ __forceinline__ unsigned at_byte(unsigned n)
 {
-    return reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + n * unsigned(sizeof(T)));
+    return n * unsigned(sizeof(T));
+}
+template <typename T>
+__device__ __forceinline__ const T *at(const T *base, unsigned bytes)
+{
+    return reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + bytes);
 }
 
 // Orders this wave's LDS writes before its later LDS reads of what other lanes of the wave wrote (the LDS
@@ -149,6 +152,8 @@ struct Way {
     }
     __device__ __forceinline__ int low(int n) const { return (descending ? tiles - 1 - n : n) * kTile; }
     __device__ __forceinline__ bool ragged(int n) const { return low(n) + kTile > L; }
+    // offset in a tile of its last token
+    __device__ __forceinline__ unsigned last_offset(int n) const { return unsigned(min(kTile - 1, L - 1 - low(n))); }
     // token(n, i) - low(n), clamped to the sequence (always a valid address)
     __device__ __forceinline__ unsigned offset(int n, int i) const
     {
@@ -199,8 +204,8 @@ __device__ __forceinline__ void column_sweep(const T *u_rows, const T *r_rows, c
 #pragma unroll
     for (int i = 0; i < kTile; ++i) {
         const unsigned t = unsigned(descending ? kTile - 1 - i : i) * unsigned(step);
-        off_k[i] = t * DK + unsigned(ch);
-        off_v[i] = t * DV + unsigned(col0);
+        off_k[i] = at_byte<T>(t * DK + unsigned(ch));
+        off_v[i] = at_byte<T>(t * DV + unsigned(col0));
     }
 
     auto half = [&](int first, int last, bool second) __attribute__((always_inline)) {
@@ -209,19 +214,17 @@ __device__ __forceinline__ void column_sweep(const T *u_rows, const T *r_rows, c
             const size_t low = size_t(way.low(n));
             const T *u = u_rows + low * step * DK, *r = r_rows + low * step * DK, *g = g_rows + low * step * DK;
             const T *b = b_rows + low * step * DV;
-            auto load = [&](auto clamped) __attribute__((always_inline)) {
+            // (a token past the sequence repeats the last one's offset, so every address is valid)
+            const unsigned last_token = way.last_offset(n) * unsigned(step);
+            const unsigned end_k = at_byte<T>(last_token * DK + unsigned(ch)), end_v = at_byte<T>(last_token * DV + unsigned(col0));
 #pragma unroll
-                for (int i = 0; i < kTile; ++i) {
-                    const unsigned tk = clamped ? way.offset(n, i) * unsigned(step) * DK + unsigned(ch) : off_k[i];
-                    const unsigned tv = clamped ? way.offset(n, i) * unsigned(step) * DV + unsigned(col0) : off_v[i];
-                    o.u[i] = io<T>::load(at(u, tk));
-                    o.r[i] = io<T>::load(at(r, tk));
-                    o.g[i] = io<T>::load(at(g, tk));
-                    load_strip(at(b, tv), o.b[i]);
-                }
-            };
-            if (way.ragged(n)) load(std::true_type{});
-            else load(std::false_type{});
+            for (int i = 0; i < kTile; ++i) {
+                const unsigned tk = min(off_k[i], end_k), tv = min(off_v[i], end_v);
+                o.u[i] = io<T>::load(at(u, tk));
+                o.r[i] = io<T>::load(at(r, tk));
+                o.g[i] = io<T>::load(at(g, tk));
+                load_strip(at(b, tv), o.b[i]);
+            }
             if (second) {
                 const size_t t = size_t(min(way.token(n, held_i), L - 1));
 #pragma unroll
@@ -354,7 +357,7 @@ __device__ __forceinline__ void row_sweep(const T *q_rows, const T *k_rows, cons
     unsigned off_v[kTile];  // a whole tile's offsets
 #pragma unroll
     for (int i = 0; i < kTile; ++i)
-        off_v[i] = unsigned(descending ? kTile - 1 - i : i) * unsigned(step) * DV + unsigned(col);
+        off_v[i] = at_byte<T>(unsigned(descending ? kTile - 1 - i : i) * unsigned(step) * DV + unsigned(col));
     float S[kStrip] = {0.f, 0.f, 0.f, 0.f}, A[kStrip] = {0.f, 0.f, 0.f, 0.f}, before[kStrip] = {0.f, 0.f, 0.f, 0.f};
 
     auto half = [&](int first, int last, bool second) __attribute__((always_inline)) {
@@ -362,16 +365,13 @@ __device__ __forceinline__ void row_sweep(const T *q_rows, const T *k_rows, cons
             n = min(n, last - 1);  // (past the end: loaded, never used; a branch would make every wait a full one)
             const size_t low = size_t(way.low(n));
             const T *v = v_rows + low * step * DV, *d = do_rows + low * step * DV;
-            auto load = [&](auto clamped) __attribute__((always_inline)) {
+            const unsigned end_v = at_byte<T>(way.last_offset(n) * unsigned(step) * DV + unsigned(col));
 #pragma unroll
-                for (int i = 0; i < kTile; ++i) {
-                    const unsigned t = clamped ? way.offset(n, i) * unsigned(step) * DV + unsigned(col) : off_v[i];
-                    o.v[i] = io<T>::load(at(v, t));
-                    o.d[i] = io<T>::load(at(d, t));
-                }
-            };
-            if (way.ragged(n)) load(std::true_type{});
-            else load(std::false_type{});
+            for (int i = 0; i < kTile; ++i) {
+                const unsigned t = min(off_v[i], end_v);
+                o.v[i] = io<T>::load(at(v, t));
+                o.d[i] = io<T>::load(at(d, t));
+            }
 #pragma unroll
             for (int j = 0; j < kLoads; ++j) {
                 int array, i, row;
