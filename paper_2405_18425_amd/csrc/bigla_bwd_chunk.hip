@@ -18,15 +18,18 @@
 // chunk or s before it; s inside and t after it; s before and t after).  Every sum of dg runs over
 // at most one chunk, so no long-range cancellation enters it; its two prefix/suffix sums are fp32
 // scans over the wave's tokens (DPP row operations) plus the other waves' totals.
-// States come from two small launches before the main one:
+// The four state matrices of every chunk (the state entering it and A', both directions) come from
+//   bigla_bwd_chunk_walk_kernel (a workgroup per slab and matrix, walking the slab's chunks with the running
+//   matrix in registers), where there are enough slabs to fill the chip that way or few chunks to walk;
+// otherwise from two small launches:
 //   1. bigla_bwd_chunk_local_kernel (workgroup per chunk): the chunk's own contributions
 //      U = (k * exp(b_end - b))^T v and W = q~^T do' for both directions, and the chunk totals of
 //      the log-gates;
 //   2. bigla_bwd_chunk_scan_kernel (elementwise over the 64x64 matrices, sequential over the
 //      chunks of a slab): S_in(c+1) = d_c S_in(c) + U_c and A'_c = d_c (W_{c+1} + A'_{c+1}), in
-//      place, fp32 running values, bf16 storage; it also marks the slabs in which some chunk's
-//      total log-decay exceeds 60 nats in some channel;
-//   3. bigla_bwd_chunk_main_kernel (workgroup per chunk): everything above for both directions,
+//      place, fp32 running values, bf16 storage.
+// Either leaves marks of the slabs in which some chunk's total log-decay exceeds 60 nats in some channel.  Then
+//   bigla_bwd_chunk_main_kernel (workgroup per chunk): everything above for both directions,
 //      dq, dk, dv accumulated in registers and written once.
 // exp(-b) grows with the decay accumulated over a chunk, so marked slabs are evaluated token by token (exact_sweep.hpp) by
 // the workgroups of the main launch; gates of the paper's form,
@@ -235,7 +238,8 @@ __device__ __forceinline__ void gate_scan(const Tile &gates, int w, int r, int g
 //     2: backward state entering the chunk from the right
 //     3: backward A' of the chunk (decayed adjoint from the left)
 //   log-decays, per (slab, chunk, direction): the chunk's total log-gate per channel, fp32
-//   slab marks: one int per slab, non-zero when the slab takes the exact form
+//   slab marks: one int per slab, non-zero when the slab takes the exact form (walks: eight ints, where the log-decays
+//     would be)
 struct Workspace {
     uint16_t *states;
     float *logdec;
@@ -425,6 +429,163 @@ __global__ __launch_bounds__(kScanThreads) void bigla_bwd_chunk_scan_kernel(uint
                 *reinterpret_cast<uint2 *>(mat + size_t(c) * 4 * kMat) = pack4(o);
             }
         }
+    }
+}
+
+// ---- passes 1 and 2 in one: a workgroup walks a slab for one of its four matrices --------------------
+// The running matrix stays in registers (fp32) and what enters each chunk is written once; a tensor is read by the two
+// walks that need it, mostly from cache the second time.  A chunk is a chain of a gate scan, exponentials and
+// scalings and then the products; four waves do the first half of chunk n + 1 while four do the second half of chunk n, one
+// barrier per chunk, on tiles that alternate.  Rows are requested two chunks before their turn.
+constexpr int kWalkThreads = 2 * kThreads;
+// The time of the walks goes with the chunks to walk, 1 us each, until about half the compute units have one; the two passes
+// take the same time per chunk at any shape.  A gradient call with the walks against the passes (event times): 48 heads of 4096
+// tokens 181 us against 198, 36: 150 / 158, 30: 138 / 140, 24: 119 / 117, 6: 82 / 60; 30 heads of 1961 tokens 73 / 76, 15: 56 / 50;
+// 48 heads of 1024 tokens 53 / 62, 12: 37 / 37; 384 heads of 196 tokens 94 / 104, 24: 24 / 28, 6: 22 / 25.
+constexpr long kWalkWorkgroups = 112;
+constexpr int kWalkShort = 8;
+
+struct WalkLds {
+    Tile gates[2], x[2], y[2];
+    float total[2][kD];  // the chunk's total log-gate per channel
+};
+
+template <int kCt>
+__global__ __launch_bounds__(kWalkThreads, 4) void bigla_bwd_chunk_walk_kernel(
+    const void *__restrict__ q_all, const void *__restrict__ k_all, const void *__restrict__ v_all,
+    const void *__restrict__ gf_all, const void *__restrict__ gb_all, const void *__restrict__ do_all,
+    uint16_t *__restrict__ states, int *__restrict__ marks /* [slab][direction][wave] */, int L, int heads_token_major,
+    int n_chunks, unsigned n_slabs)
+{
+    constexpr int dk = 16 * kCt;
+    __shared__ __align__(16) WalkLds sm;
+    // a slab's four walks on one XCD (workgroups go round-robin over the eight) and next to each other in time, where
+    // the slabs divide by eight
+    unsigned slab, kind_no;
+    if (n_slabs % 8 == 0) {
+        kind_no = blockIdx.x / 8 % 4;
+        slab = blockIdx.x / 32 * 8 + blockIdx.x % 8;
+    } else {
+        kind_no = blockIdx.x % 4;
+        slab = blockIdx.x / 4;
+    }
+    const int kind = int(kind_no), dir = kind >> 1;
+    const bool adjoint = (kind & 1) != 0, ascending = kind == 0 || kind == 3;
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x)) >> 6;
+    const int w = wave & 3, lane = int(threadIdx.x) & 63, r = lane & 15, g = lane >> 4;
+    // (past the end: the last one once more, loaded and not used; without a branch, which would make every wait a full one)
+    const int chunk0 = ascending ? 0 : n_chunks - 1, chunk_step = ascending ? 1 : -1;
+    auto chunk_of = [&](int n) { return chunk0 + chunk_step * min(n, n_chunks - 1); };
+
+    if (wave < 4) {
+        const size_t first = slab_first_row(slab, L, heads_token_major);
+        const SlabRows xs = slab_rows(adjoint ? q_all : k_all, first, L, heads_token_major, dk);
+        const SlabRows ys = slab_rows(adjoint ? do_all : v_all, first, L, heads_token_major);
+        const SlabRows gs = slab_rows(dir == 0 ? gf_all : gb_all, first, L, heads_token_major, dk);
+        auto fetch = [&](const SlabRows &rows, int n) { return fetch_rows(rows, unsigned(chunk_of(n)) * kC, w, lane); };
+        bf16x8 tri[2];
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) tri[kk] = dir == 0 ? tri_frag<kLe>(kk, g, 16 * w + r) : tri_frag<kGe>(kk, g, 16 * w + r);
+        const bf16x8 ones = __builtin_bit_cast(bf16x8, make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u));
+        // keys of a state decay to the chunk's far edge, exp(total - b); queries of an adjoint from its near edge, exp(b),
+        // and carry the 1/2 of d_out / 2
+        const float of_scan = adjoint ? kLog2e : -kLog2e, of_total = adjoint ? 0.f : kLog2e, bias = adjoint ? -1.f : 0.f;
+        // gates in tile gates[buf], the wave's own rows of x in tile x[buf] -> scaled x and the totals in tiles [buf]
+        auto scale_rows = [&](int buf) __attribute__((always_inline)) {
+            uint2 own[4];
+            take_own(sm.x[buf], w, r, g, own);
+#pragma unroll
+            for (int ct = 0; ct < kCt; ++ct) {
+                const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+                const bf16x8 a0 = col_frag(sm.gates[buf], 16 * ct, 0, r, g), a1 = col_frag(sm.gates[buf], 16 * ct, 1, r, g);
+                const f32x4 b = mfma(a1, tri[1], mfma(a0, tri[0], zero)), T = mfma(a1, ones, mfma(a0, ones, zero));
+                f32x4 x = unpack4(own[ct]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] *= fast_exp2(fmaf(of_scan, b[e], fmaf(of_total, T[e], bias)));
+                put_own(sm.x[buf], w, r, g, ct, x);
+                if (w == 0 && r == 0) *reinterpret_cast<f32x4 *>(&sm.total[buf][16 * ct + 4 * g]) = T;
+            }
+        };
+        ChunkRows cg[2], cx[2], cy[2];
+        cg[0] = fetch(gs, 0);
+        put_rows<false>(sm.gates[0], cg[0], w, lane);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            cx[j] = fetch(xs, j);
+            cy[j] = fetch(ys, j);
+            cg[j ^ 1] = fetch(gs, j + 1);
+        }
+        // chunk n + 1 into the tiles of parity j ^ 1, the gates of chunk n + 2 into those of parity j, and the next requests
+        auto advance = [&](int j, int n) __attribute__((always_inline)) {
+            put_rows<false>(sm.x[j ^ 1], cx[j ^ 1], w, lane);
+            put_rows<false>(sm.y[j ^ 1], cy[j ^ 1], w, lane);
+            put_rows<false>(sm.gates[j], cg[j], w, lane);
+            cx[j ^ 1] = fetch(xs, n + 3);
+            cy[j ^ 1] = fetch(ys, n + 3);
+            cg[j] = fetch(gs, n + 4);
+            scale_rows(j ^ 1);
+        };
+        __syncthreads();
+        advance(1, -1);
+        // (what is prepared past the last chunk is a repetition of it, unused; two chunks per turn without a way out in
+        // between, which would make the waits of the first half full ones)
+        for (int n = 0; n + 1 < n_chunks; n += 2) {
+            __syncthreads();
+            advance(0, n);
+            __syncthreads();
+            advance(1, n + 1);
+        }
+        if (n_chunks & 1) __syncthreads();
+        return;
+    }
+
+    const int it = kCt == 4 ? w : (w & 1);        // the wave's row tile of the matrix
+    const int mt0 = kCt == 4 ? 0 : 2 * (w >> 1);  // its first column tile
+    const int row = 16 * it + r;
+    uint16_t *mats = states + (size_t(slab) * unsigned(n_chunks) * 4 + kind_no) * kMat + row * kD + 4 * g;
+    bool beyond = false;
+    f32x4 s[kCt];
+#pragma unroll
+    for (int mi = 0; mi < kCt; ++mi) s[mi] = f32x4{0.f, 0.f, 0.f, 0.f};
+    __syncthreads();
+    auto step = [&](int j, int n) __attribute__((always_inline)) {
+        const float total = sm.total[j][row], d = fast_exp2(total * kLog2e);
+        beyond = beyond || -total > kFastRange;
+        uint16_t *mat = mats + size_t(chunk_of(n)) * 4 * kMat;
+        bf16x8 xf[2];
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) xf[kk] = col_frag(sm.x[j], 16 * it, kk, r, g);
+#pragma unroll
+        for (int mi = 0; mi < kCt; ++mi) {
+            const int mt = mt0 + mi;
+            f32x4 t, o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                t[e] = d * s[mi][e];
+                o[e] = adjoint ? t[e] : s[mi][e];
+            }
+            *reinterpret_cast<uint2 *>(mat + 16 * mt) = pack4(o);
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk) t = mfma(col_frag(sm.y[j], 16 * mt, kk, r, g), xf[kk], t);
+            s[mi] = t;
+        }
+    };
+    int n = 0;
+    for (; n + 1 < n_chunks; n += 2) {
+        __syncthreads();
+        step(0, n);
+        __syncthreads();
+        step(1, n + 1);
+    }
+    if (n < n_chunks) {
+        __syncthreads();
+        step(0, n);
+    }
+    // mark the slab when some chunk decays by more than the fast form can carry (a NaN gate total compares false and
+    // leaves the slab to this path, whose outputs are then NaN too): an int per direction and wave
+    if (!adjoint) {
+        const bool any = __any(beyond);
+        if (lane == 0) marks[8 * slab + 4 * dir + w] = any ? 1 : 0;
     }
 }
 
@@ -715,13 +876,20 @@ __global__ __launch_bounds__(kThreads, 2) void bigla_bwd_chunk_main_kernel(
     const void *__restrict__ q_all, const void *__restrict__ k_all, const void *__restrict__ v_all,
     const void *__restrict__ gf_all, const void *__restrict__ gb_all, const void *__restrict__ do_all,
     void *__restrict__ dq_all, void *__restrict__ dk_all, void *__restrict__ dv_all, void *__restrict__ dgf_all,
-    void *__restrict__ dgb_all, const uint16_t *__restrict__ states, const int *__restrict__ marks, float *exact_ws, int L,
+    void *__restrict__ dgb_all, const uint16_t *__restrict__ states, const int *__restrict__ marks, int marks_per_slab, float *exact_ws, int L,
     int heads_token_major, int n_chunks, unsigned n_slabs)
 {
     constexpr int dk = 16 * kCt;
     __shared__ __align__(16) MainLds sm;
     const unsigned unit = blockIdx.x, slab = unit / unsigned(n_chunks);
-    if (marks[slab] != 0) {  // gates beyond the range of this form
+    int marked;
+    if (marks_per_slab == 8) {
+        const int4 a = reinterpret_cast<const int4 *>(marks)[2 * slab], b = reinterpret_cast<const int4 *>(marks)[2 * slab + 1];
+        marked = (a.x | a.y | a.z | a.w) | (b.x | b.y | b.z | b.w);
+    } else {
+        marked = marks[slab];
+    }
+    if (marked != 0) {  // gates beyond the range of this form
         exact_slab_share<16 * kCt>(q_all, k_all, v_all, gf_all, gb_all, do_all, dq_all, dk_all, dv_all, dgf_all, dgb_all, exact_ws,
                                    L, heads_token_major, n_slabs, slab, unit - slab * unsigned(n_chunks), n_chunks);
         return;
@@ -786,17 +954,26 @@ hipError_t bigla_bwd_chunk_launch(const void *q, const void *k, const void *v, c
     ws.marks = reinterpret_cast<int *>(base + states_bytes(BH, L) + logdec_bytes(BH, L));
     auto launch = [&](auto ct) -> hipError_t {
         constexpr int kCt = decltype(ct)::value;
-        const dim3 scan_grid((unsigned)(BH * 4 * (kCt * 256 / kScanThreads)));
-        hipLaunchKernelGGL(bigla_bwd_chunk_local_kernel<kCt>, dim3((unsigned)units), dim3(kThreads), 0, stream, q, k, v,
-                           g_fwd, g_bwd, d_out, ws.states, ws.logdec, L, heads_token_major, n_chunks, dk_);
-        if (n_chunks > 16)
-            hipLaunchKernelGGL((bigla_bwd_chunk_scan_kernel<32, kCt>), scan_grid, dim3(kScanThreads), 0, stream, ws.states,
-                               ws.logdec, ws.marks, n_chunks);
-        else
-            hipLaunchKernelGGL((bigla_bwd_chunk_scan_kernel<8, kCt>), scan_grid, dim3(kScanThreads), 0, stream, ws.states,
-                               ws.logdec, ws.marks, n_chunks);
+        // Walks as long as there are enough of them, or few chunks to walk; else a workgroup per chunk and a pass over the
+        // matrices.
+        const bool walk = BH * 4 >= kWalkWorkgroups || n_chunks <= kWalkShort;
+        int *marks = walk ? reinterpret_cast<int *>(ws.logdec) : ws.marks;
+        if (walk) {
+            hipLaunchKernelGGL(bigla_bwd_chunk_walk_kernel<kCt>, dim3((unsigned)(BH * 4)), dim3(kWalkThreads), 0, stream, q, k, v,
+                               g_fwd, g_bwd, d_out, ws.states, marks, L, heads_token_major, n_chunks, unsigned(BH));
+        } else {
+            const dim3 scan_grid((unsigned)(BH * 4 * (kCt * 256 / kScanThreads)));
+            hipLaunchKernelGGL(bigla_bwd_chunk_local_kernel<kCt>, dim3((unsigned)units), dim3(kThreads), 0, stream, q, k, v,
+                               g_fwd, g_bwd, d_out, ws.states, ws.logdec, L, heads_token_major, n_chunks, dk_);
+            if (n_chunks > 16)
+                hipLaunchKernelGGL((bigla_bwd_chunk_scan_kernel<32, kCt>), scan_grid, dim3(kScanThreads), 0, stream, ws.states,
+                                   ws.logdec, ws.marks, n_chunks);
+            else
+                hipLaunchKernelGGL((bigla_bwd_chunk_scan_kernel<8, kCt>), scan_grid, dim3(kScanThreads), 0, stream, ws.states,
+                                   ws.logdec, ws.marks, n_chunks);
+        }
         hipLaunchKernelGGL(bigla_bwd_chunk_main_kernel<kCt>, dim3((unsigned)units), dim3(kThreads), 0, stream, q, k, v,
-                           g_fwd, g_bwd, d_out, dq, dk, dv, dg_fwd, dg_bwd, ws.states, ws.marks, exact_workspace, L,
+                           g_fwd, g_bwd, d_out, dq, dk, dv, dg_fwd, dg_bwd, ws.states, marks, walk ? 8 : 1, exact_workspace, L,
                            heads_token_major, n_chunks, unsigned(BH));
         return hipGetLastError();
     };
