@@ -1,9 +1,9 @@
 // Exact fp32 evaluation of the BiGLA recurrences (Section 4.2.1, Eq. (BiGLA)), token by token.
 //
 // This is the fp32 path of the library and the path for every head shape the chunkwise MFMA
-// kernels do not cover.  A pair of waves owns a strip of columns of one (batch, head) slab's state and
-// walks the two directions at the same time from the two ends (exact_sweep.hpp); each parks its partial
-// outputs of the first half as fp32 and writes (o_fwd + o_bwd)/2 for the other half.
+// kernels do not cover.  For few slabs a pair of waves owns a strip of columns of one (batch, head)
+// slab's state and walks the two directions at the same time from the two ends (exact_sweep.hpp); each parks its partial
+// outputs of the first half as fp32 and writes (o_fwd + o_bwd)/2 for the other half.  For many, a workgroup owns a slab.
 #include "exact_sweep.hpp"
 #include "vig_common.hpp"
 #include "vig_kernels.hpp"
@@ -15,6 +15,93 @@ namespace vig {
 
 namespace {
 
+// ---- many slabs: a workgroup per slab --------------------------------------------------------------
+// One direction after the other; thread (j, s) holds rows [s*DK/4, (s+1)*DK/4) of column j, so a token costs DK/4 fused
+// decay-update-readout steps per thread plus a 4-lane reduction, and a token's rows are loaded, and its gates
+// exponentiated, once per slab (a pair of waves does that for every strip of four columns again).  Tokens are staged
+// through LDS 16 at a time.
+namespace staged {
+
+constexpr int kSplit = 4;   // threads sharing one state column
+constexpr int kTile = 16;   // tokens staged per LDS tile
+
+template <typename T, int DK, int DV>
+__global__ __launch_bounds__(DV *kSplit) void bigla_recurrent_staged_kernel(
+    const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, const T *__restrict__ g_fwd,
+    const T *__restrict__ g_bwd, T *out, float *o_fwd /* may alias out (fp32) */, int L,
+    int heads_token_major /* 0: [B,H,L,d]; H: [B,L,H,d] */, bool o_fwd_in_out)
+{
+    constexpr int R = DK / kSplit;
+    constexpr int NT = DV * kSplit;
+    __shared__ float sq[kTile][DK], sk[kTile][DK], sa[kTile][DK], sv[kTile][DV];
+
+    const int tid = threadIdx.x;
+    const int j = tid / kSplit, s = tid % kSplit, c0 = s * R;
+    const size_t slab = blockIdx.x;
+    // first row of the slab and distance between its tokens, in rows of the tensor
+    const size_t row0 = slab_first_row(unsigned(slab), L, heads_token_major);
+    const size_t step = heads_token_major ? heads_token_major : 1;
+    q += row0 * DK;
+    k += row0 * DK;
+    g_fwd += row0 * DK;
+    g_bwd += row0 * DK;
+    v += row0 * DV;
+    out += row0 * DV;
+    // the fp32 side buffer is dense [slab][L][DV]; when the partial sums live in `out` they follow it
+    o_fwd += (o_fwd_in_out ? row0 : slab * size_t(L)) * DV;
+    const size_t fwd_step = o_fwd_in_out ? step : 1;
+
+    float S[R];
+
+    for (int dir = 0; dir < 2; ++dir) {
+        const T *g = dir == 0 ? g_fwd : g_bwd;
+#pragma unroll
+        for (int r = 0; r < R; ++r) S[r] = 0.f;
+        const int ntiles = (L + kTile - 1) / kTile;
+        for (int it = 0; it < ntiles; ++it) {
+            const int tile = dir == 0 ? it : ntiles - 1 - it;
+            const int t0 = tile * kTile;
+            const int n = min(kTile, L - t0);
+            __syncthreads();
+            for (int e = tid; e < n * DK; e += NT) {
+                const int tt = e / DK, c = e % DK;
+                const size_t off = size_t(t0 + tt) * step * DK + c;
+                sq[tt][c] = io<T>::load(q + off);
+                sk[tt][c] = io<T>::load(k + off);
+                sa[tt][c] = expf(io<T>::load(g + off));
+            }
+            for (int e = tid; e < n * DV; e += NT) {
+                const int tt = e / DV, c = e % DV;
+                sv[tt][c] = io<T>::load(v + size_t(t0 + tt) * step * DV + c);
+            }
+            __syncthreads();
+            for (int i = 0; i < n; ++i) {
+                const int tt = dir == 0 ? i : n - 1 - i;
+                const float vj = sv[tt][j];
+                float acc = 0.f;
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    // S_t = diag(alpha_t) S_{t -/+ 1} + k_t^T v_t ;  o_t = q_t S_t
+                    S[r] = fmaf(sa[tt][c0 + r], S[r], sk[tt][c0 + r] * vj);
+                    acc = fmaf(sq[tt][c0 + r], S[r], acc);
+                }
+                acc += __shfl_xor(acc, 1);
+                acc += __shfl_xor(acc, 2);
+                if (s == 0) {
+                    const size_t o = size_t(t0 + tt) * step * DV + j, of = size_t(t0 + tt) * fwd_step * DV + j;
+                    if (dir == 0)
+                        o_fwd[of] = acc;
+                    else
+                        io<T>::store(out + o, 0.5f * (o_fwd[of] + acc));
+                }
+            }
+        }
+    }
+}
+
+}  // namespace staged
+
+// ---- few slabs: a pair of waves per strip of columns -------------------------------------------------
 // kPairs: column strips of one slab per workgroup, so that they find the slab's rows in the compute
 // unit's own cache.
 template <typename T, int DK, int DV, int kPairs>
@@ -37,11 +124,24 @@ __global__ __launch_bounds__(128 * kPairs, 1) void bigla_recurrent_kernel(
                                    0.5f, lane);
 }
 
+// A pair of waves per strip does about 1.7 times the work of the workgroup per slab, in a sixth of the time while the chip
+// is not full of strips: 16 slabs of 196 tokens, 64 x 64, fp32: 25 us against 191; 192: 109 / 241; 256: 137 / 246; 1024 (16384
+// strips): 550 / 323.  Short sequences fill it less well: slabs of 20 tokens in bf16, 256 (4096 strips): 32 / 26 us, 1024: 123 / 34.
+inline bool take_pairs(long strips, int L) { return strips <= (L >= 64 ? 5120 : 2048); }
+
 template <typename T, int DK, int DV>
 hipError_t launch(const void *q, const void *k, const void *v, const void *gf, const void *gb, void *out,
                   float *o_part, int BH, int L, int heads_token_major, hipStream_t stream)
 {
     constexpr int kBlocks = DV / (kStrip * (64 / DK));  // column strips of a slab
+    if (!take_pairs(long(BH) * kBlocks, L)) {
+        LaunchTimer timer(kKernelRecurrent, stream);
+        hipLaunchKernelGGL((staged::bigla_recurrent_staged_kernel<T, DK, DV>), dim3(BH), dim3(DV * staged::kSplit), 0, stream,
+                           static_cast<const T *>(q), static_cast<const T *>(k), static_cast<const T *>(v),
+                           static_cast<const T *>(gf), static_cast<const T *>(gb), static_cast<T *>(out), o_part, L,
+                           heads_token_major, static_cast<void *>(o_part) == out);
+        return hipGetLastError();
+    }
     const bool part_in_out = static_cast<void *>(o_part) == out;
     auto run = [&](auto pairs) -> hipError_t {
         constexpr int kPairs = decltype(pairs)::value;

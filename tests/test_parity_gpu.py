@@ -1173,7 +1173,7 @@ def test_exact_kernels_tile_edges(L, dk, dv, layout):
     import torch
     from paper_2405_18425_amd import binding as vb
 
-    B, H = (2, 3) if L > 16 else (3, 43)  # the many short slabs: two pairs of waves per workgroup
+    B, H = (2, 3) if L > 16 else (3, 43)  # the many short slabs: two pairs of waves, or one slab, per workgroup
     _say(f"exact kernels L{L} dk{dk} dv{dv} {layout}")
     w = wl.Workload("exact", B=B, H=H, Hg=1, Wg=L, dk=dk, dv=dv, dtype="f32", gate_mu=-1.0)
     s = wl.generate(w, seed=L + dk + 3 * dv, tensors=("q", "k", "v", "g_fwd", "g_bwd"))
