@@ -1141,7 +1141,7 @@ size_t four_wave_bytes(long BH, int L)
 size_t bigla_chunk_workspace_bytes(long BH, int L)
 {
     const size_t a = four_wave_bytes(BH, L), b = bigla_chunk_ws_workspace_bytes(BH, L);
-    const size_t c = bigla_short_applicable(L) ? bigla_short_workspace_bytes(BH) : 0;
+    const size_t c = bigla_short_applicable(BH, L) ? bigla_short_workspace_bytes(BH) : 0;
     return a > b ? (a > c ? a : c) : (b > c ? b : c);
 }
 
@@ -1213,7 +1213,7 @@ hipError_t bigla_chunk_set_alias(int on)
 
 bool bigla_chunk_gated_selectable(long BH, int L, int dk)
 {
-    return !g_alias_on && (bigla_short_applicable(L) ? (dk == kD || dk == kD / 2) : bigla_chunk_ws_applicable(BH, L, dk));
+    return !g_alias_on && (bigla_short_applicable(BH, L) ? (dk == kD || dk == kD / 2) : bigla_chunk_ws_applicable(BH, L, dk));
 }
 
 // bigla_chunk_launch with the first pass over the keys (the state pass of the eight-wave kernels, or the one pass of
@@ -1231,7 +1231,7 @@ hipError_t bigla_chunk_gated_launch(const void *q, const void *k, const void *v,
     gs.bias = static_cast<const uint16_t *>(bias);
     gs.inv_tau = 1.f / tau;
     gs.n_heads = n_heads;
-    if (bigla_short_applicable(L))
+    if (bigla_short_applicable(BH, L))
         return bigla_short_launch(q, k, v, g_fwd, g_bwd, out, BH, L, dk, heads_token_major, workspace, stream, &gs);
     return bigla_chunk_ws_launch(q, k, v, g_fwd, g_bwd, out, BH, L, dk, heads_token_major, workspace, stream, &gs);
 }
@@ -1250,7 +1250,7 @@ hipError_t bigla_chunk_launch(const void *q, const void *k, const void *v, const
     // kernels: 0 = the faster set for the shape (the eight-wave kernels where they apply), 1 = four-wave,
     // 2 = eight-wave (an error where they do not apply), 3 = four-wave with one workgroup per slab
     // (with a fusion: grids narrow enough for the eight-wave epilogue's ring of conv-input rows)
-    if (kernels == 0 && !fusion && bigla_short_applicable(L))
+    if (kernels == 0 && !fusion && bigla_short_applicable(BH, L))
         return bigla_short_launch(q, k, v, g_fwd, g_bwd, out, BH, L, dk, heads_token_major, workspace, stream);
     const bool ws_ok = bigla_chunk_ws_applicable(BH, L, dk) && (!fusion || (fusion->Wg < kXHalo && L < (1 << 22)));
     if (kernels == 2 && !ws_ok) return hipErrorInvalidValue;

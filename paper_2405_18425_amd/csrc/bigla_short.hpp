@@ -120,7 +120,13 @@ __device__ __attribute__((noinline)) void short_slab_safe(
     const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
     const SlabIo<kTm, kDk> io(q_all, k_all, v_all, gf_all, gb_all, out_all, slab, L, heads);
     const ShortSlab<kDk> at(slot, n_tiles);
-    auto factors = [&](int dir, int tile) { return eb + (dir * kShortTiles + tile) * kD; };
+    // (as global memory: a generic pointer's loads count with those of LDS, and every wait for LDS would wait for them)
+    typedef __attribute__((address_space(1))) f32x4 Factors;
+    auto factors = [&](int dir, int tile) { return (Factors *)(eb + (dir * kShortTiles + tile) * kD) + 2 * g; };
+    auto load_factors = [&](int dir, int tile, f32x4 (&f)[4]) {
+        const Factors *p = factors(dir, tile);
+        f[0] = p[0]; f[1] = p[1]; f[2] = p[8]; f[3] = p[9];
+    };
 #pragma unroll 1
     for (int T = 0; T < 2; ++T) {
         const int tile = 2 * w + T;
@@ -133,7 +139,11 @@ __device__ __attribute__((noinline)) void short_slab_safe(
                 gate_factors_state<0>(short_operand_rows<kDk>(io.gf, io.key_pitch, tile, r, g), F, EB);
             else
                 gate_factors_state<1>(short_operand_rows<kDk>(io.gb, io.key_pitch, tile, r, g), F, EB);
-            if (r == 0) store_chan16(factors(dir, tile), g, EB);
+            if (r == 0) {
+                Factors *p = factors(dir, tile);
+#pragma unroll
+                for (int h = 0; h < 4; ++h) p[8 * (h >> 1) + (h & 1)] = f32x4{EB[4 * h], EB[4 * h + 1], EB[4 * h + 2], EB[4 * h + 3]};
+            }
 #pragma unroll
             for (int n = 0; n < 16; ++n) F[n] *= kf[n];
             const unsigned base = (dir == 0 ? at.kf : at.kb) + tile * 16 * ShortSlab<kDk>::kKeyBytes;
@@ -206,17 +216,23 @@ __device__ __attribute__((noinline)) void short_slab_safe(
 #pragma unroll
         for (int dir = 0; dir < 2; ++dir) {
             const unsigned base = dir == 0 ? at.kf : at.kb;
+            const int step = dir == 0 ? -1 : 1, last = dir == 0 ? 0 : n_tiles - 1;
+            f32x4 ahead[4];  // the next tile's factors, requested a tile ahead
+            load_factors(dir, dir == 0 ? max(tile - 1, 0) : min(tile + 1, last), ahead);
 #pragma unroll 1
-            for (int I = dir == 0 ? tile - 1 : tile + 1; I >= 0 && I < n_tiles; I += dir == 0 ? -1 : 1) {
+            for (int I = tile + step; I >= 0 && I < n_tiles; I += step) {
+                f32x4 now[4];
+#pragma unroll
+                for (int h = 0; h < 4; ++h) now[h] = ahead[h];
+                load_factors(dir, I == last ? I : I + step, ahead);
                 f32x4 p = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int kk = 0; kk < kKs; ++kk)
                     p = mfma(short_b128(base + I * 16 * ShortSlab<kDk>::kKeyBytes + key_place<2 * kDk>(r, 4 * kk + g)),
                              pack8(cum[dir] + 8 * kk), p);
                 add_tile(p, I);
-                load_chan16(factors(dir, I), g, tmp);
 #pragma unroll
-                for (int n = 0; n < 16; ++n) cum[dir][n] *= tmp[n];
+                for (int n = 0; n < 16; ++n) cum[dir][n] *= now[n >> 2][n & 3];
             }
         }
         short_store(io.out, io.pitch, tile, r, g, O);
@@ -585,12 +601,14 @@ __global__ __launch_bounds__(64 * kShortWaves, 4) void bigla_short_kernel(
 
 }  // namespace
 
-// At every length up to 256 and every number of slabs it was the faster one: per call in a captured graph, 6 slabs of 80 /
-// 196 / 256 tokens 8.4 / 10.8 / 11.8 us against 11.3 / 12.4 / 12.4 with the eight-wave kernels, 96 slabs 8.7 / 11.4 / 12.4
-// against 12.3 / 15.9 / 15.9; 384 slabs of 49 / 128 / 196 / 256 tokens 9.3 / 12.3 / 22.0 / 28.5 us against 26.5 / 16.9 /
-// 28.7 / 28.6 with the four-wave kernels.  The lead shrinks where a workgroup has a compute unit to itself (over 208
-// tokens), and the score matrix grows with the square of the length: beyond 256 tokens the sequence is chunked.
-bool bigla_short_applicable(int L) { return L <= kShortTokens; }
+// With gates that decay by up to 16 nats in 64 tokens it is the faster one at every length up to 256 and every number of
+// slabs: per call in a captured graph, 48 slabs of 100 / 196 / 256 tokens 10.1 / 11.7 / 13.0 us against 12.0 / 14.1 / 14.4 with the
+// eight-wave kernels; 384 slabs 12.7 / 24.8 / 32.1 us against 18.2 / 33.0 / 34.7 with the four-wave kernels.  Beyond 16 nats it takes
+// the range-safe form, as the four-wave kernels do (at -0.3 a step, 192 and 384 slabs of 196 tokens 34 and 55 us against 67 and
+// 96), but the eight-wave kernels stay in the fast form up to 60: 48 slabs 28 us against 14.  Whose gates those are is known
+// on the device only, so calls that the eight-wave kernels can take (two chunks or more, fewer than 128 slabs) stay with them.
+// The score matrix grows with the square of the length: beyond 256 tokens the sequence is chunked.
+bool bigla_short_applicable(long BH, int L) { return L <= kShortTokens && (BH >= 128 || L <= kC); }
 
 // bytes of workspace: the range-safe form's whole-tile decay factors
 size_t bigla_short_workspace_bytes(long BH) { return size_t(BH) * 2 * kShortTiles * kD * sizeof(float); }

@@ -300,7 +300,7 @@ int bigla_locality_fwd(const void *q, const void *k, const void *v, const void *
         return VIG_ERR_ALIGN;
     const size_t need = vig::bigla_chunk_workspace_bytes(long(B) * H, L);
     if (need > 0 && (!workspace || workspace_bytes < need)) return VIG_ERR_WORKSPACE;
-    if (vig::bigla_short_applicable(L)) {
+    if (vig::bigla_short_applicable(long(B) * H, L)) {
         // one launch takes the whole sequence as one chunk; the locality kernel then blends its output in place (a thread
         // reads the o_global of the pixels that it writes, before it writes them)
         const int st = bigla_fwd_layout(q, k, v, g_fwd, g_bwd, out, B, H, L, dk, dv, dtype, layout, workspace, workspace_bytes, stream);

@@ -30,7 +30,7 @@ struct LocalityFusion {
 // producer/consumer kernels (bigla_chunk_ws_selectable says where they apply; never with a fusion).
 bool bigla_chunk_ws_selectable(long BH, int L, int dk);
 // sequences that kernels = 0 takes as one chunk, in one launch (where bigla_chunk_supported)
-bool bigla_short_applicable(int L);
+bool bigla_short_applicable(long BH, int L);
 // measurement aid: every slab of the chunkwise forward kernels reads slab 0's q, k, v and gates (synchronous)
 hipError_t bigla_chunk_set_alias(int on);
 hipError_t bigla_chunk_launch(const void *q, const void *k, const void *v, const void *g_fwd, const void *g_bwd,

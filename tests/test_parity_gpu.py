@@ -1109,7 +1109,8 @@ def test_bigla_one_chunk_sequences(L, layout, dk):
     import torch
     from paper_2405_18425_amd import binding as vb
 
-    w = wl.Workload("one_chunk", B=5, H=1, Hg=1, Wg=L, dk=dk, dv=64, dtype="bf16", gate_mu=-1.0)
+    # (longer ones from 128 slabs on: 130, the last workgroup not full either)
+    w = wl.Workload("one_chunk", B=5, H=1 if L <= 64 else 26, Hg=1, Wg=L, dk=dk, dv=64, dtype="bf16", gate_mu=-1.0)
     _say(f"bigla one chunk L{L} {layout} dk{dk}")
     s = wl.generate(w, seed=L + dk, tensors=("q", "k", "v", "g_fwd", "g_bwd"))
     r = np.random.default_rng(L)
@@ -1138,7 +1139,7 @@ def test_gated_bigla_one_chunk_sequences(L, layout, dk, bias_mu):
     import torch
     from paper_2405_18425_amd import binding as vb
 
-    B, H, D = 3, 3, 192
+    B, H, D = 3 if L <= 64 else 43, 3, 192
     _say(f"gated one chunk L{L} {layout} dk{dk}")
     st = wl.generate_gate_inputs(B, L, D, H, dk, "bf16", seed=L, bias_mu=bias_mu)
     s = wl.generate(wl.Workload("gated", B=B, H=H, Hg=1, Wg=L, dk=dk, dv=64, dtype="bf16", gate_mu=0.0), seed=L,
