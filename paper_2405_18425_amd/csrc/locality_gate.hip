@@ -223,10 +223,12 @@ hipError_t launch(const void *x, const void *w, const void *bias, const void *z,
     // than one strip (1024 slabs of 7 x 7: 11.3 / 10.6 / 11.6); then 4 rows while every compute unit has a workgroup
     // (32 slabs of 56 x 56: 14.7 / 14.6 / 15.2; 80 of 28 x 28: 12.7 / 11.6 / 12.5; 15 of 37 x 53: 10.1 / 7.7 / 7.9), and 2 rows
     // for small problems (6 slabs of 14 x 14: 6.8 / 6.9 / 6.5; event times, about 3 us above the kernel's own).
+    // Strips of 4 that hang far over the grid's end (heights of 9, 10, 17) lose more than they save: 2 rows where 4 cover
+    // over 15 % more rows (a call with 160 slabs of 9 x 33: 35.3 us with 4 rows, 34.4 with 2).
     const long slabs = long(B) * H;
     auto blocks = [&](int rs) { return slabs * ((long((Hg + rs - 1) / rs) * Wg * CG + kThreads - 1) / kThreads); };
     if (Hg > 8 && blocks(8) >= 1024) return launch_rs<T, DV, 8>(x, w, bias, z, og, out, slabs, H, Hg, Wg, token_major, stream);
-    if (blocks(4) >= 256) return launch_rs<T, DV, 4>(x, w, bias, z, og, out, slabs, H, Hg, Wg, token_major, stream);
+    if (blocks(4) >= 256 && 20 * ((Hg + 3) / 4 * 4) <= 23 * ((Hg + 1) / 2 * 2)) return launch_rs<T, DV, 4>(x, w, bias, z, og, out, slabs, H, Hg, Wg, token_major, stream);
     return launch_rs<T, DV, 2>(x, w, bias, z, og, out, slabs, H, Hg, Wg, token_major, stream);
 }
 
