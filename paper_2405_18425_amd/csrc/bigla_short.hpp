@@ -114,7 +114,7 @@ __device__ __forceinline__ unsigned short_value_off(int jt, int r, int g)
 template <int kDk, bool kTm>
 __device__ __attribute__((noinline)) void short_slab_safe(
     const uint16_t *q_all, const uint16_t *k_all, const uint16_t *v_all, const uint16_t *gf_all, const uint16_t *gb_all,
-    uint16_t *out_all, float *eb, long slab, int slot, int w, int L, int n_tiles, int heads)
+    uint16_t *out_all, float *eb, long slab, int slot, int w, int n_waves, int L, int n_tiles, int heads)
 {
     constexpr int kKs = kDk / 32;
     const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
@@ -128,9 +128,7 @@ __device__ __attribute__((noinline)) void short_slab_safe(
         f[0] = p[0]; f[1] = p[1]; f[2] = p[8]; f[3] = p[9];
     };
 #pragma unroll 1
-    for (int T = 0; T < 2; ++T) {
-        const int tile = 2 * w + T;
-        if (tile >= n_tiles) break;
+    for (int tile = w; tile < n_tiles; tile += n_waves) {
         float kf[16], F[16], EB[16];
         unpack16(short_operand_rows<kDk>(io.k, io.key_pitch, tile, r, g), kf);
 #pragma unroll
@@ -153,15 +151,11 @@ __device__ __attribute__((noinline)) void short_slab_safe(
         }
     }
 #pragma unroll 1
-    for (int T = 0; T < 2; ++T) {
-        const int tile = 2 * w + T;
-        if (tile < n_tiles) short_put_values(at.v, tile, lane, load_rows(io.v, lane_rows<kD>(0, lane, io.pitch), 16u * tile));
-    }
+    for (int tile = w; tile < n_tiles; tile += n_waves)
+        short_put_values(at.v, tile, lane, load_rows(io.v, lane_rows<kD>(0, lane, io.pitch), 16u * tile));
     __syncthreads();  // keys, values and factors visible
 #pragma unroll 1
-    for (int T = 0; T < 2; ++T) {
-        const int tile = 2 * w + T;
-        if (tile >= n_tiles) break;
+    for (int tile = w; tile < n_tiles; tile += n_waves) {
         float qf[16], kf[16], cum[2][16], tmp[16];
         unpack16(short_operand_rows<kDk>(io.q, io.key_pitch, tile, r, g), qf);
         unpack16(short_operand_rows<kDk>(io.k, io.key_pitch, tile, r, g), kf);
@@ -245,7 +239,7 @@ template <int kDk, bool kTm, bool kGates>
 __global__ __launch_bounds__(64 * kShortWaves, 4) void bigla_short_kernel(
     const uint16_t *__restrict__ q_all, const uint16_t *__restrict__ k_all, const uint16_t *__restrict__ v_all,
     const uint16_t *gf_all, const uint16_t *gb_all, uint16_t *__restrict__ out_all, float *__restrict__ eb_all, int L,
-    int n_tiles, int slab_waves, int slots, long n_slabs, int heads, GateSource gs)
+    int n_tiles, int slab_waves, int waves /* per slab */, int slots, long n_slabs, int heads, GateSource gs)
 {
     constexpr int kKs = kDk / 32;        // K-steps of a contraction over channels
     constexpr int kCt = kDk / 16;        // 16-channel tiles
@@ -253,7 +247,7 @@ __global__ __launch_bounds__(64 * kShortWaves, 4) void bigla_short_kernel(
     constexpr int kGateLoads = kDk / 32;  // 16-byte loads per lane for the 16 whole rows of a gate tile
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
     const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
-    const int slot = wave / slab_waves, w = wave - slot * slab_waves;
+    const int slot = wave / waves, w = wave - slot * waves;
     // (past the last slab: the last one once more, same values)
     const long mine = long(blockIdx.x) * slots + slot, slab = mine < n_slabs ? mine : n_slabs - 1;
     const SlabIo<kTm, kDk> io(q_all, k_all, v_all, gf_all, gb_all, out_all, slab, L, heads);
@@ -262,6 +256,16 @@ __global__ __launch_bounds__(64 * kShortWaves, 4) void bigla_short_kernel(
     const bool two = 2 * w + 1 < n_tiles;  // the wave's second tile exists
     const int tile0 = 2 * w;
 
+    if (w >= slab_waves) {  // a wave for the range-safe form only: the barriers of the others
+        __syncthreads();
+        __syncthreads();
+        if (__builtin_amdgcn_readfirstlane(*strong) == 0)
+            __syncthreads();
+        else
+            short_slab_safe<kDk, kTm>(q_all, k_all, v_all, gf_all, gb_all, out_all, eb_all + slab * (2 * kShortTiles * kD), slab, slot, w,
+                                      waves, L, n_tiles, heads);
+        return;
+    }
     if (w == 0 && lane == 0) *strong = 0;
     if constexpr (!kGates) {
         // ---- the gates of the wave's 32 tokens
@@ -596,7 +600,7 @@ __global__ __launch_bounds__(64 * kShortWaves, 4) void bigla_short_kernel(
     asm volatile("" : "+s"(flag));
     if (flag != 0)
         short_slab_safe<kDk, kTm>(q_all, k_all, v_all, gf_all, gb_all, out_all, eb_all + slab * (2 * kShortTiles * kD), slab, slot, w,
-                                  L, n_tiles, heads);
+                                  waves, L, n_tiles, heads);
 }
 
 }  // namespace
@@ -618,7 +622,14 @@ hipError_t bigla_short_launch(const void *q, const void *k, const void *v, const
                               const GateSource *gates = nullptr)
 {
     const int n_tiles = (L + 15) / 16, slab_waves = (n_tiles + 1) / 2;
-    int slots = kShortWaves / slab_waves;  // slabs per workgroup
+    // Up to 64 tokens in up to 1024 slabs, a workgroup per slab with a wave per tile of the range-safe form (half of them
+    // idle in the fast form): 48 slabs of 64 tokens 6.1 us and, at -0.3 a step, 10.5, against 9.5 and 22.5 with four slabs in a
+    // workgroup and two tiles to a wave (the general single-chunk kernel: 12.0 and 15.4); 1024 slabs 14.6 / 35.8 against
+    // 15.1 / 34.3, beyond that the chip is full either way (2048 of 48: 21.3 / 54.7 against 20.1 / 48.0; dk = 64, calls in a
+    // captured graph).
+    const bool spread = L <= kC && BH <= 1024;
+    const int waves = spread ? n_tiles : slab_waves;     // per slab
+    const int slots = spread ? 1 : kShortWaves / waves;  // slabs per workgroup
     const long blocks = (BH + slots - 1) / slots;
     if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
     LaunchTimer timer(kKernelSlab, stream);
@@ -627,10 +638,10 @@ hipError_t bigla_short_launch(const void *q, const void *k, const void *v, const
         constexpr int kDk = decltype(dk_c)::value;
         constexpr bool kTm = decltype(tm_c)::value, kGates = decltype(gates_c)::value;
         const unsigned lds = unsigned(slots) * (ShortSlab<kDk>::bytes(n_tiles) + unsigned(sizeof(int)));
-        hipLaunchKernelGGL((bigla_short_kernel<kDk, kTm, kGates>), dim3((unsigned)blocks), dim3(unsigned(64 * slab_waves * slots)), lds, stream,
+        hipLaunchKernelGGL((bigla_short_kernel<kDk, kTm, kGates>), dim3((unsigned)blocks), dim3(unsigned(64 * waves * slots)), lds, stream,
                            static_cast<const uint16_t *>(q), static_cast<const uint16_t *>(k), static_cast<const uint16_t *>(v),
                            static_cast<const uint16_t *>(g_fwd), static_cast<const uint16_t *>(g_bwd), static_cast<uint16_t *>(out),
-                           static_cast<float *>(workspace), L, n_tiles, slab_waves, slots, BH, heads_token_major > 0 ? heads_token_major : 1,
+                           static_cast<float *>(workspace), L, n_tiles, slab_waves, waves, slots, BH, heads_token_major > 0 ? heads_token_major : 1,
                            gates ? *gates : none);
     };
     using std::integral_constant;

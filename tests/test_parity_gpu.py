@@ -1099,19 +1099,12 @@ def test_bigla_bwd_is_the_gradient_of_the_forward_kernels():
 # --------------------------------------------------------------------------- #
 # sequences taken as one chunk (32 to 256 tokens)
 # --------------------------------------------------------------------------- #
-@pytest.mark.parametrize("layout,dk", (("bhld", 64), ("blhd", 64), ("bhld", 32), ("blhd", 32)))
-@pytest.mark.parametrize("L", (32, 33, 48, 49, 64, 65, 97, 129, 196, 209, 241, 256))
-def test_bigla_one_chunk_sequences(L, layout, dk):
-    """The kernel that takes a whole sequence as one chunk: lengths around its tiles of 16 tokens, waves of 32 and the
-    two and four slabs that share a workgroup, five slabs (the last workgroup is not full); in one call slabs of mild
-    gates, slabs just inside and just beyond the limit of bf16 operands, hard resets, and a slab that leaves the fast
-    form by a few channels of one stretch."""
+def _check_one_chunk(w, layout):
     import torch
     from paper_2405_18425_amd import binding as vb
 
-    # (longer ones from 128 slabs on: 130, the last workgroup not full either)
-    w = wl.Workload("one_chunk", B=5, H=1 if L <= 64 else 26, Hg=1, Wg=L, dk=dk, dv=64, dtype="bf16", gate_mu=-1.0)
-    _say(f"bigla one chunk L{L} {layout} dk{dk}")
+    L, dk = w.Wg, w.dk
+    _say(f"bigla {w} {layout}")
     s = wl.generate(w, seed=L + dk, tensors=("q", "k", "v", "g_fwd", "g_bwd"))
     r = np.random.default_rng(L)
     for name in ("g_fwd", "g_bwd"):
@@ -1131,16 +1124,31 @@ def test_bigla_one_chunk_sequences(L, layout, dk):
     assert_close(wl.widen(wl.from_torch(out, "bf16"), "bf16"), run_bigla_oracle(s, "bf16"), TOL["bf16"], f"L{L}")
 
 
-@pytest.mark.parametrize("layout,dk,bias_mu", (("bhld", 64, 0.0), ("blhd", 64, -9.0), ("blhd", 32, 0.0)))
-@pytest.mark.parametrize("L", (40, 49, 196, 250))
-def test_gated_bigla_one_chunk_sequences(L, layout, dk, bias_mu):
-    """gated_bigla_fwd where one launch makes the gates and takes the sequence as one chunk: bit for bit what the gate
-    producer followed by the token mixer returns (which the oracle checks elsewhere), in and beyond the fast form."""
+@pytest.mark.parametrize("layout,dk", (("bhld", 64), ("blhd", 64), ("bhld", 32), ("blhd", 32)))
+@pytest.mark.parametrize("L", (32, 33, 48, 49, 64, 65, 97, 129, 196, 209, 241, 256))
+def test_bigla_one_chunk_sequences(L, layout, dk):
+    """The kernel that takes a whole sequence as one chunk: lengths around its tiles of 16 tokens, waves of 32 and the
+    two slabs that share a workgroup; in one call slabs of mild gates, slabs just inside and just beyond the limit of
+    bf16 operands, hard resets, and a slab that leaves the fast form by a few channels of one stretch."""
+    # (up to 64 tokens five slabs, a workgroup each; longer ones from 128 slabs on: 130, the last workgroup not full)
+    _check_one_chunk(wl.Workload("one_chunk", B=5, H=1 if L <= 64 else 26, Hg=1, Wg=L, dk=dk, dv=64, dtype="bf16", gate_mu=-1.0),
+                     layout)
+
+
+@pytest.mark.parametrize("layout,dk", (("bhld", 64), ("blhd", 64), ("bhld", 32)))
+@pytest.mark.parametrize("L", (32, 33, 48, 49, 64))
+def test_bigla_one_chunk_many_short_sequences(L, layout, dk):
+    """The same beyond 1024 slabs, where up to 64 tokens share a workgroup with other slabs and a wave takes two tiles
+    in the range-safe form; 1030 slabs, the last workgroup not full."""
+    _check_one_chunk(wl.Workload("one_chunk_many", B=5, H=206, Hg=1, Wg=L, dk=dk, dv=64, dtype="bf16", gate_mu=-1.0), layout)
+
+
+def _check_gated_one_chunk(L, B, layout, dk, bias_mu):
     import torch
     from paper_2405_18425_amd import binding as vb
 
-    B, H, D = 3 if L <= 64 else 43, 3, 192
-    _say(f"gated one chunk L{L} {layout} dk{dk}")
+    H, D = 3, 192
+    _say(f"gated one chunk L{L} {layout} dk{dk} {B * H} slabs")
     st = wl.generate_gate_inputs(B, L, D, H, dk, "bf16", seed=L, bias_mu=bias_mu)
     s = wl.generate(wl.Workload("gated", B=B, H=H, Hg=1, Wg=L, dk=dk, dv=64, dtype="bf16", gate_mu=0.0), seed=L,
                     tensors=("q", "k", "v"))
@@ -1154,6 +1162,22 @@ def test_gated_bigla_one_chunk_sequences(L, layout, dk, bias_mu):
     torch.cuda.synchronize()
     for a, b, name in zip(got, want, ("out", "g_fwd", "g_bwd")):
         assert torch.equal(a, b), name
+
+
+@pytest.mark.parametrize("layout,dk,bias_mu", (("bhld", 64, 0.0), ("blhd", 64, -9.0), ("blhd", 32, 0.0)))
+@pytest.mark.parametrize("L", (40, 49, 196, 250))
+def test_gated_bigla_one_chunk_sequences(L, layout, dk, bias_mu):
+    """gated_bigla_fwd where one launch makes the gates and takes the sequence as one chunk: bit for bit what the gate
+    producer followed by the token mixer returns (which the oracle checks elsewhere), in and beyond the fast form."""
+    _check_gated_one_chunk(L, 3 if L <= 64 else 43, layout, dk, bias_mu)
+
+
+@pytest.mark.parametrize("layout,dk,bias_mu", (("bhld", 64, 0.0), ("blhd", 64, -40.0), ("blhd", 32, -40.0)))
+@pytest.mark.parametrize("L,B", ((33, 3), (64, 3), (33, 343), (64, 343)))
+def test_gated_bigla_one_chunk_short_sequences(L, B, layout, dk, bias_mu):
+    """The same with a workgroup per slab and, beyond 1024 slabs, with several; in the range-safe form a wave reads gates
+    that another wave of its workgroup has made."""
+    _check_gated_one_chunk(L, B, layout, dk, bias_mu)
 
 
 # --------------------------------------------------------------------------- #
