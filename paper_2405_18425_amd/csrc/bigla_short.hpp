@@ -16,8 +16,8 @@
 // of its token, and nothing is bounced through LDS.  LDS rows are 128 (64) bytes without padding, their 16-byte pieces
 // permuted by row so that the accesses of 16 lanes fall into different banks.
 //
-// A slab in which some 64-token stretch decays by more than kMildRange in a channel takes the range-safe form of
-// bigla_chunk.hip, tile by tile (short_slab_safe), inside the same launch.
+// A slab in which some 64-token stretch decays by more than kMildRange in a channel (a sequence of fewer tokens: by more than
+// its share of that) takes the range-safe form of bigla_chunk.hip, tile by tile (short_slab_safe), inside the same launch.
 //
 // Measured (kernel trace): 384 slabs of 196 tokens, 57.8 MB: 22.9 us (the chunked kernel that walks a slab twice in one
 // launch: 32.0 us); 192 slabs: 14.9 us (23.2); 1024 slabs of 49 tokens: 14.4 us (the general single-chunk kernel: 69.4).
@@ -419,8 +419,11 @@ __global__ __launch_bounds__(64 * kShortWaves, 4) void bigla_short_kernel(
         }
         own_offs[c] = w < mid ? -of : of;
         own_offs[kDk + c] = w < mid ? ob : -ob;
-        // (a NaN counts as too fast)
-        if (!(stretch[0] >= -kMildRange && stretch[1] >= -kMildRange)) *strong = 1;
+        // (a NaN counts as too fast; a sequence of under 64 tokens has its share of the range: the decay per token is what
+        // leaves an output few tokens to sum over.  A last stretch of a few tokens keeps all of it: the slab's scale is that of
+        // the others, and few gates of such a stretch are an ordinary draw away from a share.)
+        const float range = kMildRange / kC * float(min(L, kC));
+        if (!(stretch[0] >= -range && stretch[1] >= -range)) *strong = 1;
         wave_lds_fence();
     }
     f32x4 offs[2][kCt];
