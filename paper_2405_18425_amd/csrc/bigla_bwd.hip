@@ -31,7 +31,7 @@ namespace {
 // 61); 1024 slabs 1.65 ms (2.97), 8192 slabs of 20 tokens in bf16 2.1 ms (12.7).  Bound by its instructions, about 90 a token and wave.
 // kPairs: strips of one slab per workgroup.  A slab's strips are first the DK / kRows of dq, dk and dg, then the
 // DV / kCols of dv; a workgroup has strips of one kind only, so that its waves meet the same barriers.
-template <typename T, int DK, int DV, int kPairs>
+template <typename T, int DK, int DV, int kPairs, typename Off>
 __global__ __launch_bounds__(128 * kPairs, 1) void bigla_bwd_exact_kernel(
     const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, const T *__restrict__ gf,
     const T *__restrict__ gb, const T *__restrict__ d_out, T *__restrict__ dq, T *__restrict__ dk, T *__restrict__ dv,
@@ -47,12 +47,12 @@ __global__ __launch_bounds__(128 * kPairs, 1) void bigla_bwd_exact_kernel(
     const size_t row0 = slab_first_row(slab, L, heads_token_major);
     const size_t step = heads_token_major ? heads_token_major : 1;
     if (work < kRowWork)
-        row_sweep<T, DK, DV>(q + row0 * DK, k + row0 * DK, v + row0 * DV, gf + row0 * DK, gb + row0 * DK, d_out + row0 * DV,
+        row_sweep<T, DK, DV, Off>(q + row0 * DK, k + row0 * DK, v + row0 * DV, gf + row0 * DK, gb + row0 * DK, d_out + row0 * DV,
                              dq + row0 * DK, dk + row0 * DK, dgf + row0 * DK, dgb + row0 * DK, part_f + size_t(slab) * L * DK,
                              part_b + size_t(slab) * L * DK, stage[wave], step, L, descending, work * kPairs + (wave >> 1), lane);
     else
         // the adjoint that runs with the wave belongs to the other direction
-        column_sweep<T, DK, DV, true>(q + row0 * DK, k + row0 * DK, (descending ? gf : gb) + row0 * DK, d_out + row0 * DV,
+        column_sweep<T, DK, DV, true, Off>(q + row0 * DK, k + row0 * DK, (descending ? gf : gb) + row0 * DK, d_out + row0 * DV,
                                       part_v + size_t(slab) * L * DV, dv + row0 * DV, step, 1, L, descending,
                                       (work - kRowWork) * kPairs + (wave >> 1), 0.5f, 1.f, lane);
 }
@@ -64,21 +64,23 @@ hipError_t launch(const void *q, const void *k, const void *v, const void *gf, c
 {
     constexpr int kRowStrips = DK / (kStrip * (64 / DV)), kColStrips = DV / (kStrip * (64 / DK));
     float *part_f = ws, *part_b = ws + size_t(BH) * L * DK, *part_v = part_b + size_t(BH) * L * DK;
-    auto run = [&](auto pairs) -> hipError_t {
+    auto run = [&](auto pairs, auto offset) -> hipError_t {
         constexpr int kPairs = decltype(pairs)::value;
         const long blocks = BH * ((kRowStrips + kColStrips) / kPairs);
         if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((bigla_bwd_exact_kernel<T, DK, DV, kPairs>), dim3((unsigned)blocks), dim3(128 * kPairs), 0, stream,
+        hipLaunchKernelGGL((bigla_bwd_exact_kernel<T, DK, DV, kPairs, decltype(offset)>), dim3((unsigned)blocks), dim3(128 * kPairs), 0, stream,
                            static_cast<const T *>(q), static_cast<const T *>(k), static_cast<const T *>(v),
                            static_cast<const T *>(gf), static_cast<const T *>(gb), static_cast<const T *>(d_out),
                            static_cast<T *>(dq), static_cast<T *>(dk), static_cast<T *>(dv), static_cast<T *>(dgf),
                            static_cast<T *>(dgb), part_f, part_b, part_v, L, heads_token_major, unsigned(BH));
         return hipGetLastError();
     };
+    if (!tile_fits_32_bits(heads_token_major ? heads_token_major : 1, DK > DV ? DK : DV, sizeof(T)))
+        return run(std::integral_constant<int, 1>{}, size_t{});
     // as in the forward: one pair per workgroup until every compute unit has one
     if constexpr (kRowStrips % 2 == 0 && kColStrips % 2 == 0)
-        if (BH * (kRowStrips + kColStrips) > 512) return run(std::integral_constant<int, 2>{});
-    return run(std::integral_constant<int, 1>{});
+        if (BH * (kRowStrips + kColStrips) > 512) return run(std::integral_constant<int, 2>{}, 0u);
+    return run(std::integral_constant<int, 1>{}, 0u);
 }
 
 template <typename T, int DK>

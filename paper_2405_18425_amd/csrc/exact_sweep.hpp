@@ -26,7 +26,15 @@ namespace {
 
 constexpr int kStrip = 4;   // matrix elements per lane
 constexpr int kTile = 8;    // tokens whose readouts are summed over the lanes together
-constexpr int kDepth = 3;   // tiles whose operands are in registers or on their way there
+// Tiles whose operands are in registers or on their way there.  Offsets inside a tile are 32 bits wide (Off = unsigned)
+// unless its eight tokens span more than that, which takes millions of token-major heads: with 64 bits they are twice the
+// registers, and the chip is full of strips whatever a wave has in flight.
+template <typename Off>
+constexpr int kDepth = sizeof(Off) == 4 ? 3 : 1;
+inline bool tile_fits_32_bits(size_t step, int width, size_t value_bytes)
+{
+    return size_t(kTile) * step * width * value_bytes <= 0xffffffffu;
+}
 constexpr int kVals = kTile * kStrip;
 
 // the partner's value under a DPP permutation that exchanges the two halves of a lane group
@@ -107,14 +115,14 @@ __device__ __forceinline__ void load_strip(const T *p, float (&f)[kStrip])
     }
 }
 
-// byte offset (32 bits: inside a tile) of element `n` of a row tensor, and what lies there
-template <typename T>
-__device__ __forceinline__ unsigned at_byte(unsigned n)
+// byte offset (inside a tile) of element `n` of a row tensor, and what lies there
+template <typename T, typename Off>
+__device__ __forceinline__ Off at_byte(Off n)
 {
-    return n * unsigned(sizeof(T));
+    return n * Off(sizeof(T));
 }
-template <typename T>
-__device__ __forceinline__ const T *at(const T *base, unsigned bytes)
+template <typename T, typename Off>
+__device__ __forceinline__ const T *at(const T *base, Off bytes)
 {
     return reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + bytes);
 }
@@ -177,7 +185,7 @@ __device__ __forceinline__ Way make_way(int L, bool descending)
 // the token itself (a state: u = k, b = v, r = q); true: the gate of the token visited before (an adjoint: u = q,
 // b = d_out, r = k).  `park`: fp32, dense or strided like the result; result = result_scale * (own + parked).
 // One barrier, executed by every wave that calls this.  `park` and `result` may be one buffer (fp32).
-template <typename T, int DK, int DV, bool kDelayed>
+template <typename T, int DK, int DV, bool kDelayed, typename Off = unsigned>
 __device__ __forceinline__ void column_sweep(const T *u_rows, const T *r_rows, const T *g_rows, const T *b_rows,
                                              float *park, T *result, size_t step, size_t park_step, int L,
                                              bool descending, int col_block, float b_scale, float result_scale, int lane)
@@ -200,10 +208,10 @@ __device__ __forceinline__ void column_sweep(const T *u_rows, const T *r_rows, c
     float M[kStrip] = {0.f, 0.f, 0.f, 0.f}, before = 0.f;
     // a whole tile's offsets, the same in every tile (a wave alone on its SIMD pays for scalar address
     // arithmetic as much as for any other instruction)
-    unsigned off_k[kTile], off_v[kTile];
+    Off off_k[kTile], off_v[kTile];
 #pragma unroll
     for (int i = 0; i < kTile; ++i) {
-        const unsigned t = unsigned(descending ? kTile - 1 - i : i) * unsigned(step);
+        const Off t = Off(descending ? kTile - 1 - i : i) * Off(step);
         off_k[i] = at_byte<T>(t * DK + unsigned(ch));
         off_v[i] = at_byte<T>(t * DV + unsigned(col0));
     }
@@ -215,11 +223,11 @@ __device__ __forceinline__ void column_sweep(const T *u_rows, const T *r_rows, c
             const T *u = u_rows + low * step * DK, *r = r_rows + low * step * DK, *g = g_rows + low * step * DK;
             const T *b = b_rows + low * step * DV;
             // (a token past the sequence repeats the last one's offset, so every address is valid)
-            const unsigned last_token = way.last_offset(n) * unsigned(step);
-            const unsigned end_k = at_byte<T>(last_token * DK + unsigned(ch)), end_v = at_byte<T>(last_token * DV + unsigned(col0));
+            const Off last_token = Off(way.last_offset(n)) * Off(step);
+            const Off end_k = at_byte<T>(last_token * DK + unsigned(ch)), end_v = at_byte<T>(last_token * DV + unsigned(col0));
 #pragma unroll
             for (int i = 0; i < kTile; ++i) {
-                const unsigned tk = min(off_k[i], end_k), tv = min(off_v[i], end_v);
+                const Off tk = min(off_k[i], end_k), tv = min(off_v[i], end_v);
                 o.u[i] = io<T>::load(at(u, tk));
                 o.r[i] = io<T>::load(at(r, tk));
                 o.g[i] = io<T>::load(at(g, tk));
@@ -269,19 +277,20 @@ __device__ __forceinline__ void column_sweep(const T *u_rows, const T *r_rows, c
             }
         };
         if (first >= last) return;
-        Operands o[kDepth];
+        constexpr int kAhead = kDepth<Off>;
+        Operands o[kAhead];
 #pragma unroll
-        for (int d = 0; d < kDepth; ++d) fetch(o[d], first + d);
+        for (int d = 0; d < kAhead; ++d) fetch(o[d], first + d);
         int n = first;
-        for (; n + kDepth <= last; n += kDepth) {
+        for (; n + kAhead <= last; n += kAhead) {
 #pragma unroll
-            for (int d = 0; d < kDepth; ++d) {
+            for (int d = 0; d < kAhead; ++d) {
                 walk(o[d], n + d);
-                fetch(o[d], n + d + kDepth);
+                fetch(o[d], n + d + kAhead);
             }
         }
 #pragma unroll
-        for (int d = 0; d < kDepth - 1; ++d)
+        for (int d = 0; d < kAhead - 1; ++d)
             if (n + d < last) walk(o[d], n + d);
     };
     half(0, way.first_half(), false);
@@ -317,7 +326,7 @@ struct RowStage {
     float x[kTile][4][kStrip * (64 / DV)];
 };
 
-template <typename T, int DK, int DV>
+template <typename T, int DK, int DV, typename Off = unsigned>
 __device__ __forceinline__ void row_sweep(const T *q_rows, const T *k_rows, const T *v_rows, const T *gf_rows,
                                           const T *gb_rows, const T *do_rows, T *dq_rows, T *dk_rows, T *dgf_rows,
                                           T *dgb_rows, float *part_f, float *part_b, RowStage<DV> &stage, size_t step,
@@ -354,10 +363,10 @@ __device__ __forceinline__ void row_sweep(const T *q_rows, const T *k_rows, cons
     struct Operands {
         float v[kTile], d[kTile], s[kLoads], other_f[kH], other_b[kH];
     };
-    unsigned off_v[kTile];  // a whole tile's offsets
+    Off off_v[kTile];  // a whole tile's offsets
 #pragma unroll
     for (int i = 0; i < kTile; ++i)
-        off_v[i] = at_byte<T>(unsigned(descending ? kTile - 1 - i : i) * unsigned(step) * DV + unsigned(col));
+        off_v[i] = at_byte<T>(Off(descending ? kTile - 1 - i : i) * Off(step) * DV + unsigned(col));
     float S[kStrip] = {0.f, 0.f, 0.f, 0.f}, A[kStrip] = {0.f, 0.f, 0.f, 0.f}, before[kStrip] = {0.f, 0.f, 0.f, 0.f};
 
     auto half = [&](int first, int last, bool second) __attribute__((always_inline)) {
@@ -365,10 +374,10 @@ __device__ __forceinline__ void row_sweep(const T *q_rows, const T *k_rows, cons
             n = min(n, last - 1);  // (past the end: loaded, never used; a branch would make every wait a full one)
             const size_t low = size_t(way.low(n));
             const T *v = v_rows + low * step * DV, *d = do_rows + low * step * DV;
-            const unsigned end_v = at_byte<T>(way.last_offset(n) * unsigned(step) * DV + unsigned(col));
+            const Off end_v = at_byte<T>(Off(way.last_offset(n)) * Off(step) * DV + unsigned(col));
 #pragma unroll
             for (int i = 0; i < kTile; ++i) {
-                const unsigned t = min(off_v[i], end_v);
+                const Off t = min(off_v[i], end_v);
                 o.v[i] = io<T>::load(at(v, t));
                 o.d[i] = io<T>::load(at(d, t));
             }
@@ -450,19 +459,20 @@ __device__ __forceinline__ void row_sweep(const T *q_rows, const T *k_rows, cons
             lds_order();  // the totals' reads of the stage before the next tile's writes
         };
         if (first >= last) return;
-        Operands o[kDepth];
+        constexpr int kAhead = kDepth<Off>;
+        Operands o[kAhead];
 #pragma unroll
-        for (int d = 0; d < kDepth; ++d) fetch(o[d], first + d);
+        for (int d = 0; d < kAhead; ++d) fetch(o[d], first + d);
         int n = first;
-        for (; n + kDepth <= last; n += kDepth) {
+        for (; n + kAhead <= last; n += kAhead) {
 #pragma unroll
-            for (int d = 0; d < kDepth; ++d) {
+            for (int d = 0; d < kAhead; ++d) {
                 walk(o[d], n + d);
-                fetch(o[d], n + d + kDepth);
+                fetch(o[d], n + d + kAhead);
             }
         }
 #pragma unroll
-        for (int d = 0; d < kDepth - 1; ++d)
+        for (int d = 0; d < kAhead - 1; ++d)
             if (n + d < last) walk(o[d], n + d);
     };
     half(0, way.first_half(), false);

@@ -1245,6 +1245,32 @@ def test_exact_kernels_tile_edges(L, dk, dv, layout):
         assert np.all(err <= bound + 1e-37), f"{name}: {np.max(err / (bound + 1e-37)):.2f} of the bound"
 
 
+def test_bigla_bwd_exact_tile_beyond_32_bits():
+    """Token-major with so many heads that eight tokens span more than 2^32 bytes: heads from all over against the oracle.
+    Inputs and outputs are 33 GB, of which only the sampled heads leave the card."""
+    import oracle
+    import torch
+    from paper_2405_18425_amd import binding as vb
+
+    H, L, dk, dv = 2_400_000, 8, 16, 64
+    assert 7 * H * dv * 4 >= 1 << 32
+    heads = torch.tensor([0, 1, 77_777, H // 2, H - 2, H - 1])
+    _say(f"exact gradient, {H} heads token-major")
+    g = torch.Generator(device="cuda").manual_seed(3)
+    make = lambda d: torch.randn((1, L, H, d), generator=g, device="cuda")
+    t = {"q": make(dk), "k": make(dk), "v": make(dv), "g_fwd": -make(dk).abs_(), "g_bwd": -make(dk).abs_(), "d_out": make(dv)}
+    got = vb.bigla_bwd(*t.values(), layout="blhd")
+    pick = lambda a: a[:, :, heads.cuda()].transpose(1, 2).cpu().numpy().astype(np.float64)
+    ref = oracle.bigla_bwd(*(pick(a) for a in t.values()))
+    # fp32 sums of at most 8 tokens x 64 columns x 2 directions, and of 8 tokens more for the gates: (1024 + 8) 2^-24 of
+    # the terms' magnitudes would be 6e-5; as rounding errors of random sign they stay far under a tenth of that
+    for name, a, r in zip(("dq", "dk", "dv", "dg_fwd", "dg_bwd"), got, ref):
+        worst = float(np.max(np.abs(pick(a) - r)) / np.max(np.abs(r)))
+        assert worst <= 6e-6, f"{name}: {worst:.2e}"
+    del t, got
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("layout,dk", (("bhld", 64), ("blhd", 64), ("blhd", 32)))
 @pytest.mark.parametrize("L", (32, 64, 65, 128, 129, 192, 193, 256, 257))
 def test_bigla_bwd_slabs_of_both_forms(L, layout, dk):
