@@ -36,11 +36,12 @@ __global__ __launch_bounds__(128 * kPairs, 1) void bigla_bwd_exact_kernel(
     const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, const T *__restrict__ gf,
     const T *__restrict__ gb, const T *__restrict__ d_out, T *__restrict__ dq, T *__restrict__ dk, T *__restrict__ dv,
     T *__restrict__ dgf, T *__restrict__ dgb, float *part_f /* [slabs][L][DK] */, float *part_b /* same */,
-    float *part_v /* [slabs][L][DV] */, int L, int heads_token_major /* 0: [B,H,L,d]; H: [B,L,H,d] */, unsigned n_slabs)
+    float *part_v /* [slabs][L][DV] */, int L, int heads_token_major /* 0: [B,H,L,d]; H: [B,L,H,d] */, unsigned first_slab,
+    unsigned n_slabs /* of this launch */)
 {
     constexpr int kRowWork = DK / (kStrip * (64 / DV)) / kPairs;  // workgroups of a slab that take rows
     __shared__ RowStage<DV> stage[2 * kPairs];
-    const unsigned slab = blockIdx.x % n_slabs;
+    const unsigned slab = first_slab + blockIdx.x % n_slabs;
     const int work = int(blockIdx.x / n_slabs);
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x)) >> 6, lane = int(threadIdx.x) & 63;
     const bool descending = (wave & 1) != 0;
@@ -66,14 +67,21 @@ hipError_t launch(const void *q, const void *k, const void *v, const void *gf, c
     float *part_f = ws, *part_b = ws + size_t(BH) * L * DK, *part_v = part_b + size_t(BH) * L * DK;
     auto run = [&](auto pairs, auto offset) -> hipError_t {
         constexpr int kPairs = decltype(pairs)::value;
-        const long blocks = BH * ((kRowStrips + kColStrips) / kPairs);
-        if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((bigla_bwd_exact_kernel<T, DK, DV, kPairs, decltype(offset)>), dim3((unsigned)blocks), dim3(128 * kPairs), 0, stream,
-                           static_cast<const T *>(q), static_cast<const T *>(k), static_cast<const T *>(v),
-                           static_cast<const T *>(gf), static_cast<const T *>(gb), static_cast<const T *>(d_out),
-                           static_cast<T *>(dq), static_cast<T *>(dk), static_cast<T *>(dv), static_cast<T *>(dgf),
-                           static_cast<T *>(dgb), part_f, part_b, part_v, L, heads_token_major, unsigned(BH));
-        return hipGetLastError();
+        // a launch has fewer than 2^32 work-items (one of more goes wrong without an error): further slabs in another one
+        constexpr long kMost = 0xffffffffL / (128 * (kRowStrips + kColStrips));
+        for (long first = 0; first < BH; first += kMost) {
+            const long slabs = BH - first < kMost ? BH - first : kMost;
+            const long blocks = slabs * ((kRowStrips + kColStrips) / kPairs);
+            hipLaunchKernelGGL((bigla_bwd_exact_kernel<T, DK, DV, kPairs, decltype(offset)>), dim3((unsigned)blocks), dim3(128 * kPairs), 0, stream,
+                               static_cast<const T *>(q), static_cast<const T *>(k), static_cast<const T *>(v),
+                               static_cast<const T *>(gf), static_cast<const T *>(gb), static_cast<const T *>(d_out),
+                               static_cast<T *>(dq), static_cast<T *>(dk), static_cast<T *>(dv), static_cast<T *>(dgf),
+                               static_cast<T *>(dgb), part_f, part_b, part_v, L, heads_token_major, unsigned(first),
+                               unsigned(slabs));
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
     };
     if (!tile_fits_32_bits(heads_token_major ? heads_token_major : 1, DK > DV ? DK : DV, sizeof(T)))
         return run(std::integral_constant<int, 1>{}, size_t{});

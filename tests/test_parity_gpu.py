@@ -1271,6 +1271,32 @@ def test_bigla_bwd_exact_tile_beyond_32_bits():
     torch.cuda.empty_cache()
 
 
+def test_bigla_bwd_exact_more_slabs_than_a_launch_holds():
+    """64 x 64 heads take 4096 work-items a slab, and a launch has fewer than 2^32 (one of more goes wrong): slabs from all over, the last of one
+    launch and the first of the next among them, against the oracle."""
+    import oracle
+    import torch
+    from paper_2405_18425_amd import binding as vb
+
+    BH, L = 1_060_000, 2
+    edge = 0xffffffff // 4096
+    assert edge < BH
+    slabs = torch.tensor([0, 1, 77_777, edge - 1, edge, edge + 1, BH - 1])
+    _say(f"exact gradient, {BH} slabs")
+    g = torch.Generator(device="cuda").manual_seed(4)
+    make = lambda: torch.randn((BH, 1, L, 64), generator=g, device="cuda")
+    t = {"q": make(), "k": make(), "v": make(), "g_fwd": -make().abs_(), "g_bwd": -make().abs_(), "d_out": make()}
+    got = vb.bigla_bwd(*t.values())
+    pick = lambda a: a[slabs.cuda()].cpu().numpy().astype(np.float64)
+    ref = oracle.bigla_bwd(*(pick(a) for a in t.values()))
+    # as above, of 2 tokens
+    for name, a, r in zip(("dq", "dk", "dv", "dg_fwd", "dg_bwd"), got, ref):
+        worst = float(np.max(np.abs(pick(a) - r)) / np.max(np.abs(r)))
+        assert worst <= 6e-6, f"{name}: {worst:.2e}"
+    del t, got
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("layout,dk", (("bhld", 64), ("blhd", 64), ("blhd", 32)))
 @pytest.mark.parametrize("L", (32, 64, 65, 128, 129, 192, 193, 256, 257))
 def test_bigla_bwd_slabs_of_both_forms(L, layout, dk):
