@@ -42,6 +42,7 @@
 // with ds_read_b64_tr_b16.  Tokens past the sequence are read as zeros (q = k = v = do = 0,
 // log-gate 0: a no-op) and their stores are dropped, both by the bounds check of the buffer
 // resource that spans the slab.
+#include <algorithm>
 #include <type_traits>
 
 #include "exact_sweep.hpp"
@@ -238,12 +239,18 @@ __device__ __forceinline__ void gate_scan(const Tile &gates, int w, int r, int g
 //     2: backward state entering the chunk from the right
 //     3: backward A' of the chunk (decayed adjoint from the left)
 //   log-decays, per (slab, chunk, direction): the chunk's total log-gate per channel, fp32
-//   slab marks: one int per slab, non-zero when the slab takes the exact form (walks: eight ints, where the log-decays
-//     would be)
+//   slab marks: two bytes per slab (walks: one of each direction), not both zero when the slab takes the exact form; with
+//     zeros up to a multiple of kShareSlabs slabs
+constexpr unsigned kShareSlabs = 16;  // slabs whose workgroups share out the exact form of the marked ones among them
+__device__ __forceinline__ void end_marks(uint16_t *marks, unsigned n_slabs, unsigned lane)  // the zeros, a wave's work
+{
+    if (lane < (0u - n_slabs) % kShareSlabs) marks[size_t(n_slabs) + lane] = 0;
+}
+
 struct Workspace {
     uint16_t *states;
     float *logdec;
-    int *marks;
+    uint16_t *marks;
 };
 
 inline size_t align256(size_t n) { return (n + 255) / 256 * 256; }
@@ -252,7 +259,7 @@ inline int chunks_of(int L) { return (L + kC - 1) / kC; }
 
 inline size_t states_bytes(long BH, int L) { return align256(size_t(BH) * chunks_of(L) * 4 * kMat * sizeof(uint16_t)); }
 inline size_t logdec_bytes(long BH, int L) { return align256(size_t(BH) * chunks_of(L) * 2 * kD * sizeof(float)); }
-inline size_t marks_bytes(long BH) { return align256(size_t(BH) * sizeof(int)); }
+inline size_t marks_bytes(long BH) { return align256((size_t(BH) + kShareSlabs - 1) / kShareSlabs * kShareSlabs * 2); }
 
 struct LocalLds {
     Tile v, dout, gates, qt, kh;
@@ -265,12 +272,14 @@ template <int kCt>
 __global__ __launch_bounds__(kThreads, 2) void bigla_bwd_chunk_local_kernel(
     const void *__restrict__ q_all, const void *__restrict__ k_all, const void *__restrict__ v_all,
     const void *__restrict__ gf_all, const void *__restrict__ gb_all, const void *__restrict__ do_all,
-    uint16_t *__restrict__ states, float *__restrict__ logdec, int L, int heads_token_major, int n_chunks, int dk)
+    uint16_t *__restrict__ states, float *__restrict__ logdec, uint16_t *__restrict__ marks, int L, int heads_token_major, int n_chunks,
+    int dk)
 {
     __shared__ __align__(16) LocalLds sm;
     const unsigned unit = blockIdx.x, slab = unit / unsigned(n_chunks);
     const unsigned t0 = (unit - slab * unsigned(n_chunks)) * kC;
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r = lane & 15, g = lane >> 4;
+    if (unit == 0 && w == 0) end_marks(marks, gridDim.x / unsigned(n_chunks), unsigned(lane));
 
     const size_t first = slab_first_row(slab, L, heads_token_major);
     const SlabRows q = slab_rows(q_all, first, L, heads_token_major, dk), k = slab_rows(k_all, first, L, heads_token_major, dk);
@@ -356,7 +365,7 @@ constexpr int kScanThreads = 256;
 template <int kScanAhead, int kCt>
 __global__ __launch_bounds__(kScanThreads) void bigla_bwd_chunk_scan_kernel(uint16_t *__restrict__ states,
                                                                        const float *__restrict__ logdec,
-                                                                       int *__restrict__ marks, int n_chunks)
+                                                                       uint16_t *__restrict__ marks, int n_chunks)
 {
     constexpr int kScanParts = kCt * 256 / kScanThreads;  // workgroups per matrix: 16 * kCt rows of 16 pieces
     const unsigned slab = blockIdx.x / (4 * kScanParts);
@@ -454,7 +463,7 @@ template <int kCt>
 __global__ __launch_bounds__(kWalkThreads, 4) void bigla_bwd_chunk_walk_kernel(
     const void *__restrict__ q_all, const void *__restrict__ k_all, const void *__restrict__ v_all,
     const void *__restrict__ gf_all, const void *__restrict__ gb_all, const void *__restrict__ do_all,
-    uint16_t *__restrict__ states, int *__restrict__ marks /* [slab][direction][wave] */, int L, int heads_token_major,
+    uint16_t *__restrict__ states, uint16_t *__restrict__ marks, int L, int heads_token_major,
     int n_chunks, unsigned n_slabs)
 {
     constexpr int dk = 16 * kCt;
@@ -549,8 +558,8 @@ __global__ __launch_bounds__(kWalkThreads, 4) void bigla_bwd_chunk_walk_kernel(
     for (int mi = 0; mi < kCt; ++mi) s[mi] = f32x4{0.f, 0.f, 0.f, 0.f};
     __syncthreads();
     auto step = [&](int j, int n) __attribute__((always_inline)) {
-        const float total = sm.total[j][row], d = fast_exp2(total * kLog2e);
-        beyond = beyond || -total > kFastRange;
+        const float d = fast_exp2(sm.total[j][row] * kLog2e);
+        beyond = beyond || -sm.total[j][lane % dk] > kFastRange;  // (every wave: all channels)
         uint16_t *mat = mats + size_t(chunk_of(n)) * 4 * kMat;
         bf16x8 xf[2];
 #pragma unroll
@@ -582,10 +591,11 @@ __global__ __launch_bounds__(kWalkThreads, 4) void bigla_bwd_chunk_walk_kernel(
         step(0, n);
     }
     // mark the slab when some chunk decays by more than the fast form can carry (a NaN gate total compares false and
-    // leaves the slab to this path, whose outputs are then NaN too): an int per direction and wave
-    if (!adjoint) {
+    // leaves the slab to this path, whose outputs are then NaN too)
+    if (!adjoint && w == 0) {
         const bool any = __any(beyond);
-        if (lane == 0) marks[8 * slab + 4 * dir + w] = any ? 1 : 0;
+        if (lane == 0) reinterpret_cast<uint8_t *>(marks)[2 * size_t(slab) + dir] = any ? 1 : 0;
+        if (slab == n_slabs - 1 && dir == 0) end_marks(marks, n_slabs, unsigned(lane));
     }
 }
 
@@ -838,36 +848,51 @@ __device__ __forceinline__ void chunk_direction(MainLds &sm, const DirInputs &in
     }
 }
 
-// A slab that is marked: the workgroups of its chunks share out the strips of the exact form, two pairs of waves at a
-// time.  Inside this launch and not in one of its own: a launch that finds no marked slab still took 4.7 us (and
-// two of them, 9.5 us, were 7 % of a call at 384 slabs of 196 tokens).  Not inlined, so that its registers stay out of
-// the chunkwise code's allocation; its LDS is a namespace-scope object, which such a function can address as LDS.
-__shared__ RowStage<kD> g_exact_stage[4];
+// Marked slabs: the workgroups of every sixteen slabs share out the strips of the exact form, two pairs of waves at a time,
+// of those that are marked among them.  Inside this launch and not in one of its own: a launch that finds no marked
+// slab still took 4.7 us (and two of them, 9.5 us, were 7 % of a call at 384 slabs of 196 tokens).  A gradient call with one
+// marked slab, and with all marked: 48 slabs of 64 tokens 27 and 50 us (a slab's strips dealt to the workgroups of its own
+// chunks, from a function that spilled: 410 and 476; the token-by-token kernels before these, in launches of their own: 65 and
+// 107), 384 of 196 tokens 113 and 634 us (298 / 1494; 218 / 1052), 48 of 4096 tokens 0.84 and 1.60 ms (0.94 / 3.42; 2.35 / 2.41).
+// What the exact form needs is a kernel argument of its own, read where it is used: the chunkwise code's copies of the same
+// pointers, kept for it, cost that code scalar registers.
+struct ExactArgs {
+    const bf16_t *q, *k, *v, *gf, *gb, *d_out;
+    bf16_t *dq, *dk, *dv, *dgf, *dgb;
+    float *parts;
+    int L, heads_token_major;
+    unsigned n_slabs, workers_per_slab;
+};
 
 template <int DK>
-__device__ __attribute__((noinline)) void exact_slab_share(
-    const void *q_all, const void *k_all, const void *v_all, const void *gf_all, const void *gb_all, const void *do_all,
-    void *dq_all, void *dk_all, void *dv_all, void *dgf_all, void *dgb_all, float *exact_ws, int L, int heads_token_major,
-    unsigned n_slabs, unsigned slab, unsigned first_item, int n_chunks)
+__device__ __forceinline__ void exact_strips(const ExactArgs &a, RowStage<kD> (&stage)[4], unsigned first_slab,
+                                             unsigned marked /* a bit per slab from there on */, unsigned worker, unsigned workers)
 {
-    constexpr int kRowItems = DK / kStrip / 2, kColItems = kD / (kStrip * (kD / DK)) / 2;
-    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x)) >> 6, lane = int(threadIdx.x) & 63;
+    constexpr unsigned kRowItems = DK / kStrip / 2, kColItems = kD / (kStrip * (kD / DK)) / 2;
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x)) >> 6;
     const bool descending = (wave & 1) != 0;
-    const size_t row0 = slab_first_row(slab, L, heads_token_major), step = heads_token_major ? heads_token_major : 1;
-    const size_t keys = size_t(L) * DK, all_keys = keys * n_slabs;
-    auto in = [&](const void *p, int width) { return static_cast<const bf16_t *>(p) + row0 * width; };
-    auto out = [&](void *p, int width) { return static_cast<bf16_t *>(p) + row0 * width; };
+    const size_t step = a.heads_token_major ? a.heads_token_major : 1, keys = size_t(a.L) * DK, all_keys = keys * a.n_slabs;
+    const unsigned n_marked = unsigned(__popc(marked));
 #pragma unroll 1
-    for (int item = int(first_item); item < kRowItems + kColItems; item += n_chunks) {
+    for (unsigned i = worker; i < n_marked * (kRowItems + kColItems); i += workers) {
+        // (what depends on the lane is formed anew for every strip: hoisted out of this loop, the offsets of both kinds of
+        // strips together spilled 2 KB a lane, and a strip took three times as long)
+        int lane = int(threadIdx.x) & 63;
+        asm volatile("" : "+v"(lane));
+        const unsigned item = i / n_marked;
+        unsigned bits = marked;
+        for (unsigned skip = i - item * n_marked; skip > 0; --skip) bits &= bits - 1;
+        const unsigned slab = first_slab + unsigned(__ffs(int(bits)) - 1);
+        const size_t row0 = slab_first_row(slab, a.L, a.heads_token_major), k0 = row0 * DK, v0 = row0 * kD;
+        float *parts = a.parts + slab * keys;
         if (item < kRowItems)
-            row_sweep<bf16_t, DK, kD>(in(q_all, DK), in(k_all, DK), in(v_all, kD), in(gf_all, DK), in(gb_all, DK), in(do_all, kD),
-                                      out(dq_all, DK), out(dk_all, DK), out(dgf_all, DK), out(dgb_all, DK),
-                                      exact_ws + slab * keys, exact_ws + all_keys + slab * keys, g_exact_stage[wave], step, L,
-                                      descending, 2 * item + (wave >> 1), lane);
+            row_sweep<bf16_t, DK, kD>(a.q + k0, a.k + k0, a.v + v0, a.gf + k0, a.gb + k0, a.d_out + v0, a.dq + k0, a.dk + k0,
+                                      a.dgf + k0, a.dgb + k0, parts, parts + all_keys, stage[wave], step, a.L, descending,
+                                      int(2 * item) + (wave >> 1), lane);
         else
-            column_sweep<bf16_t, DK, kD, true>(in(q_all, DK), in(k_all, DK), in(descending ? gf_all : gb_all, DK), in(do_all, kD),
-                                               exact_ws + 2 * all_keys + size_t(slab) * L * kD, out(dv_all, kD), step, 1, L,
-                                               descending, 2 * (item - kRowItems) + (wave >> 1), 0.5f, 1.f, lane);
+            column_sweep<bf16_t, DK, kD, true>(a.q + k0, a.k + k0, (descending ? a.gf : a.gb) + k0, a.d_out + v0,
+                                               a.parts + 2 * all_keys + size_t(slab) * a.L * kD, a.dv + v0, step, 1, a.L,
+                                               descending, int(2 * (item - kRowItems)) + (wave >> 1), 0.5f, 1.f, lane);
     }
 }
 
@@ -876,58 +901,73 @@ __global__ __launch_bounds__(kThreads, 2) void bigla_bwd_chunk_main_kernel(
     const void *__restrict__ q_all, const void *__restrict__ k_all, const void *__restrict__ v_all,
     const void *__restrict__ gf_all, const void *__restrict__ gb_all, const void *__restrict__ do_all,
     void *__restrict__ dq_all, void *__restrict__ dk_all, void *__restrict__ dv_all, void *__restrict__ dgf_all,
-    void *__restrict__ dgb_all, const uint16_t *__restrict__ states, const int *__restrict__ marks, int marks_per_slab, float *exact_ws, int L,
-    int heads_token_major, int n_chunks, unsigned n_slabs)
+    void *__restrict__ dgb_all, const uint16_t *__restrict__ states, const uint16_t *__restrict__ marks, int L,
+    int heads_token_major, int n_chunks, unsigned n_slabs, unsigned extra /* workgroups per slab without a chunk */, ExactArgs exact)
 {
     constexpr int dk = 16 * kCt;
     __shared__ __align__(16) MainLds sm;
-    const unsigned unit = blockIdx.x, slab = unit / unsigned(n_chunks);
-    int marked;
-    if (marks_per_slab == 8) {
-        const int4 a = reinterpret_cast<const int4 *>(marks)[2 * slab], b = reinterpret_cast<const int4 *>(marks)[2 * slab + 1];
-        marked = (a.x | a.y | a.z | a.w) | (b.x | b.y | b.z | b.w);
-    } else {
-        marked = marks[slab];
-    }
-    if (marked != 0) {  // gates beyond the range of this form
-        exact_slab_share<16 * kCt>(q_all, k_all, v_all, gf_all, gb_all, do_all, dq_all, dk_all, dv_all, dgf_all, dgb_all, exact_ws,
-                                   L, heads_token_major, n_slabs, slab, unit - slab * unsigned(n_chunks), n_chunks);
-        return;
-    }
-    const unsigned t0 = (unit - slab * unsigned(n_chunks)) * kC;
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r = lane & 15, g = lane >> 4;
+    __shared__ RowStage<kD> exact_stage[4];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const unsigned unit = blockIdx.x, units = n_slabs * unsigned(n_chunks);
+    const bool has_chunk = unit < units;
+    const unsigned slab = has_chunk ? unit / unsigned(n_chunks) : (unit - units) / extra;
+    const unsigned chunk = unit - slab * unsigned(n_chunks);
+    // the slabs that share out the exact form, and which of them take it (their marks are one scalar load, and as a rule all
+    // zero; a lane each for the first look at them made calls on a few slabs 0.2 us longer)
+    const unsigned first_slab = slab & ~(kShareSlabs - 1), sharing = min(kShareSlabs, n_slabs - first_slab);
+    unsigned marked;
+    const uint4 *group = reinterpret_cast<const uint4 *>(marks + first_slab);
+    const uint4 m0 = group[0], m1 = group[1];
+    marked = (m0.x | m0.y | m0.z | m0.w) | (m1.x | m1.y | m1.z | m1.w);
+    if (marked != 0) marked = unsigned(__ballot(marks[first_slab + unsigned(lane) % kShareSlabs] != 0)) & ((1u << kShareSlabs) - 1u);
+    const bool own_marked = (marked >> (slab - first_slab) & 1u) != 0;
+    if (has_chunk && !own_marked) {
+        const unsigned t0 = chunk * kC;
+        const int w = tid >> 6, r = lane & 15, g = lane >> 4;
 
-    const size_t first = slab_first_row(slab, L, heads_token_major);
-    const SlabRows q = slab_rows(q_all, first, L, heads_token_major, dk), k = slab_rows(k_all, first, L, heads_token_major, dk);
-    const SlabRows v = slab_rows(v_all, first, L, heads_token_major), dout = slab_rows(do_all, first, L, heads_token_major);
-    const SlabRows gf = slab_rows(gf_all, first, L, heads_token_major, dk), gb = slab_rows(gb_all, first, L, heads_token_major, dk);
-    const SlabRows dgf = slab_rows(dgf_all, first, L, heads_token_major, dk), dgb = slab_rows(dgb_all, first, L, heads_token_major, dk);
+        const size_t first = slab_first_row(slab, L, heads_token_major);
+        const SlabRows q = slab_rows(q_all, first, L, heads_token_major, dk), k = slab_rows(k_all, first, L, heads_token_major, dk);
+        const SlabRows v = slab_rows(v_all, first, L, heads_token_major), dout = slab_rows(do_all, first, L, heads_token_major);
+        const SlabRows gf = slab_rows(gf_all, first, L, heads_token_major, dk), gb = slab_rows(gb_all, first, L, heads_token_major, dk);
+        const SlabRows dgf = slab_rows(dgf_all, first, L, heads_token_major, dk), dgb = slab_rows(dgb_all, first, L, heads_token_major, dk);
 
-    uint2 qr[4], kr[4];
-    const uint16_t *mats = states + size_t(unit) * 4 * kMat;
-    {
-        const ChunkRows cq = fetch_rows(q, t0, w, lane), ck = fetch_rows(k, t0, w, lane);
-        const ChunkRows cv = fetch_rows(v, t0, w, lane), cd = fetch_rows(dout, t0, w, lane);
-        put_rows<false>(sm.qt, cq, w, lane);
-        put_rows<false>(sm.kt, ck, w, lane);
-        put_rows<false>(sm.v, cv, w, lane);
-        put_rows<true>(sm.dout, cd, w, lane);
-    }
-    const DirInputs in_f = fetch_dir<0, kCt>(gf, mats, t0, tid, w, lane);
-    take_own(sm.qt, w, r, g, qr);
-    take_own(sm.kt, w, r, g, kr);
+        uint2 qr[4], kr[4];
+        const uint16_t *mats = states + size_t(unit) * 4 * kMat;
+        {
+            const ChunkRows cq = fetch_rows(q, t0, w, lane), ck = fetch_rows(k, t0, w, lane);
+            const ChunkRows cv = fetch_rows(v, t0, w, lane), cd = fetch_rows(dout, t0, w, lane);
+            put_rows<false>(sm.qt, cq, w, lane);
+            put_rows<false>(sm.kt, ck, w, lane);
+            put_rows<false>(sm.v, cv, w, lane);
+            put_rows<true>(sm.dout, cd, w, lane);
+        }
+        const DirInputs in_f = fetch_dir<0, kCt>(gf, mats, t0, tid, w, lane);
+        take_own(sm.qt, w, r, g, qr);
+        take_own(sm.kt, w, r, g, kr);
 
-    Grads acc;
+        Grads acc;
 #pragma unroll
-    for (int ct = 0; ct < 4; ++ct) acc.dq[ct] = acc.dk[ct] = acc.dv[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-    DirInputs in_b;
-    chunk_direction<0, kCt>(sm, in_f, dgf, t0, tid, w, lane, r, g, qr, kr, acc,
-                            [&]() { in_b = fetch_dir<1, kCt>(gb, mats, t0, tid, w, lane); });
-    chunk_direction<1, kCt>(sm, in_b, dgb, t0, tid, w, lane, r, g, qr, kr, acc, []() {});
+        for (int ct = 0; ct < 4; ++ct) acc.dq[ct] = acc.dk[ct] = acc.dv[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+        DirInputs in_b;
+        chunk_direction<0, kCt>(sm, in_f, dgf, t0, tid, w, lane, r, g, qr, kr, acc,
+                                [&]() { in_b = fetch_dir<1, kCt>(gb, mats, t0, tid, w, lane); });
+        chunk_direction<1, kCt>(sm, in_b, dgb, t0, tid, w, lane, r, g, qr, kr, acc, []() {});
 
-    store_own(sm.st, slab_rows(dq_all, first, L, heads_token_major, dk), t0, w, lane, r, g, acc.dq);
-    store_own(sm.ad, slab_rows(dk_all, first, L, heads_token_major, dk), t0, w, lane, r, g, acc.dk);
-    store_own(sm.v, slab_rows(dv_all, first, L, heads_token_major), t0, w, lane, r, g, acc.dv);
+        store_own(sm.st, slab_rows(dq_all, first, L, heads_token_major, dk), t0, w, lane, r, g, acc.dq);
+        store_own(sm.ad, slab_rows(dk_all, first, L, heads_token_major, dk), t0, w, lane, r, g, acc.dk);
+        store_own(sm.v, slab_rows(dv_all, first, L, heads_token_major), t0, w, lane, r, g, acc.dv);
+    }
+    if (marked == 0) return;
+    // gates beyond the range of this form; workgroups without a chunk to do come first
+    const unsigned below = unsigned(__popc(marked & ((1u << (slab - first_slab)) - 1u))), free_units = unsigned(__popc(marked)) * unsigned(n_chunks);
+    unsigned worker;
+    if (!has_chunk)
+        worker = free_units + (unit - units - first_slab * extra);
+    else if (own_marked)
+        worker = below * unsigned(n_chunks) + chunk;
+    else
+        worker = free_units + sharing * extra + (slab - first_slab - below) * unsigned(n_chunks) + chunk;
+    exact_strips<dk>(exact, exact_stage, first_slab, marked, worker, sharing * exact.workers_per_slab);
 }
 
 }  // namespace
@@ -951,20 +991,19 @@ hipError_t bigla_bwd_chunk_launch(const void *q, const void *k, const void *v, c
     char *base = static_cast<char *>(workspace);
     ws.states = reinterpret_cast<uint16_t *>(base);
     ws.logdec = reinterpret_cast<float *>(base + states_bytes(BH, L));
-    ws.marks = reinterpret_cast<int *>(base + states_bytes(BH, L) + logdec_bytes(BH, L));
+    ws.marks = reinterpret_cast<uint16_t *>(base + states_bytes(BH, L) + logdec_bytes(BH, L));
     auto launch = [&](auto ct) -> hipError_t {
         constexpr int kCt = decltype(ct)::value;
         // Walks as long as there are enough of them, or few chunks to walk; else a workgroup per chunk and a pass over the
         // matrices.
         const bool walk = BH * 4 >= kWalkWorkgroups || n_chunks <= kWalkShort;
-        int *marks = walk ? reinterpret_cast<int *>(ws.logdec) : ws.marks;
         if (walk) {
             hipLaunchKernelGGL(bigla_bwd_chunk_walk_kernel<kCt>, dim3((unsigned)(BH * 4)), dim3(kWalkThreads), 0, stream, q, k, v,
-                               g_fwd, g_bwd, d_out, ws.states, marks, L, heads_token_major, n_chunks, unsigned(BH));
+                               g_fwd, g_bwd, d_out, ws.states, ws.marks, L, heads_token_major, n_chunks, unsigned(BH));
         } else {
             const dim3 scan_grid((unsigned)(BH * 4 * (kCt * 256 / kScanThreads)));
             hipLaunchKernelGGL(bigla_bwd_chunk_local_kernel<kCt>, dim3((unsigned)units), dim3(kThreads), 0, stream, q, k, v,
-                               g_fwd, g_bwd, d_out, ws.states, ws.logdec, L, heads_token_major, n_chunks, dk_);
+                               g_fwd, g_bwd, d_out, ws.states, ws.logdec, ws.marks, L, heads_token_major, n_chunks, dk_);
             if (n_chunks > 16)
                 hipLaunchKernelGGL((bigla_bwd_chunk_scan_kernel<32, kCt>), scan_grid, dim3(kScanThreads), 0, stream, ws.states,
                                    ws.logdec, ws.marks, n_chunks);
@@ -972,9 +1011,16 @@ hipError_t bigla_bwd_chunk_launch(const void *q, const void *k, const void *v, c
                 hipLaunchKernelGGL((bigla_bwd_chunk_scan_kernel<8, kCt>), scan_grid, dim3(kScanThreads), 0, stream, ws.states,
                                    ws.logdec, ws.marks, n_chunks);
         }
-        hipLaunchKernelGGL(bigla_bwd_chunk_main_kernel<kCt>, dim3((unsigned)units), dim3(kThreads), 0, stream, q, k, v,
-                           g_fwd, g_bwd, d_out, dq, dk, dv, dg_fwd, dg_bwd, ws.states, marks, walk ? 8 : 1, exact_workspace, L,
-                           heads_token_major, n_chunks, unsigned(BH));
+        // Where the chunks leave compute units idle, workgroups without a chunk take strips of marked slabs (a slab
+        // has 16 for a workgroup each, 12 with 32-wide keys), up to two workgroups a unit.
+        const long extra = units < 512 ? std::min((512 - units) / BH, std::max(16L - n_chunks, 0L)) : 0;
+        auto in = [](const void *p) { return static_cast<const bf16_t *>(p); };
+        auto out = [](void *p) { return static_cast<bf16_t *>(p); };
+        const ExactArgs exact = {in(q), in(k), in(v), in(g_fwd), in(g_bwd), in(d_out), out(dq), out(dk), out(dv), out(dg_fwd), out(dg_bwd),
+                                 exact_workspace, L, heads_token_major, unsigned(BH), unsigned(n_chunks + extra)};
+        hipLaunchKernelGGL(bigla_bwd_chunk_main_kernel<kCt>, dim3((unsigned)(units + BH * extra)), dim3(kThreads), 0, stream, q, k, v,
+                           g_fwd, g_bwd, d_out, dq, dk, dv, dg_fwd, dg_bwd, ws.states, ws.marks, L, heads_token_major, n_chunks, unsigned(BH),
+                           unsigned(extra), exact);
         return hipGetLastError();
     };
     return dk_ == kD ? launch(std::integral_constant<int, 4>{}) : launch(std::integral_constant<int, 2>{});

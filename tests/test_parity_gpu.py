@@ -1311,3 +1311,21 @@ def test_bigla_bwd_slabs_of_both_forms(L, layout, dk):
     _say(f"bigla_bwd both forms L={L} dk={dk} {layout}")
     worst = _check_bwd(s, "bf16", layout, "auto")
     _say(f"  worst error / bound = {worst:.3f}")
+
+
+@pytest.mark.parametrize("B,H,L,dk,layout", ((1, 37, 40, 64, "bhld"), (5, 11, 64, 32, "blhd"), (3, 17, 130, 64, "blhd"),
+                                             (1, 17, 600, 64, "bhld"), (1, 5, 1100, 32, "blhd"), (41, 13, 50, 64, "bhld")))
+def test_bigla_bwd_marked_slabs_share_workgroups(B, H, L, dk, layout):
+    """Sixteen slabs' workgroups share out the token-by-token form of the marked ones among them: groups with one, some
+    and all marked and with none, the last group not full; fewer workgroups than strips, workgroups without a chunk, and
+    (533 slabs) a chip that is full without those; marks from walks and (17 and 5 long slabs) from the scan."""
+    w = wl.Workload("bwdmarked", B=B, H=H, Hg=1, Wg=L, dk=dk, dv=64, dtype="bf16", gate_mu=0.0)
+    s = _bwd_inputs(w, seed=L + dk)
+    gf, gb = (wl.widen(s[n], "bf16").reshape(B * H, L, dk) for n in ("g_fwd", "g_bwd"))
+    marked = [i for i in range(B * H) if i < 16 or i % 16 in (3, 4, 15) and i // 16 % 3 == 1 or i == B * H - 1]
+    for i in marked:
+        (gf if i % 2 else gb)[i, L // 3:] = -3.5
+    s["g_fwd"], s["g_bwd"] = (wl.store(g.reshape(B, H, L, dk), "bf16") for g in (gf, gb))
+    _say(f"bigla_bwd {B * H} slabs, {len(marked)} marked, L={L} dk={dk} {layout}")
+    worst = _check_bwd(s, "bf16", layout, "auto")
+    _say(f"  worst error / bound = {worst:.3f}")
