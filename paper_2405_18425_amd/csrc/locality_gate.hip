@@ -217,18 +217,23 @@ hipError_t launch(const void *x, const void *w, const void *bias, const void *z,
                   int H, int Hg, int Wg, int token_major, hipStream_t stream)
 {
     constexpr int CG = DV / vec4<T>::N;
-    // Taller strips re-read less (a strip of RS rows reads RS + 2 input rows) but mean fewer threads and
-    // more registers per thread.  8 rows while that still leaves about four workgroups per compute unit (48 slabs of
-    // 64 x 64: 20.2 us against 21.1 with 4 rows and 23.7 with 2; 384 of 14 x 14: 12.6 / 13.1 / 13.3) and the grid is taller
-    // than one strip (1024 slabs of 7 x 7: 11.3 / 10.6 / 11.6); then 4 rows while every compute unit has a workgroup
-    // (32 slabs of 56 x 56: 14.7 / 14.6 / 15.2; 80 of 28 x 28: 12.7 / 11.6 / 12.5; 15 of 37 x 53: 10.1 / 7.7 / 7.9), and 2 rows
-    // for small problems (6 slabs of 14 x 14: 6.8 / 6.9 / 6.5; event times, about 3 us above the kernel's own).
-    // Strips of 4 that hang far over the grid's end (heights of 9, 10, 17) lose more than they save: 2 rows where 4 cover
-    // over 15 % more rows (a call with 160 slabs of 9 x 33: 35.3 us with 4 rows, 34.4 with 2).
+    // Taller strips re-read less (a strip of RS rows reads RS + 2 input rows) but mean fewer threads and more registers per
+    // thread, and rows past the grid's end.  Full, a workgroup of strips of 8 takes as long as about 1.7 of strips of 4, and one
+    // of those as long as 1.6 of strips of 2; so the taller strip pays where the lower one needs more workgroups than that, or,
+    // where both leave lanes empty, more waves, as long as it leaves four workgroups per compute unit.
+    // Measured at 9400 shapes (both types, dv 16 to 64, 1 to 64 rows and columns, 6 to 4096 slabs; every strip height): within 2 %
+    // of the best height on average, 1.5 % with inputs from memory.  Examples, 2 / 4 / 8 rows in us: 32 slabs of 64 x 64 15.8 / 14.3 /
+    // 13.9, 1024 of 7 x 7 9.5 / 8.3 / 8.0, of 3 x 14 9.1 / 7.8 / 10.9, of 9 x 7 10.5 / 12.3 / 11.3 (bf16, 64 wide), 4096 of 8 x 33 49.7 / 62.6 /
+    // 49.2, 384 of 17 x 7 6.4 / 8.2 / 7.2 (fp32, 16 and 32 wide).
     const long slabs = long(B) * H;
-    auto blocks = [&](int rs) { return slabs * ((long((Hg + rs - 1) / rs) * Wg * CG + kThreads - 1) / kThreads); };
-    if (Hg > 8 && blocks(8) >= 1024) return launch_rs<T, DV, 8>(x, w, bias, z, og, out, slabs, H, Hg, Wg, token_major, stream);
-    if (blocks(4) >= 256 && 20 * ((Hg + 3) / 4 * 4) <= 23 * ((Hg + 1) / 2 * 2)) return launch_rs<T, DV, 4>(x, w, bias, z, og, out, slabs, H, Hg, Wg, token_major, stream);
+    auto strips = [&](int rs) { return (Hg + rs - 1) / rs; };
+    auto blocks = [&](int rs) { return slabs * ((long(strips(rs)) * Wg * CG + kThreads - 1) / kThreads); };
+    auto waves = [&](int rs) { return slabs * ((long(strips(rs)) * Wg * CG + 63) / 64); };
+    const bool fits = blocks(2) <= 0xffffffffL / kThreads;  // (work-items of a launch)
+    if (!fits || (blocks(8) >= 1024 && (10 * blocks(4) >= 17 * blocks(8) || 10 * waves(4) >= 17 * waves(8))))
+        return launch_rs<T, DV, 8>(x, w, bias, z, og, out, slabs, H, Hg, Wg, token_major, stream);
+    if (blocks(4) >= 1024 && (5 * blocks(2) >= 8 * blocks(4) || 5 * waves(2) >= 9 * waves(4)))
+        return launch_rs<T, DV, 4>(x, w, bias, z, og, out, slabs, H, Hg, Wg, token_major, stream);
     return launch_rs<T, DV, 2>(x, w, bias, z, og, out, slabs, H, Hg, Wg, token_major, stream);
 }
 

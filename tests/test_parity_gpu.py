@@ -401,6 +401,19 @@ def test_locality_edge_grids(dtype, Hg, Wg, dv):
         assert_close(got, ref, 8e-3 if dtype == "bf16" else 1e-5, f"{Hg}x{Wg}")
 
 
+@pytest.mark.parametrize("dtype", ("bf16", "f32"))
+@pytest.mark.parametrize("B,H,Hg,Wg,dv", [(26, 40, 7, 7, 64), (26, 40, 9, 7, 64), (26, 40, 5, 7, 64),  # strips of 8 rows
+                                          (26, 40, 3, 14, 64), (26, 40, 17, 3, 64),                    # of 4
+                                          (26, 40, 3, 5, 16), (26, 40, 1, 33, 64), (16, 24, 28, 9, 32), (16, 24, 17, 7, 32)])
+def test_locality_strip_heights(dtype, B, H, Hg, Wg, dv):
+    """Every height of the strips, in many slabs, at grid heights that are no multiple of it."""
+    w = wl.Workload("loc_strips", B=B, H=H, Hg=Hg, Wg=Wg, dk=dv, dv=dv, dtype=dtype, gate_mu=0.0)
+    _say(f"locality strips {dtype} {B * H} slabs of {Hg}x{Wg} dv{dv}")
+    x, cw, z, og = _loc_inputs(w, Hg * 100 + Wg)
+    got = run_locality_gpu(x, cw, z, og, Hg, Wg, dtype)
+    assert_close(got, run_locality_oracle(x, cw, z, og, Hg, Wg, dtype), 8e-3 if dtype == "bf16" else 1e-5, f"{Hg}x{Wg}")
+
+
 def test_path_end_to_end_config0():
     """BiGLA then the locality gate on v, as the benchmark chains them (x := v, o_global := BiGLA out)."""
     import torch
