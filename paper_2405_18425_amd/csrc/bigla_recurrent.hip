@@ -126,8 +126,14 @@ __global__ __launch_bounds__(128 * kPairs, 1) void bigla_recurrent_kernel(
 
 // A pair of waves per strip does about 1.7 times the work of the workgroup per slab, in a sixth of the time while the chip
 // is not full of strips: 16 slabs of 196 tokens, 64 x 64, fp32: 25 us against 191; 192: 109 / 241; 256: 137 / 246; 1024 (16384
-// strips): 550 / 323.  Short sequences fill it less well: slabs of 20 tokens in bf16, 256 (4096 strips): 32 / 26 us, 1024: 123 / 34.
-inline bool take_pairs(long strips, int L) { return strips <= (L >= 64 ? 5120 : 2048); }
+// strips): 550 / 323.  Short sequences fill it less well.  The limits are where the pairs are still no slower in any of the
+// nine head shapes, in fp32 and bf16 (time of the pairs over that of the workgroups, mean and largest of the shapes): 5120 strips of 400,
+// 196, 128, 100, 64 tokens 0.63 / 0.82, 0.72 / 1.00, 0.74 / 1.00, 0.84 / 1.15, 0.91 / 1.23; 4096 of 100, 80, 64: 0.71 / 0.97, 0.68 / 0.90,
+// 0.79 / 1.11; 3072 of 64: 0.66 / 0.96; 2048 of 49, 20, 16, 8: 0.65 / 0.93, 0.82 / 1.02, 0.83 / 0.94, 1.10 / 1.34; 1024 of 8: 0.68 / 0.84.
+inline bool take_pairs(long strips, int L)
+{
+    return strips <= (L >= 128 ? 5120 : L >= 80 ? 4096 : L >= 64 ? 3072 : L >= 16 ? 2048 : 1024);
+}
 
 template <typename T, int DK, int DV>
 hipError_t launch(const void *q, const void *k, const void *v, const void *gf, const void *gb, void *out,
