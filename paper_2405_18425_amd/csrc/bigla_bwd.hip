@@ -121,6 +121,7 @@ hipError_t launch_dk(int dk_, int dv_, const void *q, const void *k, const void 
 
 size_t bigla_bwd_workspace_bytes(long BH, int L, int dk, int dv, bool is_bf16)
 {
+    // (part_f, part_b and part_v are 2 dk + dv of these: what callers have asked for and may have written down stays)
     const size_t exact = size_t(BH) * L * (size_t(3) * dk + dv) * sizeof(float);
     return exact + (bigla_bwd_chunk_supported(dk, dv, is_bf16) ? bigla_bwd_chunk_workspace_bytes(BH, L) : 0);
 }

@@ -1342,3 +1342,25 @@ def test_bigla_bwd_marked_slabs_share_workgroups(B, H, L, dk, layout):
     _say(f"bigla_bwd {B * H} slabs, {len(marked)} marked, L={L} dk={dk} {layout}")
     worst = _check_bwd(s, "bf16", layout, "auto")
     _say(f"  worst error / bound = {worst:.3f}")
+
+
+@pytest.mark.parametrize("dtype,dk,dv,plan,L", (("f32", 64, 16, "auto", 50), ("f32", 16, 64, "auto", 9), ("bf16", 64, 64, "recurrent", 70),
+                                                ("bf16", 64, 64, "auto", 70), ("bf16", 32, 64, "auto", 700)))
+def test_bigla_bwd_stays_inside_its_workspace(dtype, dk, dv, plan, L):
+    """A workspace of exactly the bytes asked for, between guards that stay as they were; half the slabs marked."""
+    import torch
+    from paper_2405_18425_amd import binding as vb
+
+    B, H, guard = 1, 11, 1 << 16
+    s = _bwd_inputs(wl.Workload("bwdws", B=B, H=H, Hg=1, Wg=L, dk=dk, dv=dv, dtype=dtype, gate_mu=0.0), seed=L)
+    g = wl.widen(s["g_fwd"], dtype)
+    g[:, ::2] = -4.0
+    s["g_fwd"] = wl.store(g, dtype)
+    need = vb.lib().bigla_bwd_workspace_bytes(B, H, L, dk, dv, vb.VIG_F32 if dtype == "f32" else vb.VIG_BF16)
+    whole = torch.full((need + 2 * guard,), 0x5a, dtype=torch.uint8, device="cuda")
+    t = [wl.to_torch(s[n], dtype, "cuda:0") for n in BWD_NAMES]
+    got = vb.bigla_bwd(*t, plan=plan, workspace=whole[guard:guard + need])
+    want = vb.bigla_bwd(*t, plan=plan)
+    torch.cuda.synchronize()
+    assert bool((whole[:guard] == 0x5a).all()) and bool((whole[guard + need:] == 0x5a).all())
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
