@@ -324,6 +324,31 @@ def test_bigla_fwd_plans(plan, B, H, L, dk, mu):
     _say(f"  max|err|/max|ref| = {rel:.3e}")
 
 
+@pytest.mark.parametrize("plan", ("four_wave", "slab_sweep"))
+@pytest.mark.parametrize("layout,dk", (("bhld", 64), ("blhd", 64), ("bhld", 32)))
+@pytest.mark.parametrize("B,H,L", ((2, 3, 33), (2, 3, 64), (2, 3, 65), (2, 3, 250), (26, 5, 49), (26, 5, 129), (26, 5, 196)))
+def test_bigla_fwd_plans_short_sequences(plan, layout, dk, B, H, L):
+    """The four-wave kernels on one to four chunks, few slabs and many (one workgroup per slab), which bigla_fwd takes as one
+    chunk or with the eight-wave kernels: reached by name only.  One slab of fast decay and one with a stretch of it."""
+    import torch
+    from paper_2405_18425_amd import binding as vb
+
+    w = wl.Workload("plans_short", B=B, H=H, Hg=1, Wg=L, dk=dk, dv=64, dtype="bf16", gate_mu=-1.0)
+    _say(f"bigla_fwd_plan {plan} {layout} {w}")
+    s = wl.generate(w, seed=L + dk, tensors=("q", "k", "v", "g_fwd", "g_bwd"))
+    g = wl.widen(s["g_fwd"], "bf16")
+    g[0, 0] = -1.5
+    g[-1, -1, L // 3:L // 3 + 20, ::2] = -2.0
+    s["g_fwd"] = wl.store(g, "bf16")
+    t = [wl.to_torch(s[n], "bf16", "cuda:0") for n in ("q", "k", "v", "g_fwd", "g_bwd")]
+    if layout == "blhd":
+        t = [a.transpose(1, 2).contiguous() for a in t]
+    out = vb.bigla_fwd(*t, layout=layout, plan=plan)
+    torch.cuda.synchronize()
+    out = out.transpose(1, 2).contiguous() if layout == "blhd" else out
+    assert_close(wl.widen(wl.from_torch(out, "bf16"), "bf16"), run_bigla_oracle(s, "bf16"), TOL["bf16"], plan)
+
+
 @pytest.mark.parametrize("L", (1, 2, 3, 5, 31))
 def test_bigla_bwd_regression_tiny_slabs(L):
     """Slabs of a few tokens (inputs scaled by 1/4, gates near 1, both layouts): three-token slabs once
@@ -466,9 +491,9 @@ def test_path_end_to_end_hierarchical_stage_shapes(grid, H):
 
 
 @pytest.mark.parametrize("B,H,Hg,Wg,dk,layout,mu,with_bias", [
-    (2, 3, 8, 8, 64, "bhld", 0.0, False),       # one chunk per sequence: the general output kernel
+    (2, 3, 8, 8, 64, "bhld", 0.0, False),       # taken as one chunk, then blended in place
     (3, 3, 14, 14, 64, "bhld", 0.0, True),      # ragged final chunk, several segments per slab
-    (64, 2, 14, 14, 64, "bhld", 0.0, False),    # one-segment plan: state and output pass in one launch
+    (64, 2, 14, 14, 64, "bhld", 0.0, False),    # 196 tokens in many slabs: the same
     (2, 6, 32, 32, 64, "blhd", 2.0, True),
     (2, 3, 64, 64, 32, "bhld", -2.0, False),    # the benchmark grid, 32-wide keys
     (1, 3, 20, 13, 32, "blhd", -40.0, True),    # strong decay: range-safe form
@@ -482,12 +507,15 @@ def test_path_end_to_end_hierarchical_stage_shapes(grid, H):
     (1, 2, 128, 33, 64, "blhd", -1.0, True),    # 66 chunks in 33-token rows, many segments
     (2, 3, 40, 40, 64, "bhld", -12.0, True),    # every unit outside the fast form: general code inside the launches
     (1, 3, 33, 65, 64, "bhld", 0.0, True),      # one column too wide for it: the four-wave epilogue
+    (43, 6, 5, 70, 64, "bhld", 0.0, True),      # the same in many slabs: both passes and the epilogue in one launch
+    (43, 6, 5, 70, 32, "blhd", -1.0, False),
+    (43, 6, 4, 70, 64, "blhd", -30.0, True),    # and beyond the fast form
 ])
 def test_bigla_locality_plans(B, H, Hg, Wg, dk, layout, mu, with_bias):
     """Token mixer + locality blend as one call: the two-launch plan returns the same bits as the two
-    separate entry points; the fused-epilogue plan (the blend inside the output pass) does too wherever it
-    runs the kernel set that bigla_fwd runs, and elsewhere agrees to a few bf16 steps of the mixer's output
-    (the two sets round their operands differently); both are the oracle's chain within the path's
+    separate entry points; the fused-epilogue plan (the blend inside the output pass) does too where the token
+    mixer is one launch with the blend after it, and elsewhere agrees to a few bf16 steps of the mixer's output
+    (taps summed in pairs, operands rounded differently); both are the oracle's chain within the path's
     tolerance.  The conv input is a tensor of its own (not the mixer's v)."""
     import torch
     from paper_2405_18425_amd import binding as vb
@@ -515,13 +543,12 @@ def test_bigla_locality_plans(B, H, Hg, Wg, dk, layout, mu, with_bias):
     for plan in ("two_launches", "auto"):
         o = outs[plan]
         assert torch.equal(o, separate), f"{plan}: {(o != separate).sum().item()} elements differ from the separate calls"
-    # bigla_fwd runs the eight-wave kernels for at least two chunks unless the sequences are short and many;
-    # elsewhere both calls run the four-wave kernels, whose epilogue repeats the locality kernel's arithmetic
-    # (the eight-wave epilogue sums the taps in pairs)
-    n_chunks = (Hg * Wg + 63) // 64
-    eight_wave = n_chunks > 1 and not (B * H >= 128 and n_chunks <= 4)
+    # up to 64 tokens, and up to 256 in at least 128 slabs, bigla_fwd takes the sequence as one chunk and the
+    # fused plan does too, with the locality kernel after it; elsewhere bigla_fwd runs the eight-wave kernels
+    # and the plan those or, for wide grids, the four-wave ones (the eight-wave epilogue sums the taps in pairs)
+    one_chunk = Hg * Wg <= 64 or (B * H >= 128 and Hg * Wg <= 256)
     o = outs["fused_epilogue"]
-    if not eight_wave:
+    if one_chunk:
         assert torch.equal(o, separate), f"fused: {(o != separate).sum().item()} elements differ from the separate calls"
     else:  # a bf16 step of an output here and there
         d = (o.float() - separate.float()).abs()
