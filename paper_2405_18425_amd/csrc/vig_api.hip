@@ -303,8 +303,11 @@ int bigla_locality_fwd(const void *q, const void *k, const void *v, const void *
     if (vig::bigla_short_applicable(long(B) * H, L)) {
         // one launch takes the whole sequence as one chunk; the locality kernel then blends its output in place (a thread
         // reads the o_global of the pixels that it writes, before it writes them)
-        const int st = bigla_fwd_layout(q, k, v, g_fwd, g_bwd, out, B, H, L, dk, dv, dtype, layout, workspace, workspace_bytes, stream);
-        if (st != VIG_OK) return st;
+        // (its own entry point takes fewer token-major heads than the checks above)
+        clear_stale_hip_error();
+        const hipError_t e = vig::bigla_chunk_launch(q, k, v, g_fwd, g_bwd, out, long(B) * H, L, dk, layout == VIG_LAYOUT_BLHD ? H : 0,
+                                                     nullptr, VIG_FWD_AUTO, workspace, static_cast<hipStream_t>(stream));
+        if (e != hipSuccess) return hip_status(e);
         return locality_gate_fwd_layout(x, w, bias, gate_logits, out, out, B, H, Hg, Wg, dv, dtype, layout, stream);
     }
     const vig::LocalityFusion fusion = {x, w, bias, gate_logits, H, Hg, Wg};

@@ -1391,3 +1391,30 @@ def test_bigla_bwd_stays_inside_its_workspace(dtype, dk, dv, plan, L):
     torch.cuda.synchronize()
     assert bool((whole[:guard] == 0x5a).all()) and bool((whole[guard + need:] == 0x5a).all())
     assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+def test_bigla_locality_fused_plan_many_heads_token_major():
+    """More token-major heads than the token mixer's own entry takes: the fused plan's limit is the slab's 32-bit
+    offsets.  Heads from all over against the oracle."""
+    import oracle
+    import torch
+    from paper_2405_18425_amd import binding as vb
+
+    H, Hg, Wg, dk = 262_160, 4, 8, 32
+    heads = torch.tensor([0, 1, 77_777, H // 2, H - 2, H - 1])
+    _say(f"fused plan, {H} heads token-major")
+    g = torch.Generator(device="cuda").manual_seed(5)
+    make = lambda d: torch.randn((1, Hg * Wg, H, d), generator=g, device="cuda", dtype=torch.bfloat16)
+    t = [make(dk), make(dk), make(64), -make(dk).abs_() / 16, -make(dk).abs_() / 16, make(64)]
+    w, z = torch.randn((H * 64, 3, 3), generator=g, device="cuda", dtype=torch.bfloat16), make(64)
+    out = vb.bigla_locality_fwd(*t, w, z, Hg, Wg, layout="blhd", plan="fused_epilogue")
+    torch.cuda.synchronize()
+    pick = lambda a: a[:, :, heads.cuda()].transpose(1, 2).double().cpu().numpy()
+    taps = w.view(H, 64, 3, 3)[heads.cuda()].reshape(-1, 3, 3).double().cpu().numpy()
+    og = oracle.bigla(*(pick(a) for a in t[:5]))
+    ref = oracle.locality_gate(pick(t[5]), taps, pick(z), og, Hg, Wg)
+    rms = lambda a: np.sqrt(np.mean(a ** 2, axis=(2, 3), keepdims=True))
+    bound = TOL["bf16"] * (np.abs(ref) + rms(ref) + np.abs(og) + rms(og))
+    assert np.all(np.abs(pick(out) - ref) <= bound)
+    del t, w, z, out
+    torch.cuda.empty_cache()
