@@ -27,7 +27,7 @@ namespace vig {
 
 namespace {
 
-// 12 slabs of 196 tokens, 64 x 64, fp32: 40.4 us (a workgroup per 16 rows or columns, tokens through LDS, two launches: 54 +
+// 12 slabs of 196 tokens, 64 x 64, fp32: 40.7 us (a workgroup per 16 rows or columns, tokens through LDS, two launches: 54 +
 // 61); 1024 slabs 1.65 ms (2.97), 8192 slabs of 20 tokens in bf16 2.1 ms (12.7).  Bound by its instructions, about 90 a token and wave.
 // kPairs: strips of one slab per workgroup.  A slab's strips are first the DK / kRows of dq, dk and dg, then the
 // DV / kCols of dv; a workgroup has strips of one kind only, so that its waves meet the same barriers.

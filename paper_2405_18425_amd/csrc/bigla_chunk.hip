@@ -1191,7 +1191,7 @@ hipError_t chunk_launch(const void *q, const void *k, const void *v, const void 
                                dim3(kThreads), 0, stream, qq, kk, vv, gf, gb, oo, seg_in, flags, stash, L, p.n_chunks,
                                p.seg_chunks, p.n_seg, heads_token_major, lf);
         else if constexpr (kLoc)
-            return hipErrorInvalidValue;  // (sequences of a single chunk are blended by the locality kernel)
+            return hipErrorInvalidValue;  // (a guard: sequences of a single chunk are blended by the locality kernel)
         else  // a single chunk per sequence: no state kernel has run, no flags exist
             hipLaunchKernelGGL((bigla_segment_out_kernel<false, kDk, kTm, kLoc>), dim3((unsigned)blocks),
                                dim3(kThreads), 0, stream, qq, kk, vv, gf, gb, oo, seg_in, flags, stash, L, p.n_chunks,

@@ -952,7 +952,7 @@ __global__ __launch_bounds__(kWsThreads) void bigla_ws_out_kernel(
 bool bigla_chunk_ws_applicable(long BH, int L, int dk)
 {
     const Plan p = make_ws_plan(BH, L);
-    // short sequences with at least half a chip of slabs stay with the single-launch slab kernel
+    // short sequences with at least half a chip of slabs are one launch: the one-chunk kernel, or by name the slab kernel
     if (BH >= 128 && p.n_chunks <= 4) return false;
     return (dk == kD || dk == kD / 2) && p.n_chunks > 1;
 }

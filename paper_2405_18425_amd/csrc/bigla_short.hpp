@@ -19,8 +19,8 @@
 // A slab in which some 64-token stretch decays by more than kMildRange in a channel (a sequence of fewer tokens: by more than
 // its share of that) takes the range-safe form of bigla_chunk.hip, tile by tile (short_slab_safe), inside the same launch.
 //
-// Measured (kernel trace): 384 slabs of 196 tokens, 57.8 MB: 22.9 us (the chunked kernel that walks a slab twice in one
-// launch: 32.0 us); 192 slabs: 14.9 us (23.2); 1024 slabs of 49 tokens: 14.4 us (the general single-chunk kernel: 69.4).
+// Measured (kernel trace): 384 slabs of 196 tokens, 57.8 MB: 23.0 us (the chunked kernel that walks a slab twice in one
+// launch: 32.0 us); 192 slabs: 14.7 us (23.2); 1024 slabs of 49 tokens: 13.8 us (the general single-chunk kernel: 69.4).
 // What bounds it: with two workgroups per CU the phases of one overlap those of the other, and a SIMD then spends about
 // equal times on the exponentials and scalings (24 vector instructions and 4 exponentials per 64 elements of q and k)
 // and on matrix instructions; a lone workgroup is a chain of 25 000 cycles: 6000 until the rows arrive, 5000 for the
@@ -614,6 +614,9 @@ __global__ __launch_bounds__(64 * kShortWaves, 4) void bigla_short_kernel(
 // the range-safe form, as the four-wave kernels do (at -0.3 a step, 192 and 384 slabs of 196 tokens 34 and 55 us against 67 and
 // 96), but the eight-wave kernels stay in the fast form up to 60: 48 slabs 28 us against 14.  Whose gates those are is known
 // on the device only, so calls that the eight-wave kernels can take (two chunks or more, fewer than 128 slabs) stay with them.
+// Up to 64 tokens the other choice is the general single-chunk kernel, the slower one in either form: 3 / 48 / 192 / 1024 slabs of 64
+// tokens with mild gates 5.9 / 6.1 / 6.8 / 14.6 us against 10.8 / 12.0 / 19.0 / 68.7, at -0.3 a step 10.0 / 10.5 / 12.2 / 35.8
+// against 14.0 / 15.4 / 23.7 / 80.9.
 // The score matrix grows with the square of the length: beyond 256 tokens the sequence is chunked.
 bool bigla_short_applicable(long BH, int L) { return L <= kShortTokens && (BH >= 128 || L <= kC); }
 
