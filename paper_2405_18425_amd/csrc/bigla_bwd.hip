@@ -27,12 +27,12 @@ namespace vig {
 
 namespace {
 
-// 12 slabs of 196 tokens, 64 x 64, fp32: 40.7 us (a workgroup per 16 rows or columns, tokens through LDS, two launches: 54 +
-// 61); 1024 slabs 1.65 ms (2.97), 8192 slabs of 20 tokens in bf16 2.1 ms (12.7).  Bound by its instructions, about 90 a token and wave.
+// 12 slabs of 196 tokens, 64 x 64, fp32: 34.8 us (in one part per strip 39.7; a workgroup per 16 rows or columns, tokens through
+// LDS, two launches: 54 + 61); 1024 slabs 1.65 ms (2.97), 8192 slabs of 20 tokens in bf16 2.1 ms (12.7).  Bound by its instructions, about 90 a token and wave.
 // kPairs: strips of one slab per workgroup.  A slab's strips are first the DK / kRows of dq, dk and dg, then the
 // DV / kCols of dv; a workgroup has strips of one kind only, so that its waves meet the same barriers.
-template <typename T, int DK, int DV, int kPairs, typename Off>
-__global__ __launch_bounds__(128 * kPairs, 1) void bigla_bwd_exact_kernel(
+template <typename T, int DK, int DV, int kPairs, typename Off, int kParts>
+__global__ __launch_bounds__(128 * kPairs * kParts, 1) void bigla_bwd_exact_kernel(
     const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, const T *__restrict__ gf,
     const T *__restrict__ gb, const T *__restrict__ d_out, T *__restrict__ dq, T *__restrict__ dk, T *__restrict__ dv,
     T *__restrict__ dgf, T *__restrict__ dgb, float *part_f /* [slabs][L][DK] */, float *part_b /* same */,
@@ -40,22 +40,25 @@ __global__ __launch_bounds__(128 * kPairs, 1) void bigla_bwd_exact_kernel(
     unsigned n_slabs /* of this launch */)
 {
     constexpr int kRowWork = DK / (kStrip * (64 / DV)) / kPairs;  // workgroups of a slab that take rows
-    __shared__ RowStage<DV> stage[2 * kPairs];
+    static_assert(kPairs == 1 || kParts == 1, "one strip's parts per workgroup");
+    __shared__ RowStage<DV> stage[2 * kPairs * kParts];
+    __shared__ PartStage<kParts> parts;
     const unsigned slab = first_slab + blockIdx.x % n_slabs;
     const int work = int(blockIdx.x / n_slabs);
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x)) >> 6, lane = int(threadIdx.x) & 63;
     const bool descending = (wave & 1) != 0;
+    const int pair = kPairs > 1 ? wave >> 1 : 0, part = kParts > 1 ? wave >> 1 : 0;
     const size_t row0 = slab_first_row(slab, L, heads_token_major);
     const size_t step = heads_token_major ? heads_token_major : 1;
     if (work < kRowWork)
-        row_sweep<T, DK, DV, Off>(q + row0 * DK, k + row0 * DK, v + row0 * DV, gf + row0 * DK, gb + row0 * DK, d_out + row0 * DV,
+        row_sweep<T, DK, DV, Off, kParts>(q + row0 * DK, k + row0 * DK, v + row0 * DV, gf + row0 * DK, gb + row0 * DK, d_out + row0 * DV,
                              dq + row0 * DK, dk + row0 * DK, dgf + row0 * DK, dgb + row0 * DK, part_f + size_t(slab) * L * DK,
-                             part_b + size_t(slab) * L * DK, stage[wave], step, L, descending, work * kPairs + (wave >> 1), lane);
+                             part_b + size_t(slab) * L * DK, stage[wave], step, L, descending, part, parts, work * kPairs + pair, lane);
     else
         // the adjoint that runs with the wave belongs to the other direction
-        column_sweep<T, DK, DV, true, Off>(q + row0 * DK, k + row0 * DK, (descending ? gf : gb) + row0 * DK, d_out + row0 * DV,
+        column_sweep<T, DK, DV, true, Off, kParts>(q + row0 * DK, k + row0 * DK, (descending ? gf : gb) + row0 * DK, d_out + row0 * DV,
                                       part_v + size_t(slab) * L * DV, dv + row0 * DV, step, 1, L, descending,
-                                      (work - kRowWork) * kPairs + (wave >> 1), 0.5f, 1.f, lane);
+                                      part, parts, (work - kRowWork) * kPairs + pair, 0.5f, 1.f, lane);
 }
 
 template <typename T, int DK, int DV>
@@ -65,14 +68,14 @@ hipError_t launch(const void *q, const void *k, const void *v, const void *gf, c
 {
     constexpr int kRowStrips = DK / (kStrip * (64 / DV)), kColStrips = DV / (kStrip * (64 / DK));
     float *part_f = ws, *part_b = ws + size_t(BH) * L * DK, *part_v = part_b + size_t(BH) * L * DK;
-    auto run = [&](auto pairs, auto offset) -> hipError_t {
-        constexpr int kPairs = decltype(pairs)::value;
+    auto run = [&](auto pairs, auto offset, auto parts) -> hipError_t {
+        constexpr int kPairs = decltype(pairs)::value, kParts = decltype(parts)::value;
         // a launch has fewer than 2^32 work-items (one of more goes wrong without an error): further slabs in another one
-        constexpr long kMost = 0xffffffffL / (128 * (kRowStrips + kColStrips));
+        constexpr long kMost = 0xffffffffL / (128 * kParts * (kRowStrips + kColStrips));
         for (long first = 0; first < BH; first += kMost) {
             const long slabs = BH - first < kMost ? BH - first : kMost;
             const long blocks = slabs * ((kRowStrips + kColStrips) / kPairs);
-            hipLaunchKernelGGL((bigla_bwd_exact_kernel<T, DK, DV, kPairs, decltype(offset)>), dim3((unsigned)blocks), dim3(128 * kPairs), 0, stream,
+            hipLaunchKernelGGL((bigla_bwd_exact_kernel<T, DK, DV, kPairs, decltype(offset), kParts>), dim3((unsigned)blocks), dim3(128 * kPairs * kParts), 0, stream,
                                static_cast<const T *>(q), static_cast<const T *>(k), static_cast<const T *>(v),
                                static_cast<const T *>(gf), static_cast<const T *>(gb), static_cast<const T *>(d_out),
                                static_cast<T *>(dq), static_cast<T *>(dk), static_cast<T *>(dv), static_cast<T *>(dgf),
@@ -83,12 +86,20 @@ hipError_t launch(const void *q, const void *k, const void *v, const void *gf, c
         }
         return hipSuccess;
     };
+    using std::integral_constant;
     if (!tile_fits_32_bits(heads_token_major ? heads_token_major : 1, DK > DV ? DK : DV, sizeof(T)))
-        return run(std::integral_constant<int, 1>{}, size_t{});
+        return run(integral_constant<int, 1>{}, size_t{}, integral_constant<int, 1>{});
+    // Parts of a strip's tokens (exact_sweep.hpp) while a compute unit has one strip, or two of two parts each.  fp32, us for 1 / 2 /
+    // 4 parts: 8 slabs (256 strips, 64 x 64) of 196 tokens 37.8 / 32.9 / 25.8, of 98 22.0 / 20.1 / 15.6, of 56 13.7 / 12.6 / 10.0, of 32
+    // 8.4 / 8.0 / 8.3; 12 slabs of 196 39.7 / 34.8 / 44.8, of 17 8.7 / 8.4 / 12.7; 20 (640 strips) of 196 41.9 / 54.7 / 63.5; 128 slabs of
+    // 196, 16 x 16, 54.6 / 48.9 / 36.1.
+    const long strips = BH * (kRowStrips + kColStrips);
+    if (strips <= 256 && L >= 40) return run(integral_constant<int, 1>{}, 0u, integral_constant<int, 4>{});
+    if (strips <= 512 && L > kTile) return run(integral_constant<int, 1>{}, 0u, integral_constant<int, 2>{});
     // as in the forward: one pair per workgroup until every compute unit has one
     if constexpr (kRowStrips % 2 == 0 && kColStrips % 2 == 0)
-        if (BH * (kRowStrips + kColStrips) > 512) return run(std::integral_constant<int, 2>{}, 0u);
-    return run(std::integral_constant<int, 1>{}, 0u);
+        if (BH * (kRowStrips + kColStrips) > 512) return run(integral_constant<int, 2>{}, 0u, integral_constant<int, 1>{});
+    return run(integral_constant<int, 1>{}, 0u, integral_constant<int, 1>{});
 }
 
 template <typename T, int DK>

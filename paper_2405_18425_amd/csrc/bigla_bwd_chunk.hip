@@ -873,6 +873,7 @@ __device__ __forceinline__ void exact_strips(const ExactArgs &a, RowStage<kD> (&
     const bool descending = (wave & 1) != 0;
     const size_t step = a.heads_token_major ? a.heads_token_major : 1, keys = size_t(a.L) * DK, all_keys = keys * a.n_slabs;
     const unsigned n_marked = unsigned(__popc(marked));
+    PartStage<1> whole;
 #pragma unroll 1
     for (unsigned i = worker; i < n_marked * (kRowItems + kColItems); i += workers) {
         // (what depends on the lane is formed anew for every strip: hoisted out of this loop, the offsets of both kinds of
@@ -887,12 +888,12 @@ __device__ __forceinline__ void exact_strips(const ExactArgs &a, RowStage<kD> (&
         float *parts = a.parts + slab * keys;
         if (item < kRowItems)
             row_sweep<bf16_t, DK, kD>(a.q + k0, a.k + k0, a.v + v0, a.gf + k0, a.gb + k0, a.d_out + v0, a.dq + k0, a.dk + k0,
-                                      a.dgf + k0, a.dgb + k0, parts, parts + all_keys, stage[wave], step, a.L, descending,
+                                      a.dgf + k0, a.dgb + k0, parts, parts + all_keys, stage[wave], step, a.L, descending, 0, whole,
                                       int(2 * item) + (wave >> 1), lane);
         else
             column_sweep<bf16_t, DK, kD, true>(a.q + k0, a.k + k0, (descending ? a.gf : a.gb) + k0, a.d_out + v0,
                                                a.parts + 2 * all_keys + size_t(slab) * a.L * kD, a.dv + v0, step, 1, a.L,
-                                               descending, int(2 * (item - kRowItems)) + (wave >> 1), 0.5f, 1.f, lane);
+                                               descending, 0, whole, int(2 * (item - kRowItems)) + (wave >> 1), 0.5f, 1.f, lane);
     }
 }
 

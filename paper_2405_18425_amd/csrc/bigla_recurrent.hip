@@ -104,24 +104,26 @@ __global__ __launch_bounds__(DV *kSplit) void bigla_recurrent_staged_kernel(
 // ---- few slabs: a pair of waves per strip of columns -------------------------------------------------
 // kPairs: column strips of one slab per workgroup, so that they find the slab's rows in the compute
 // unit's own cache.
-template <typename T, int DK, int DV, int kPairs>
-__global__ __launch_bounds__(128 * kPairs, 1) void bigla_recurrent_kernel(
+template <typename T, int DK, int DV, int kPairs, int kParts>
+__global__ __launch_bounds__(128 * kPairs * kParts, 1) void bigla_recurrent_kernel(
     const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, const T *__restrict__ g_fwd,
     const T *__restrict__ g_bwd, T *out, float *o_part /* may alias out (fp32) */, int L,
     int heads_token_major /* 0: [B,H,L,d]; H: [B,L,H,d] */, unsigned n_slabs, bool part_in_out)
 {
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x)) >> 6, lane = int(threadIdx.x) & 63;
+    static_assert(kPairs == 1 || kParts == 1, "one strip's parts per workgroup");
+    __shared__ PartStage<kParts> parts;
     const unsigned slab = blockIdx.x % n_slabs;
-    const int col_block = int(blockIdx.x / n_slabs) * kPairs + (wave >> 1);
+    const int col_block = int(blockIdx.x / n_slabs) * kPairs + (kPairs > 1 ? wave >> 1 : 0);
     const bool descending = (wave & 1) != 0;
     // first row of the slab and distance between its tokens, in rows of the tensor
     const size_t row0 = slab_first_row(slab, L, heads_token_major);
     const size_t step = heads_token_major ? heads_token_major : 1;
     // the fp32 side buffer is dense [slab][L][DV]; when the partial sums live in `out` they follow it
     float *park = o_part + (part_in_out ? row0 : size_t(slab) * L) * DV;
-    column_sweep<T, DK, DV, false>(k + row0 * DK, q + row0 * DK, (descending ? g_bwd : g_fwd) + row0 * DK, v + row0 * DV,
-                                   park, out + row0 * DV, step, part_in_out ? step : 1, L, descending, col_block, 1.f,
-                                   0.5f, lane);
+    column_sweep<T, DK, DV, false, unsigned, kParts>(k + row0 * DK, q + row0 * DK, (descending ? g_bwd : g_fwd) + row0 * DK,
+                                                     v + row0 * DV, park, out + row0 * DV, step, part_in_out ? step : 1, L,
+                                                     descending, kParts > 1 ? wave >> 1 : 0, parts, col_block, 1.f, 0.5f, lane);
 }
 
 // A pair of waves per strip does about 1.7 times the work of the workgroup per slab, in a sixth of the time while the chip
@@ -149,22 +151,29 @@ hipError_t launch(const void *q, const void *k, const void *v, const void *gf, c
         return hipGetLastError();
     }
     const bool part_in_out = static_cast<void *>(o_part) == out;
-    auto run = [&](auto pairs) -> hipError_t {
-        constexpr int kPairs = decltype(pairs)::value;
+    auto run = [&](auto pairs, auto parts) -> hipError_t {
+        constexpr int kPairs = decltype(pairs)::value, kParts = decltype(parts)::value;
         const long blocks = long(BH) * (kBlocks / kPairs);
         if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
         LaunchTimer timer(kKernelRecurrent, stream);
-        hipLaunchKernelGGL((bigla_recurrent_kernel<T, DK, DV, kPairs>), dim3((unsigned)blocks), dim3(128 * kPairs), 0,
+        hipLaunchKernelGGL((bigla_recurrent_kernel<T, DK, DV, kPairs, kParts>), dim3((unsigned)blocks), dim3(128 * kPairs * kParts), 0,
                            stream, static_cast<const T *>(q), static_cast<const T *>(k), static_cast<const T *>(v),
                            static_cast<const T *>(gf), static_cast<const T *>(gb), static_cast<T *>(out), o_part, L,
                            heads_token_major, unsigned(BH), part_in_out);
         return hipGetLastError();
     };
+    using std::integral_constant;
+    // A strip per compute unit at most, of sequences long enough for a walk over a quarter of them to pay for the one that
+    // finds what enters it: four parts.  The walks are bound by the instructions their SIMD can issue, so with two strips on
+    // a compute unit the extra ones cost more than the shorter way gains.  fp32, us for 1 / 2 / 4 parts: 12 slabs (192 strips, 64 x 64) of
+    // 196 tokens 23.3 / 23.2 / 20.5, of 98 14.3 / 14.6 / 13.3, of 56 9.7 / 9.5 / 8.1, of 32 5.8 / 6.0 / 6.1; 20 slabs (320 strips) of 196
+    // 26.2 / 30.9 / 37.5; one slab of 1024 104 / 88 / 68.
+    if (long(BH) * kBlocks <= 256 && L >= 40) return run(integral_constant<int, 1>{}, integral_constant<int, 4>{});
     // Few strips: one pair per workgroup, so that they spread over the compute units.  More than one pair
     // for every unit: two per workgroup, which read the slab's rows from memory once.
     if constexpr (kBlocks % 2 == 0)
-        if (long(BH) * kBlocks > 256) return run(std::integral_constant<int, 2>{});
-    return run(std::integral_constant<int, 1>{});
+        if (long(BH) * kBlocks > 256) return run(integral_constant<int, 2>{}, integral_constant<int, 1>{});
+    return run(integral_constant<int, 1>{}, integral_constant<int, 1>{});
 }
 
 template <typename T, int DK>

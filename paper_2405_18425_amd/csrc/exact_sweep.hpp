@@ -16,7 +16,14 @@
 // other has parked to its own.  For 12 slabs of 196 tokens, 64 x 64, fp32 (a workgroup per slab and one
 // direction after the other, tokens through LDS, took 236 us for the forward; a workgroup per 16 rows,
 // tokens through LDS, 54 + 61 us for the gradient) see the measurements at the kernels.
+// Where the strips leave most of the chip idle, a strip's tokens are cut into kParts parts with a pair of waves
+// each.  The matrix is linear in what enters a part, so a wave first walks its part from zero for the matrix it
+// leaves and its total decay alone (about half the instructions of the walk with readouts), the waves of a direction
+// exchange the two through LDS, and each then walks its part from what the parts before it leave.  The same products
+// and sums as in one walk, in fewer steps: the error against fp64 stays what it was.
 #pragma once
+
+#include <type_traits>
 
 #include "vig_common.hpp"
 
@@ -29,8 +36,8 @@ constexpr int kTile = 8;    // tokens whose readouts are summed over the lanes t
 // Tiles whose operands are in registers or on their way there.  Offsets inside a tile are 32 bits wide (Off = unsigned)
 // unless its eight tokens span more than that, which takes millions of token-major heads: with 64 bits they are twice the
 // registers, and the chip is full of strips whatever a wave has in flight.
-template <typename Off>
-constexpr int kDepth = sizeof(Off) == 4 ? 3 : 1;
+template <typename Off, int kParts>
+constexpr int kDepth = sizeof(Off) == 4 ? (kParts > 1 ? 2 : 3) : 1;
 inline bool tile_fits_32_bits(size_t step, int width, size_t value_bytes)
 {
     return size_t(kTile) * step * width * value_bytes <= 0xffffffffu;
@@ -148,17 +155,14 @@ __device__ __forceinline__ float gate_factor(float g)
     return fmaf(e, 0.693147182464599609375f * rest, e);
 }
 
-// The way of one direction over the tokens: tile number n of it covers the tokens token(n, 0..kTile-1) in
-// visiting order.  Both directions share the tile boundaries; a ragged last tile belongs to the
+// The way of one direction over the tokens of a part (whole tiles of the sequence): tile number n of it covers the tokens
+// token(n, 0..kTile-1) in visiting order.  Both directions share the tile boundaries; a ragged last tile belongs to the
 // sequence's end.
 struct Way {
-    int L, tiles;
+    int L, start, tiles;  // first tile of the part and how many it has
     bool descending;
-    __device__ __forceinline__ int token(int n, int i) const
-    {
-        return descending ? (tiles - 1 - n) * kTile + (kTile - 1 - i) : n * kTile + i;
-    }
-    __device__ __forceinline__ int low(int n) const { return (descending ? tiles - 1 - n : n) * kTile; }
+    __device__ __forceinline__ int low(int n) const { return (start + (descending ? tiles - 1 - n : n)) * kTile; }
+    __device__ __forceinline__ int token(int n, int i) const { return low(n) + (descending ? kTile - 1 - i : i); }
     __device__ __forceinline__ bool ragged(int n) const { return low(n) + kTile > L; }
     // offset in a tile of its last token
     __device__ __forceinline__ unsigned last_offset(int n) const { return unsigned(min(kTile - 1, L - 1 - low(n))); }
@@ -171,28 +175,78 @@ struct Way {
     __device__ __forceinline__ int first_half() const { return descending ? tiles - tiles / 2 : tiles / 2; }
 };
 
-__device__ __forceinline__ Way make_way(int L, bool descending)
+template <int kParts>
+__device__ __forceinline__ Way make_way(int L, bool descending, int part)
 {
+    const int tiles = (L + kTile - 1) / kTile;
     Way w;
     w.L = L;
-    w.tiles = (L + kTile - 1) / kTile;
+    w.start = tiles * part / kParts;
+    w.tiles = tiles * (part + 1) / kParts - w.start;
     w.descending = descending;
     return w;
+}
+
+// Calls walk(operands, n) for the tiles first .. last - 1 of a way, with the operands of kDepth tiles requested ahead by fetch
+template <typename Operands, int kAhead, typename Fetch, typename Walk>
+__device__ __forceinline__ void over_tiles(int first, int last, Fetch fetch, Walk walk)
+{
+    if (first >= last) return;
+    Operands o[kAhead];
+#pragma unroll
+    for (int d = 0; d < kAhead; ++d) fetch(o[d], first + d);
+    int n = first;
+    for (; n + kAhead <= last; n += kAhead) {
+#pragma unroll
+        for (int d = 0; d < kAhead; ++d) {
+            walk(o[d], n + d);
+            fetch(o[d], n + d + kAhead);
+        }
+    }
+#pragma unroll
+    for (int d = 0; d < kAhead - 1; ++d)
+        if (n + d < last) walk(o[d], n + d);
+}
+
+// What the waves of a strip exchange between its parts: a lane's elements of the matrices a part leaves when nothing enters
+// it, and the decay over the part, per direction and part.  (A column sweep has one matrix, a row sweep two.)
+template <int kParts>
+struct PartStage {
+    float4 end[2][kParts][2][64], decay[2][kParts][2][64];
+};
+template <>
+struct PartStage<1> {};
+
+// M: what enters the wave's part, from what the parts before it on its way leave
+template <int kParts>
+__device__ __forceinline__ void enter_part(const PartStage<kParts> &ex, int matrix, bool descending, int part, int lane, float (&M)[kStrip])
+{
+    const int before = descending ? kParts - 1 - part : part;
+    for (int u = 0; u < before; ++u) {
+        const int from = descending ? kParts - 1 - u : u;
+        const float4 e = ex.end[descending][from][matrix][lane], d = ex.decay[descending][from][matrix][lane];
+        M[0] = fmaf(d.x, M[0], e.x);
+        M[1] = fmaf(d.y, M[1], e.y);
+        M[2] = fmaf(d.z, M[2], e.z);
+        M[3] = fmaf(d.w, M[3], e.w);
+    }
 }
 
 // Readouts over the rows of the matrix: M_t = diag(alpha) M_prev + u_t^T (b_scale * b_t), result_t = r_t M_t, for the
 // strip of columns col0 .. (64 / DK strips of four side by side in a wave).  kDelayed false: alpha is the gate of
 // the token itself (a state: u = k, b = v, r = q); true: the gate of the token visited before (an adjoint: u = q,
 // b = d_out, r = k).  `park`: fp32, dense or strided like the result; result = result_scale * (own + parked).
-// One barrier, executed by every wave that calls this.  `park` and `result` may be one buffer (fp32).
-template <typename T, int DK, int DV, bool kDelayed, typename Off = unsigned>
+// One barrier, and one more with several parts, executed by every wave that calls this.  `park` and `result` may be one
+// buffer (fp32).
+template <typename T, int DK, int DV, bool kDelayed, typename Off = unsigned, int kParts = 1>
 __device__ __forceinline__ void column_sweep(const T *u_rows, const T *r_rows, const T *g_rows, const T *b_rows,
                                              float *park, T *result, size_t step, size_t park_step, int L,
-                                             bool descending, int col_block, float b_scale, float result_scale, int lane)
+                                             bool descending, int part, PartStage<kParts> &parts, int col_block,
+                                             float b_scale, float result_scale, int lane)
 {
     constexpr int kGroups = 64 / DK;
     constexpr int kH = kHeld<DK>;
-    const Way way = make_way(L, descending);
+    const Way way = make_way<kParts>(L, descending, part);
     const int ch = lane % DK;
     int col0 = (col_block * kGroups + lane / DK) * kStrip;
     // kept out of the scalar unit where a wave has one strip: scalar loads of the strip's operands, three
@@ -205,7 +259,8 @@ __device__ __forceinline__ void column_sweep(const T *u_rows, const T *r_rows, c
     struct Operands {
         float u[kTile], r[kTile], g[kTile], b[kTile][kStrip], other[kH];
     };
-    float M[kStrip] = {0.f, 0.f, 0.f, 0.f}, before = 0.f;
+    // (delayed: `before` is the gate of the token visited before; what enters a part has it applied already)
+    float M[kStrip] = {0.f, 0.f, 0.f, 0.f}, before = 1.f;
     // a whole tile's offsets, the same in every tile (a wave alone on its SIMD pays for scalar address
     // arithmetic as much as for any other instruction)
     Off off_k[kTile], off_v[kTile];
@@ -216,23 +271,70 @@ __device__ __forceinline__ void column_sweep(const T *u_rows, const T *r_rows, c
         off_v[i] = at_byte<T>(t * DV + unsigned(col0));
     }
 
+    // the rows of tile n, readout operands too where kRead
+    auto fetch_rows = [&](Operands &o, int n, auto read) __attribute__((always_inline)) {
+        const size_t low = size_t(way.low(n));
+        const T *u = u_rows + low * step * DK, *r = r_rows + low * step * DK, *g = g_rows + low * step * DK;
+        const T *b = b_rows + low * step * DV;
+        // (a token past the sequence repeats the last one's offset, so every address is valid)
+        const Off last_token = Off(way.last_offset(n)) * Off(step);
+        const Off end_k = at_byte<T>(last_token * DK + unsigned(ch)), end_v = at_byte<T>(last_token * DV + unsigned(col0));
+#pragma unroll
+        for (int i = 0; i < kTile; ++i) {
+            const Off tk = min(off_k[i], end_k), tv = min(off_v[i], end_v);
+            o.u[i] = io<T>::load(at(u, tk));
+            if constexpr (decltype(read)::value) o.r[i] = io<T>::load(at(r, tk));
+            o.g[i] = io<T>::load(at(g, tk));
+            load_strip(at(b, tv), o.b[i]);
+        }
+    };
+    // tokens past the sequence: nothing enters the matrix (ascending they come last, descending first, when it is still zero)
+    auto clear_past_end = [&](Operands &o, int n) __attribute__((always_inline)) {
+        if (way.ragged(n)) {
+#pragma unroll
+            for (int i = 0; i < kTile; ++i) {
+                if (way.token(n, i) < L) continue;
+                o.u[i] = 0.f;
+                o.g[i] = 0.f;
+#pragma unroll
+                for (int c = 0; c < kStrip; ++c) o.b[i][c] = 0.f;
+            }
+        }
+    };
+    auto advance = [&](const Operands &o, int i) __attribute__((always_inline)) {
+        const float alpha = gate_factor(o.g[i]);
+        const float decay = kDelayed ? before : alpha;
+#pragma unroll
+        for (int c = 0; c < kStrip; ++c)
+            M[c] = fmaf(decay, M[c], o.u[i] * (kDelayed ? b_scale * o.b[i][c] : o.b[i][c]));
+        before = alpha;
+        return alpha;
+    };
+    if constexpr (kParts > 1) {
+        if (part != (descending ? 0 : kParts - 1)) {  // (nobody enters anything after the last part)
+            float total = 1.f;
+            auto fetch = [&](Operands &o, int n) __attribute__((always_inline)) { fetch_rows(o, min(n, way.tiles - 1), std::false_type{}); };
+            auto walk = [&](Operands &o, int n) __attribute__((always_inline)) {
+                clear_past_end(o, n);
+#pragma unroll
+                for (int i = 0; i < kTile; ++i) total *= advance(o, i);
+            };
+            over_tiles<Operands, kDepth<Off, kParts>>(0, way.tiles, fetch, walk);
+            const float f = kDelayed ? before : 1.f;
+            parts.end[descending][part][0][lane] = make_float4(f * M[0], f * M[1], f * M[2], f * M[3]);
+            parts.decay[descending][part][0][lane] = make_float4(total, total, total, total);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < kStrip; ++c) M[c] = 0.f;
+        before = 1.f;
+        enter_part(parts, 0, descending, part, lane, M);
+    }
+
     auto half = [&](int first, int last, bool second) __attribute__((always_inline)) {
         auto fetch = [&](Operands &o, int n) __attribute__((always_inline)) {
             n = min(n, last - 1);  // (past the end: loaded, never used; a branch would make every wait a full one)
-            const size_t low = size_t(way.low(n));
-            const T *u = u_rows + low * step * DK, *r = r_rows + low * step * DK, *g = g_rows + low * step * DK;
-            const T *b = b_rows + low * step * DV;
-            // (a token past the sequence repeats the last one's offset, so every address is valid)
-            const Off last_token = Off(way.last_offset(n)) * Off(step);
-            const Off end_k = at_byte<T>(last_token * DK + unsigned(ch)), end_v = at_byte<T>(last_token * DV + unsigned(col0));
-#pragma unroll
-            for (int i = 0; i < kTile; ++i) {
-                const Off tk = min(off_k[i], end_k), tv = min(off_v[i], end_v);
-                o.u[i] = io<T>::load(at(u, tk));
-                o.r[i] = io<T>::load(at(r, tk));
-                o.g[i] = io<T>::load(at(g, tk));
-                load_strip(at(b, tv), o.b[i]);
-            }
+            fetch_rows(o, n, std::true_type{});
             if (second) {
                 const size_t t = size_t(min(way.token(n, held_i), L - 1));
 #pragma unroll
@@ -240,29 +342,13 @@ __device__ __forceinline__ void column_sweep(const T *u_rows, const T *r_rows, c
             }
         };
         auto walk = [&](Operands &o, int n) __attribute__((always_inline)) {
-            // tokens past the sequence: nothing enters the matrix (ascending they come last, descending
-            // first, when it is still zero)
-            if (way.ragged(n)) {
-#pragma unroll
-                for (int i = 0; i < kTile; ++i) {
-                    if (way.token(n, i) < L) continue;
-                    o.u[i] = 0.f;
-                    o.g[i] = 0.f;
-#pragma unroll
-                    for (int c = 0; c < kStrip; ++c) o.b[i][c] = 0.f;
-                }
-            }
+            clear_past_end(o, n);
             float x[kVals];
 #pragma unroll
             for (int i = 0; i < kTile; ++i) {
-                const float alpha = gate_factor(o.g[i]);
-                const float decay = kDelayed ? before : alpha;
+                advance(o, i);
 #pragma unroll
-                for (int c = 0; c < kStrip; ++c) {
-                    M[c] = fmaf(decay, M[c], o.u[i] * (kDelayed ? b_scale * o.b[i][c] : o.b[i][c]));
-                    x[kStrip * i + c] = o.r[i] * M[c];
-                }
-                before = alpha;
+                for (int c = 0; c < kStrip; ++c) x[kStrip * i + c] = o.r[i] * M[c];
             }
             sum_over_lanes<DK>(x, lane);
             const int t = way.token(n, held_i);
@@ -276,22 +362,7 @@ __device__ __forceinline__ void column_sweep(const T *u_rows, const T *r_rows, c
                 }
             }
         };
-        if (first >= last) return;
-        constexpr int kAhead = kDepth<Off>;
-        Operands o[kAhead];
-#pragma unroll
-        for (int d = 0; d < kAhead; ++d) fetch(o[d], first + d);
-        int n = first;
-        for (; n + kAhead <= last; n += kAhead) {
-#pragma unroll
-            for (int d = 0; d < kAhead; ++d) {
-                walk(o[d], n + d);
-                fetch(o[d], n + d + kAhead);
-            }
-        }
-#pragma unroll
-        for (int d = 0; d < kAhead - 1; ++d)
-            if (n + d < last) walk(o[d], n + d);
+        over_tiles<Operands, kDepth<Off, kParts>>(first, last, fetch, walk);
     };
     half(0, way.first_half(), false);
     __threadfence_block();
@@ -319,24 +390,24 @@ __device__ __forceinline__ float wave_scan(float x, int lane)
 //   e^f = q * dq^f - k * dk^f ,  e^b = q * dq^b - k * dk^b
 // take the place of the parked partial results (part_f, part_b: dense fp32 [L][DK]); their running sums over
 // the tokens, descending and ascending, are dg_fwd and dg_bwd.
-// Two barriers, executed by every wave that calls this.  `stage` is the wave's own LDS.
+// Two barriers, and one more with several parts, executed by every wave that calls this.  `stage` is the wave's own LDS.
 template <int DV>
 struct RowStage {
     // per token of the tile: both gates' factors, k and q of the wave's rows
     float x[kTile][4][kStrip * (64 / DV)];
 };
 
-template <typename T, int DK, int DV, typename Off = unsigned>
+template <typename T, int DK, int DV, typename Off = unsigned, int kParts = 1>
 __device__ __forceinline__ void row_sweep(const T *q_rows, const T *k_rows, const T *v_rows, const T *gf_rows,
                                           const T *gb_rows, const T *do_rows, T *dq_rows, T *dk_rows, T *dgf_rows,
                                           T *dgb_rows, float *part_f, float *part_b, RowStage<DV> &stage, size_t step,
-                                          int L, bool descending, int row_block, int lane)
+                                          int L, bool descending, int part, PartStage<kParts> &parts, int row_block, int lane)
 {
     constexpr int kGroups = 64 / DV;
     constexpr int kRows = kStrip * kGroups;   // rows of the wave
     constexpr int kLoads = 2 * kGroups;       // staged values a lane loads per tile
     constexpr int kH = kHeld<DV>;
-    const Way way = make_way(L, descending);
+    const Way way = make_way<kParts>(L, descending, part);
     const int col = lane % DV, grp = lane / DV, first_row = row_block * kRows;
     const int held = lane_value<DV>(lane);
     const int held_i = held / kStrip, held_c = kStrip * grp + held % kStrip;  // token and row (of the wave's) of the totals held
@@ -367,28 +438,117 @@ __device__ __forceinline__ void row_sweep(const T *q_rows, const T *k_rows, cons
 #pragma unroll
     for (int i = 0; i < kTile; ++i)
         off_v[i] = at_byte<T>(Off(descending ? kTile - 1 - i : i) * Off(step) * DV + unsigned(col));
-    float S[kStrip] = {0.f, 0.f, 0.f, 0.f}, A[kStrip] = {0.f, 0.f, 0.f, 0.f}, before[kStrip] = {0.f, 0.f, 0.f, 0.f};
+    // (`before`: gates of the token visited before; what enters a part has them applied already)
+    float S[kStrip] = {0.f, 0.f, 0.f, 0.f}, A[kStrip] = {0.f, 0.f, 0.f, 0.f}, before[kStrip] = {1.f, 1.f, 1.f, 1.f};
+
+    auto fetch_rows = [&](Operands &o, int n) __attribute__((always_inline)) {
+        const size_t low = size_t(way.low(n));
+        const T *v = v_rows + low * step * DV, *d = do_rows + low * step * DV;
+        const Off end_v = at_byte<T>(Off(way.last_offset(n)) * Off(step) * DV + unsigned(col));
+#pragma unroll
+        for (int i = 0; i < kTile; ++i) {
+            const Off t = min(off_v[i], end_v);
+            o.v[i] = io<T>::load(at(v, t));
+            o.d[i] = io<T>::load(at(d, t));
+        }
+#pragma unroll
+        for (int j = 0; j < kLoads; ++j) {
+            int array, i, row;
+            staged(j, array, i, row);
+            o.s[j] = io<T>::load(staged_rows[j] + (low + way.offset(n, i)) * step * DK);
+        }
+    };
+    // the staged values of tile n, gates as factors, into the wave's stage (and in o.s); tokens past the sequence: nothing
+    // enters the matrices
+    auto put_stage = [&](Operands &o, int n) __attribute__((always_inline)) {
+        const bool ragged = way.ragged(n);
+#pragma unroll
+        for (int j = 0; j < kLoads; ++j) {
+            int array, i, row;
+            staged(j, array, i, row);
+            float x = array < 2 ? gate_factor(o.s[j]) : o.s[j];
+            if (ragged && way.token(n, i) >= L) x = array < 2 ? 1.f : 0.f;
+            stage.x[i][array][row] = o.s[j] = x;
+        }
+        if (ragged) {
+#pragma unroll
+            for (int i = 0; i < kTile; ++i)
+                if (way.token(n, i) >= L) o.v[i] = o.d[i] = 0.f;
+        }
+        lds_order();
+    };
+    // both matrices through token i of the tile in the stage; d: d_out / 2
+    auto advance = [&](float v, float d, int i) __attribute__((always_inline)) {
+        float gs[kStrip], ga[kStrip], kr[kStrip], qr[kStrip];
+        load_strip(&stage.x[i][0][kStrip * grp], gs);
+        load_strip(&stage.x[i][1][kStrip * grp], ga);
+        load_strip(&stage.x[i][2][kStrip * grp], kr);
+        load_strip(&stage.x[i][3][kStrip * grp], qr);
+#pragma unroll
+        for (int c = 0; c < kStrip; ++c) {
+            S[c] = fmaf(gs[c], S[c], kr[c] * v);
+            A[c] = fmaf(before[c], A[c], qr[c] * d);
+            before[c] = ga[c];
+        }
+    };
+    if constexpr (kParts > 1) {
+        if (part != (descending ? 0 : kParts - 1)) {  // (nobody enters anything after the last part)
+            // the decay over the part: a lane multiplies the factors it stages (the first half of its values), then every
+            // lane those of its rows
+            float total[kLoads / 2];
+#pragma unroll
+            for (int j = 0; j < kLoads / 2; ++j) total[j] = 1.f;
+            auto fetch = [&](Operands &o, int n) __attribute__((always_inline)) { fetch_rows(o, min(n, way.tiles - 1)); };
+            auto walk = [&](Operands &o, int n) __attribute__((always_inline)) {
+                put_stage(o, n);
+#pragma unroll
+                for (int j = 0; j < kLoads / 2; ++j) total[j] *= o.s[j];
+#pragma unroll
+                for (int i = 0; i < kTile; ++i) advance(o.v[i], 0.5f * o.d[i], i);
+                lds_order();
+            };
+            // (one value a lane in a stage of 64-wide columns: the upper half of the wave stages the second gate)
+            static_assert(kLoads / 2 * 64 == 2 * kTile * kRows, "the first half of the staged values are the gates");
+            over_tiles<Operands, kDepth<Off, kParts>>(0, way.tiles, fetch, walk);
+#pragma unroll
+            for (int j = 0; j < kLoads / 2; ++j) {
+                int array, i, row;
+                staged(j, array, i, row);
+                stage.x[i][array][row] = total[j];
+            }
+            lds_order();
+            float decay[2][kStrip];
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                load_strip(&stage.x[0][m][kStrip * grp], decay[m]);
+#pragma unroll
+                for (int i = 1; i < kTile; ++i) {
+                    float f[kStrip];
+                    load_strip(&stage.x[i][m][kStrip * grp], f);
+#pragma unroll
+                    for (int c = 0; c < kStrip; ++c) decay[m][c] *= f[c];
+                }
+                parts.decay[descending][part][m][lane] = make_float4(decay[m][0], decay[m][1], decay[m][2], decay[m][3]);
+            }
+            parts.end[descending][part][0][lane] = make_float4(S[0], S[1], S[2], S[3]);
+            parts.end[descending][part][1][lane] = make_float4(before[0] * A[0], before[1] * A[1], before[2] * A[2], before[3] * A[3]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < kStrip; ++c) {
+            S[c] = A[c] = 0.f;
+            before[c] = 1.f;
+        }
+        enter_part(parts, 0, descending, part, lane, S);
+        enter_part(parts, 1, descending, part, lane, A);
+    }
 
     auto half = [&](int first, int last, bool second) __attribute__((always_inline)) {
         auto fetch = [&](Operands &o, int n) __attribute__((always_inline)) {
             n = min(n, last - 1);  // (past the end: loaded, never used; a branch would make every wait a full one)
-            const size_t low = size_t(way.low(n));
-            const T *v = v_rows + low * step * DV, *d = do_rows + low * step * DV;
-            const Off end_v = at_byte<T>(Off(way.last_offset(n)) * Off(step) * DV + unsigned(col));
-#pragma unroll
-            for (int i = 0; i < kTile; ++i) {
-                const Off t = min(off_v[i], end_v);
-                o.v[i] = io<T>::load(at(v, t));
-                o.d[i] = io<T>::load(at(d, t));
-            }
-#pragma unroll
-            for (int j = 0; j < kLoads; ++j) {
-                int array, i, row;
-                staged(j, array, i, row);
-                o.s[j] = io<T>::load(staged_rows[j] + (low + way.offset(n, i)) * step * DK);
-            }
+            fetch_rows(o, n);
             if (second) {
-                const size_t t = low + way.offset(n, held_i);
+                const size_t t = size_t(way.low(n)) + way.offset(n, held_i);
 #pragma unroll
                 for (int h = 0; h < kH; ++h) {
                     o.other_f[h] = part_f[t * DK + first_row + held_c + h];
@@ -397,36 +557,14 @@ __device__ __forceinline__ void row_sweep(const T *q_rows, const T *k_rows, cons
             }
         };
         auto walk = [&](Operands &o, int n) __attribute__((always_inline)) {
-            const bool ragged = way.ragged(n);
-#pragma unroll
-            for (int j = 0; j < kLoads; ++j) {
-                int array, i, row;
-                staged(j, array, i, row);
-                float x = array < 2 ? gate_factor(o.s[j]) : o.s[j];
-                // tokens past the sequence: nothing enters the matrices
-                if (ragged && way.token(n, i) >= L) x = array < 2 ? 1.f : 0.f;
-                stage.x[i][array][row] = x;
-            }
-            if (ragged) {
-#pragma unroll
-                for (int i = 0; i < kTile; ++i)
-                    if (way.token(n, i) >= L) o.v[i] = o.d[i] = 0.f;
-            }
-            lds_order();
+            put_stage(o, n);
             float xq[kVals], xk[kVals];
 #pragma unroll
             for (int i = 0; i < kTile; ++i) {
                 const float d = 0.5f * o.d[i], v = o.v[i];
-                float gs[kStrip], ga[kStrip], kr[kStrip], qr[kStrip];
-                load_strip(&stage.x[i][0][kStrip * grp], gs);
-                load_strip(&stage.x[i][1][kStrip * grp], ga);
-                load_strip(&stage.x[i][2][kStrip * grp], kr);
-                load_strip(&stage.x[i][3][kStrip * grp], qr);
+                advance(v, d, i);
 #pragma unroll
                 for (int c = 0; c < kStrip; ++c) {
-                    S[c] = fmaf(gs[c], S[c], kr[c] * v);
-                    A[c] = fmaf(before[c], A[c], qr[c] * d);
-                    before[c] = ga[c];
                     xq[kStrip * i + c] = S[c] * d;
                     xk[kStrip * i + c] = A[c] * v;
                 }
@@ -458,22 +596,7 @@ __device__ __forceinline__ void row_sweep(const T *q_rows, const T *k_rows, cons
             }
             lds_order();  // the totals' reads of the stage before the next tile's writes
         };
-        if (first >= last) return;
-        constexpr int kAhead = kDepth<Off>;
-        Operands o[kAhead];
-#pragma unroll
-        for (int d = 0; d < kAhead; ++d) fetch(o[d], first + d);
-        int n = first;
-        for (; n + kAhead <= last; n += kAhead) {
-#pragma unroll
-            for (int d = 0; d < kAhead; ++d) {
-                walk(o[d], n + d);
-                fetch(o[d], n + d + kAhead);
-            }
-        }
-#pragma unroll
-        for (int d = 0; d < kAhead - 1; ++d)
-            if (n + d < last) walk(o[d], n + d);
+        over_tiles<Operands, kDepth<Off, kParts>>(first, last, fetch, walk);
     };
     half(0, way.first_half(), false);
     __threadfence_block();
@@ -483,17 +606,29 @@ __device__ __forceinline__ void row_sweep(const T *q_rows, const T *k_rows, cons
     __syncthreads();
 
     // running sums, a lane per token: dg_fwd from the last token on (descending wave), dg_bwd from the first
-    const float *part = descending ? part_f : part_b;
+    const float *part_sums = descending ? part_f : part_b;
     T *dg = descending ? dgf_rows : dgb_rows;
-    for (int r0 = 0; r0 < kRows; r0 += kStrip) {
-        float run[kStrip] = {0.f, 0.f, 0.f, 0.f};
+    // (several parts: a wave takes its share of each strip's rows)
+    constexpr int kMine = kStrip / kParts;
+    static_assert(kStrip % kParts == 0, "rows of a strip shared out to the parts");
+    for (int r0 = part * kMine; r0 < kRows; r0 += kStrip) {
+        float run[kMine];
+#pragma unroll
+        for (int c = 0; c < kMine; ++c) run[c] = 0.f;
         for (int n = 0; n < L; n += 64) {
             const int t = descending ? L - 1 - n - lane : n + lane;
             const bool live = n + lane < L;
             float e[kStrip] = {0.f, 0.f, 0.f, 0.f};
-            if (live) load_strip(part + size_t(t) * DK + first_row + r0, e);
+            if (live) {
+                const float *p = part_sums + size_t(t) * DK + first_row + r0;
+                if constexpr (kMine == kStrip)
+                    load_strip(p, e);
+                else
 #pragma unroll
-            for (int c = 0; c < kStrip; ++c) {
+                    for (int c = 0; c < kMine; ++c) e[c] = p[c];
+            }
+#pragma unroll
+            for (int c = 0; c < kMine; ++c) {
                 e[c] = run[c] + wave_scan(e[c], lane);
                 run[c] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(e[c]), 63));
                 if (live) io<T>::store(dg + size_t(t) * step * DK + first_row + r0 + c, e[c]);

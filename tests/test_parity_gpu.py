@@ -1254,12 +1254,25 @@ def test_exact_kernels_tile_edges(L, dk, dv, layout):
     of L + 64 additions; with u = 2^-24 that is (5 L + 64) u of the sum of the terms' magnitudes, which is what the
     oracle gives for |q|, |k|, |v|, |d_out|.  The gate gradients are running sums of q dq - k dk over the sequence: the same
     of |q| |dq| + |k| |dk|, summed, and once more L additions."""
+    B, H = (2, 3) if L > 16 else (3, 43)  # the many short slabs: two pairs of waves, or one slab, per workgroup
+    _check_exact(B, H, L, dk, dv, layout)
+
+
+@pytest.mark.parametrize("B,H,L,dk,dv,layout", ((2, 2, 39, 64, 64, "bhld"), (2, 2, 40, 64, 64, "blhd"), (1, 3, 41, 32, 32, "bhld"),
+                                                (2, 4, 57, 16, 16, "blhd"), (3, 4, 9, 64, 64, "bhld"), (3, 4, 16, 64, 64, "blhd"),
+                                                (4, 4, 50, 64, 64, "bhld"), (4, 17, 50, 32, 16, "blhd")))
+def test_exact_kernels_parts(B, H, L, dk, dv, layout):
+    """Strips cut into four and into two parts of tokens, and the line between (256 and 512 strips, 40 and 9 tokens): parts of
+    unequal length, of a tile, and without one."""
+    _check_exact(B, H, L, dk, dv, layout)
+
+
+def _check_exact(B, H, L, dk, dv, layout):
     import oracle
     import torch
     from paper_2405_18425_amd import binding as vb
 
-    B, H = (2, 3) if L > 16 else (3, 43)  # the many short slabs: two pairs of waves, or one slab, per workgroup
-    _say(f"exact kernels L{L} dk{dk} dv{dv} {layout}")
+    _say(f"exact kernels {B}x{H} L{L} dk{dk} dv{dv} {layout}")
     w = wl.Workload("exact", B=B, H=H, Hg=1, Wg=L, dk=dk, dv=dv, dtype="f32", gate_mu=-1.0)
     s = wl.generate(w, seed=L + dk + 3 * dv, tensors=("q", "k", "v", "g_fwd", "g_bwd"))
     s["d_out"] = np.random.default_rng(L).standard_normal(s["v"].shape).astype(np.float32)
