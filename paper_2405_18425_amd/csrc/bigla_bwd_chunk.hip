@@ -29,19 +29,16 @@
 //      chunks of a slab): S_in(c+1) = d_c S_in(c) + U_c and A'_c = d_c (W_{c+1} + A'_{c+1}), in
 //      place, fp32 running values, bf16 storage.
 // Either leaves marks of the slabs in which some chunk's total log-decay exceeds 60 nats in some channel.  Then
-//   bigla_bwd_chunk_main_kernel (workgroup per chunk): everything above for both directions,
-//      dq, dk, dv accumulated in registers and written once.
+//   bigla_bwd_chunk_main_kernel (workgroup per chunk): everything above for both directions at once (bigla_bwd_main.hpp).
 // exp(-b) grows with the decay accumulated over a chunk, so marked slabs are evaluated token by token (exact_sweep.hpp) by
 // the workgroups of the main launch; gates of the paper's form,
 // sigmoid(z)^(1/16), reach 60 nats in 64 steps only for z < -15 throughout.
 //
-// Wavefront mapping (256 threads = 4 waves): wave w owns tokens 16w..16w+15 of the chunk; results
-// are produced transposed, so that lane (r = lane%16, g = lane/16) holds, for token 16w + r,
-// channels 16ct + 4g + e (ct, e = 0..3) -- four 8-byte pieces of the token's row.  All tiles are
-// row-major bf16 in LDS; an operand whose contraction index runs along the tile's rows is read
-// with ds_read_b64_tr_b16.  Tokens past the sequence are read as zeros (q = k = v = do = 0,
-// log-gate 0: a no-op) and their stores are dropped, both by the bounds check of the buffer
-// resource that spans the slab.
+// Wavefront mapping of the passes that make the states (256 threads = 4 waves): wave w owns tokens 16w..16w+15 of the chunk; lane
+// (r = lane%16, g = lane/16) holds, for token 16w + r, channels 16ct + 4g + e (ct, e = 0..3) -- four 8-byte pieces of the
+// token's row.  All tiles are row-major bf16 in LDS; an operand whose contraction index runs along the tile's rows is read
+// with ds_read_b64_tr_b16.  Tokens past the sequence are read as zeros (q = k = v = do = 0, log-gate 0: a no-op) and their
+// stores are dropped, both by the bounds check of the buffer resource that spans the slab.
 #include <algorithm>
 #include <type_traits>
 
@@ -64,34 +61,12 @@ constexpr size_t kMat = size_t(kD) * kD;  // elements of one state matrix
 
 typedef uint16_t Tile[kC][kPitch];
 
-template <int SUFFIX>
-__device__ __forceinline__ float row_total(float scanned)
-{
-    return SUFFIX == 0 ? dpp_or_zero<0x15f>(scanned) : dpp_or_zero<0x150>(scanned);  // row_newbcast:15 / :0
-}
-
-// MFMA operand whose 16 rows (A) or columns (B) are tile rows row0..row0+15 and whose contraction
-// index runs along the tile's columns: k-slot j of K-step kk is column 32kk + 8g + j.
-__device__ __forceinline__ bf16x8 row_frag(const Tile &tile, int row0, int kk, int r, int g)
-{
-    return *reinterpret_cast<const bf16x8 *>(&tile[row0 + r][32 * kk + 8 * g]);
-}
-
 // MFMA operand whose 16 rows (A) or columns (B) are tile columns col0..col0+15 and whose contraction
 // index runs along the tile's rows: k-slot j of K-step kk is row 32kk + 8g + j.
 __device__ __forceinline__ bf16x8 col_frag(const Tile &tile, int col0, int kk, int r, int g)
 {
     const int row = 32 * kk + 8 * g + (r >> 2), col = col0 + 4 * (r & 3);
     return join(lds_read_tr(&tile[row][col]), lds_read_tr(&tile[row + 4][col]));
-}
-
-// MFMA A operand whose 16 rows are tile columns col0..col0+15, contracted over the tile's rows
-// (tokens) in accumulator order: k-slots 0..3 of K-step kk are rows 32kk + 4g + e, slots 4..7 rows
-// 32kk + 16 + 4g + e, which is where a lane's accumulators of two stacked 16x16 tiles sit.
-__device__ __forceinline__ bf16x8 token_frag(const Tile &tile, int col0, int kk, int r, int g)
-{
-    const int row = 32 * kk + 4 * g + (r >> 2), col = col0 + 4 * (r & 3);
-    return join(lds_read_tr(&tile[row][col]), lds_read_tr(&tile[row + 16][col]));
 }
 
 // B operand of a contraction over the chunk's tokens with a 0/1 triangle: k-slot j of K-step kk is
@@ -188,25 +163,6 @@ __device__ __forceinline__ void take_own(const Tile &tile, int w, int r, int g, 
     wave_lds_fence();
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct) x[ct] = *reinterpret_cast<const uint2 *>(&tile[16 * w + r][16 * ct + 4 * g]);
-}
-
-// The wave's 16 result rows, held as the lanes' own pieces, to global memory as whole rows: through
-// the wave's rows of a tile that nobody reads at that point, then 16 bytes per lane, 8 lanes a row.
-__device__ __forceinline__ void store_own(Tile &tile, const SlabRows &rows, unsigned t0, int w, int lane, int r, int g,
-                                          const f32x4 (&x)[4])
-{
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct) *reinterpret_cast<uint2 *>(&tile[16 * w + r][16 * ct + 4 * g]) = pack4(x[ct]);
-    wave_lds_fence();
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int row = 16 * w + 8 * h + (lane >> 3);
-        const uint4 v = *reinterpret_cast<const uint4 *>(&tile[row][8 * (lane & 7)]);
-        const unsigned off = (t0 + row) * rows.pitch + 16u * (lane & 7);
-        __builtin_amdgcn_raw_buffer_store_b128(u32x4{v.x, v.y, v.z, v.w}, rows.rsrc,
-                                               unsigned(lane & 7) < rows.pieces ? off : kBeyond, 0, 0);
-    }
-    wave_lds_fence();  // the rows may be reused by this wave right away
 }
 
 // the lane's piece of tile row 16w + r
@@ -599,254 +555,17 @@ __global__ __launch_bounds__(kWalkThreads, 4) void bigla_bwd_chunk_walk_kernel(
     }
 }
 
+}  // namespace
+
+}  // namespace vig
+
+#include "bigla_bwd_main.hpp"
+
+namespace vig {
+
+namespace {
+
 // ---- pass 3: the gradients of one chunk ------------------------------------------------------------
-
-struct MainLds {
-    Tile v;      // values                                   [token][column]
-    Tile dout;   // d_out / 2                                [token][column]
-    Tile gp;     // log-gates                                [token][channel]
-    Tile qt;     // q~                                       [token][channel]
-    Tile kt;     // k~
-    Tile st;     // S_in                                     [channel][column]
-    Tile ad;     // A'
-    float R[kD]; // rowsum(S_in * A') per channel
-    float tot[2][4][kD];  // per wave and channel: the wave's sums of the two kinds of dg summands
-};
-
-struct Grads {
-    f32x4 dq[4], dk[4], dv[4];  // token 16w + r, channels / columns 16ct + 4g + e
-};
-
-// What one direction reads beside q, k, v, do: its log-gates and its two state matrices.  Requested
-// ahead of the phase that needs them (the global latency then overlaps other work).
-struct DirInputs {
-    ChunkRows gates;
-    uint4 st[2], ad[2];
-};
-
-template <int DIR, int kCt>
-__device__ __forceinline__ DirInputs fetch_dir(const SlabRows &gates, const uint16_t *mats, unsigned t0, int tid, int w,
-                                               int lane)
-{
-    DirInputs in;
-    in.gates = fetch_rows(gates, t0, w, lane);
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        in.st[h] = in.ad[h] = make_uint4(0u, 0u, 0u, 0u);
-        if (2 * h < kCt) {  // piece tid + 256 h lies in rows 32h .. 32h + 31
-            in.st[h] = reinterpret_cast<const uint4 *>(mats + size_t(2 * DIR) * kMat)[tid + kThreads * h];
-            in.ad[h] = reinterpret_cast<const uint4 *>(mats + size_t(2 * DIR + 1) * kMat)[tid + kThreads * h];
-        }
-    }
-    return in;
-}
-
-__device__ __forceinline__ void put_matrix(Tile &tile, const uint4 (&x)[2], int tid)
-{
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int p = tid + kThreads * h;
-        *reinterpret_cast<uint4 *>(&tile[p >> 3][8 * (p & 7)]) = x[h];
-    }
-}
-
-// `in`: this direction's inputs, already requested; `next`: called once the contractions are done,
-// to request the other direction's.
-template <int DIR, int kCt, class Next>
-__device__ __forceinline__ void chunk_direction(MainLds &sm, const DirInputs &in, const SlabRows &dg_rows, unsigned t0,
-                                                int tid, int w, int lane, int r, int g, const uint2 (&qr)[4],
-                                                const uint2 (&kr)[4], Grads &acc, Next next)
-{
-    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    if (DIR == 1) __syncthreads();  // the first direction's last reads of the tiles are done
-    put_rows<false>(sm.gp, in.gates, w, lane);
-    put_matrix(sm.st, in.st, tid);
-    put_matrix(sm.ad, in.ad, tid);
-    __syncthreads();
-
-    // cumulative gates, scaled queries and keys (kept as rounded: the gate gradient below must use
-    // exactly the operands of the contractions, see there)
-    f32x4 Ep[4];
-    {
-        f32x4 b[4];
-        gate_scan<DIR, kCt>(sm.gp, w, r, g, b);
-#pragma unroll
-        for (int ct = 0; ct < kCt; ++ct) {
-            const f32x4 qv = unpack4(qr[ct]), kv = unpack4(kr[ct]);
-            f32x4 qs, ks;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float x = b[ct][e] * kLog2e;
-                Ep[ct][e] = fast_exp2(x);
-                qs[e] = qv[e] * Ep[ct][e];
-                ks[e] = kv[e] * fast_exp2(-x);
-            }
-            put_own(sm.qt, w, r, g, ct, qs);
-            put_own(sm.kt, w, r, g, ct, ks);
-        }
-    }
-    // rowsum(S_in * A'): four threads per row, 16 columns each
-    if ((tid >> 2) < 16 * kCt) {
-        const int row = tid >> 2, c0 = 16 * (tid & 3);
-        float sum = 0.f;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const uint4 a = *reinterpret_cast<const uint4 *>(&sm.st[row][c0 + 8 * h]);
-            const uint4 b = *reinterpret_cast<const uint4 *>(&sm.ad[row][c0 + 8 * h]);
-            sum += bf16_lo_to_f32(a.x) * bf16_lo_to_f32(b.x) + bf16_hi_to_f32(a.x) * bf16_hi_to_f32(b.x);
-            sum += bf16_lo_to_f32(a.y) * bf16_lo_to_f32(b.y) + bf16_hi_to_f32(a.y) * bf16_hi_to_f32(b.y);
-            sum += bf16_lo_to_f32(a.z) * bf16_lo_to_f32(b.z) + bf16_hi_to_f32(a.z) * bf16_hi_to_f32(b.z);
-            sum += bf16_lo_to_f32(a.w) * bf16_lo_to_f32(b.w) + bf16_hi_to_f32(a.w) * bf16_hi_to_f32(b.w);
-        }
-        sum += __shfl_xor(sum, 1);
-        sum += __shfl_xor(sum, 2);
-        if ((tid & 3) == 0) sm.R[row] = sum;
-    }
-    __syncthreads();  // q~, k~ complete; every wave is done with the gates
-
-    // The wave's strips of the masked score matrices, straight from the accumulators into the B
-    // operands of the contractions over tokens (no trip through LDS): the row strip of dP for X
-    // (keys 16m + 4g + e, query 16w + r) and the column strips of dP and P for Yi and dv (queries
-    // 16m + 4g + e, key 16w + r).  A lane's accumulators of tiles m = 2kk, 2kk + 1 are exactly its
-    // k-slots of K-step kk when slots 0..3 are tokens 32kk + 4g + e and slots 4..7 tokens
-    // 32kk + 16 + 4g + e; the A operands (token_frag) use the same order.
-    const bf16x8 own_k[2] = {row_frag(sm.kt, 16 * w, 0, r, g), row_frag(sm.kt, 16 * w, 1, r, g)};
-    const bf16x8 own_d[2] = {row_frag(sm.dout, 16 * w, 0, r, g), row_frag(sm.dout, 16 * w, 1, r, g)};
-    const bf16x8 own_v[2] = {row_frag(sm.v, 16 * w, 0, r, g), row_frag(sm.v, 16 * w, 1, r, g)};
-    // Each strip is split into two bf16 halves (value = hi + lo to 16 bits): the scores then enter
-    // the second contraction unrounded, for one more MFMA per product and no further LDS traffic.
-    bf16x8 bX[2], bY[2], bP[2], bXl[2], bYl[2], bPl[2];
-#pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-        uint2 x[2], y[2], p[2], xl[2], yl[2], pl[2];
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            const int m = 2 * kk + half;
-            f32x4 dr = zero, dc = zero, pc = zero;
-#pragma unroll
-            for (int k2 = 0; k2 < 2; ++k2) {
-                dr = mfma(row_frag(sm.v, 16 * m, k2, r, g), own_d[k2], dr);     // dP[t own][s]
-                dc = mfma(row_frag(sm.dout, 16 * m, k2, r, g), own_v[k2], dc);  // dP[t][s own]
-                if (2 * k2 < kCt) pc = mfma(row_frag(sm.qt, 16 * m, k2, r, g), own_k[k2], pc);  // P[t][s own]
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int far = 16 * m + 4 * g + e, own = 16 * w + r;
-                // row strip: far is the key, own the query; column strips: the other way round
-                const bool keep_row = DIR == 0 ? far <= own : far >= own;
-                const bool keep_col = DIR == 0 ? own <= far : own >= far;
-                dr[e] = keep_row ? dr[e] : 0.f;
-                dc[e] = keep_col ? dc[e] : 0.f;
-                pc[e] = keep_col ? pc[e] : 0.f;
-            }
-            x[half] = pack4(dr);
-            y[half] = pack4(dc);
-            p[half] = pack4(pc);
-            const f32x4 xh = unpack4(x[half]), yh = unpack4(y[half]), ph = unpack4(p[half]);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                dr[e] -= xh[e];
-                dc[e] -= yh[e];
-                pc[e] -= ph[e];
-            }
-            xl[half] = pack4(dr);
-            yl[half] = pack4(dc);
-            pl[half] = pack4(pc);
-        }
-        bX[kk] = __builtin_bit_cast(bf16x8, make_uint4(x[0].x, x[0].y, x[1].x, x[1].y));
-        bY[kk] = __builtin_bit_cast(bf16x8, make_uint4(y[0].x, y[0].y, y[1].x, y[1].y));
-        bP[kk] = __builtin_bit_cast(bf16x8, make_uint4(p[0].x, p[0].y, p[1].x, p[1].y));
-        bXl[kk] = __builtin_bit_cast(bf16x8, make_uint4(xl[0].x, xl[0].y, xl[1].x, xl[1].y));
-        bYl[kk] = __builtin_bit_cast(bf16x8, make_uint4(yl[0].x, yl[0].y, yl[1].x, yl[1].y));
-        bPl[kk] = __builtin_bit_cast(bf16x8, make_uint4(pl[0].x, pl[0].y, pl[1].x, pl[1].y));
-    }
-
-    f32x4 E1[4], E2[4];
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct) {
-        f32x4 X = zero, Yi = zero, Ye = zero, V = zero;
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk) {
-            if (ct < kCt) {
-                // X^T[c][t] = sum_s k~[s][c] dP[t][s] + sum_j S_in[c][j] do'[t][j]
-                const bf16x8 ak = token_frag(sm.kt, 16 * ct, kk, r, g);
-                X = mfma(ak, bXl[kk], X);
-                X = mfma(ak, bX[kk], X);
-                X = mfma(row_frag(sm.st, 16 * ct, kk, r, g), own_d[kk], X);
-                // Yi^T[c][s] = sum_t q~[t][c] dP[t][s],  Ye^T[c][s] = sum_j A'[c][j] v[s][j]
-                const bf16x8 aq = token_frag(sm.qt, 16 * ct, kk, r, g);
-                Yi = mfma(aq, bYl[kk], Yi);
-                Yi = mfma(aq, bY[kk], Yi);
-                Ye = mfma(row_frag(sm.ad, 16 * ct, kk, r, g), own_v[kk], Ye);
-            }
-            // dv^T[j][s] = sum_t do'[t][j] P[t][s] + sum_i A'[i][j] k~[s][i]   (column tile j = ct)
-            const bf16x8 ad = token_frag(sm.dout, 16 * ct, kk, r, g);
-            V = mfma(ad, bPl[kk], V);
-            V = mfma(ad, bP[kk], V);
-            if (2 * kk < kCt) V = mfma(col_frag(sm.ad, 16 * ct, kk, r, g), own_k[kk], V);
-        }
-        if (ct >= kCt) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc.dv[ct][e] += V[e];
-            continue;
-        }
-        // The summands of the gate gradient take q~ and k~ as the contractions saw them (rounded to
-        // bf16): sum_{t>=u} q~ * X - sum_{s>=u} k~ * Yi is then, term by term, the sum over the pairs
-        // s < u <= t of q~_t dP_ts k~_s, and the rounding of the operands perturbs each pair once
-        // instead of leaving the difference of two long sums that no longer cancel.
-        const f32x4 qv = unpack4(*reinterpret_cast<const uint2 *>(&sm.qt[16 * w + r][16 * ct + 4 * g]));
-        const f32x4 kv = unpack4(*reinterpret_cast<const uint2 *>(&sm.kt[16 * w + r][16 * ct + 4 * g]));
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            acc.dq[ct][e] += Ep[ct][e] * X[e];
-            acc.dk[ct][e] += __builtin_amdgcn_rcpf(Ep[ct][e]) * (Yi[e] + Ye[e]);
-            acc.dv[ct][e] += V[e];
-            E1[ct][e] = qv[e] * X[e] - kv[e] * Yi[e];
-            E2[ct][e] = kv[e] * Ye[e];
-        }
-    }
-    next();
-    // dg_u = sum_{t >= u} E1_t + sum_{t < u} E2_t + rowsum(S_in * A')   (forward; mirrored backward):
-    // scans over the wave's 16 tokens with DPP row operations, in fp32, then the other waves' totals
-    {
-        constexpr int kFar = DIR == 0 ? 1 : 0;  // E1 accumulates from the far side of the direction
-        f32x4 dg[4];
-#pragma unroll
-        for (int ct = kCt; ct < 4; ++ct) dg[ct] = zero;
-#pragma unroll
-        for (int ct = 0; ct < kCt; ++ct) {
-            f32x4 t1, t2;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float a = row_scan<kFar>(E1[ct][e]);
-                const float b = row_scan<1 - kFar>(E2[ct][e]);
-                dg[ct][e] = a + (b - E2[ct][e]);
-                t1[e] = row_total<kFar>(a);
-                t2[e] = row_total<1 - kFar>(b);
-            }
-            if (r == 0) {
-                *reinterpret_cast<f32x4 *>(&sm.tot[0][w][16 * ct + 4 * g]) = t1;
-                *reinterpret_cast<f32x4 *>(&sm.tot[1][w][16 * ct + 4 * g]) = t2;
-            }
-        }
-        __syncthreads();  // totals visible; every wave is done with S_in, whose tile carries dg out
-#pragma unroll
-        for (int ct = 0; ct < kCt; ++ct) {
-            f32x4 s = *reinterpret_cast<const f32x4 *>(&sm.R[16 * ct + 4 * g]);
-#pragma unroll
-            for (int w2 = 0; w2 < 4; ++w2) {
-                if (w2 == w) continue;
-                const bool far = DIR == 0 ? w2 > w : w2 < w;
-                const f32x4 t = *reinterpret_cast<const f32x4 *>(&sm.tot[far ? 0 : 1][w2][16 * ct + 4 * g]);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) s[e] += t[e];
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) dg[ct][e] += s[e];
-        }
-        store_own(sm.st, dg_rows, t0, w, lane, r, g, dg);
-    }
-}
 
 // Marked slabs: the workgroups of every sixteen slabs share out the strips of the exact form, two pairs of waves at a time,
 // of those that are marked among them.  Inside this launch and not in one of its own: a launch that finds no marked
@@ -903,12 +622,12 @@ __global__ __launch_bounds__(kThreads, 2) void bigla_bwd_chunk_main_kernel(
     const void *__restrict__ gf_all, const void *__restrict__ gb_all, const void *__restrict__ do_all,
     void *__restrict__ dq_all, void *__restrict__ dk_all, void *__restrict__ dv_all, void *__restrict__ dgf_all,
     void *__restrict__ dgb_all, const uint16_t *__restrict__ states, const uint16_t *__restrict__ marks, int L,
-    int heads_token_major, int n_chunks, unsigned n_slabs, unsigned extra /* workgroups per slab without a chunk */, ExactArgs exact)
+    int heads_token_major, int n_chunks, unsigned n_slabs, unsigned extra /* workgroups per slab without a chunk */,
+    ExactArgs exact)
 {
     constexpr int dk = 16 * kCt;
-    __shared__ __align__(16) MainLds sm;
-    __shared__ RowStage<kD> exact_stage[4];
     const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid) >> 6;
     const unsigned unit = blockIdx.x, units = n_slabs * unsigned(n_chunks);
     const bool has_chunk = unit < units;
     const unsigned slab = has_chunk ? unit / unsigned(n_chunks) : (unit - units) / extra;
@@ -923,42 +642,12 @@ __global__ __launch_bounds__(kThreads, 2) void bigla_bwd_chunk_main_kernel(
     if (marked != 0) marked = unsigned(__ballot(marks[first_slab + unsigned(lane) % kShareSlabs] != 0)) & ((1u << kShareSlabs) - 1u);
     const bool own_marked = (marked >> (slab - first_slab) & 1u) != 0;
     if (has_chunk && !own_marked) {
-        const unsigned t0 = chunk * kC;
-        const int w = tid >> 6, r = lane & 15, g = lane >> 4;
-
         const size_t first = slab_first_row(slab, L, heads_token_major);
-        const SlabRows q = slab_rows(q_all, first, L, heads_token_major, dk), k = slab_rows(k_all, first, L, heads_token_major, dk);
-        const SlabRows v = slab_rows(v_all, first, L, heads_token_major), dout = slab_rows(do_all, first, L, heads_token_major);
-        const SlabRows gf = slab_rows(gf_all, first, L, heads_token_major, dk), gb = slab_rows(gb_all, first, L, heads_token_major, dk);
-        const SlabRows dgf = slab_rows(dgf_all, first, L, heads_token_major, dk), dgb = slab_rows(dgb_all, first, L, heads_token_major, dk);
-
-        uint2 qr[4], kr[4];
-        const uint16_t *mats = states + size_t(unit) * 4 * kMat;
-        {
-            const ChunkRows cq = fetch_rows(q, t0, w, lane), ck = fetch_rows(k, t0, w, lane);
-            const ChunkRows cv = fetch_rows(v, t0, w, lane), cd = fetch_rows(dout, t0, w, lane);
-            put_rows<false>(sm.qt, cq, w, lane);
-            put_rows<false>(sm.kt, ck, w, lane);
-            put_rows<false>(sm.v, cv, w, lane);
-            put_rows<true>(sm.dout, cd, w, lane);
-        }
-        const DirInputs in_f = fetch_dir<0, kCt>(gf, mats, t0, tid, w, lane);
-        take_own(sm.qt, w, r, g, qr);
-        take_own(sm.kt, w, r, g, kr);
-
-        Grads acc;
-#pragma unroll
-        for (int ct = 0; ct < 4; ++ct) acc.dq[ct] = acc.dk[ct] = acc.dv[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-        DirInputs in_b;
-        chunk_direction<0, kCt>(sm, in_f, dgf, t0, tid, w, lane, r, g, qr, kr, acc,
-                                [&]() { in_b = fetch_dir<1, kCt>(gb, mats, t0, tid, w, lane); });
-        chunk_direction<1, kCt>(sm, in_b, dgb, t0, tid, w, lane, r, g, qr, kr, acc, []() {});
-
-        store_own(sm.st, slab_rows(dq_all, first, L, heads_token_major, dk), t0, w, lane, r, g, acc.dq);
-        store_own(sm.ad, slab_rows(dk_all, first, L, heads_token_major, dk), t0, w, lane, r, g, acc.dk);
-        store_own(sm.v, slab_rows(dv_all, first, L, heads_token_major), t0, w, lane, r, g, acc.dv);
+        const GradRows io = {q_all, k_all, v_all, gf_all, gb_all, do_all, dq_all, dk_all, dv_all, dgf_all, dgb_all, first, L, heads_token_major};
+        chunk_gradients<kCt>(io, states + size_t(unit) * 4 * kMat, chunk * kC, wave, lane, tid);
     }
     if (marked == 0) return;
+    __syncthreads();  // the chunk's LDS is used anew
     // gates beyond the range of this form; workgroups without a chunk to do come first
     const unsigned below = unsigned(__popc(marked & ((1u << (slab - first_slab)) - 1u))), free_units = unsigned(__popc(marked)) * unsigned(n_chunks);
     unsigned worker;
@@ -968,7 +657,7 @@ __global__ __launch_bounds__(kThreads, 2) void bigla_bwd_chunk_main_kernel(
         worker = below * unsigned(n_chunks) + chunk;
     else
         worker = free_units + sharing * extra + (slab - first_slab - below) * unsigned(n_chunks) + chunk;
-    exact_strips<dk>(exact, exact_stage, first_slab, marked, worker, sharing * exact.workers_per_slab);
+    exact_strips<dk>(exact, *reinterpret_cast<RowStage<kD>(*)[4]>(g_grad_lds), first_slab, marked, worker, sharing * exact.workers_per_slab);
 }
 
 }  // namespace
@@ -1019,9 +708,9 @@ hipError_t bigla_bwd_chunk_launch(const void *q, const void *k, const void *v, c
         auto out = [](void *p) { return static_cast<bf16_t *>(p); };
         const ExactArgs exact = {in(q), in(k), in(v), in(g_fwd), in(g_bwd), in(d_out), out(dq), out(dk), out(dv), out(dg_fwd), out(dg_bwd),
                                  exact_workspace, L, heads_token_major, unsigned(BH), unsigned(n_chunks + extra)};
-        hipLaunchKernelGGL(bigla_bwd_chunk_main_kernel<kCt>, dim3((unsigned)(units + BH * extra)), dim3(kThreads), 0, stream, q, k, v,
-                           g_fwd, g_bwd, d_out, dq, dk, dv, dg_fwd, dg_bwd, ws.states, ws.marks, L, heads_token_major, n_chunks, unsigned(BH),
-                           unsigned(extra), exact);
+        hipLaunchKernelGGL(bigla_bwd_chunk_main_kernel<kCt>, dim3((unsigned)(units + BH * extra)), dim3(kThreads), GradLds<kCt>::bytes,
+                           stream, q, k, v, g_fwd, g_bwd, d_out, dq, dk, dv, dg_fwd, dg_bwd, ws.states, ws.marks, L, heads_token_major, n_chunks,
+                           unsigned(BH), unsigned(extra), exact);
         return hipGetLastError();
     };
     return dk_ == kD ? launch(std::integral_constant<int, 4>{}) : launch(std::integral_constant<int, 2>{});

@@ -61,7 +61,7 @@ __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c)
 template <int CTRL>
 __device__ __forceinline__ float dpp_or_zero(float x)
 {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, false));
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
 }
 
 // Inclusive scan over the 16 lanes of a DPP row: prefix sums (SUFFIX 0) or suffix sums (SUFFIX 1).

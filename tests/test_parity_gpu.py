@@ -976,6 +976,16 @@ def test_bigla_bwd_chunkwise_lengths(L):
     _say(f"  worst error / bound = {worst:.3f}")
 
 
+@pytest.mark.parametrize("layout,dk", (("bhld", 64), ("blhd", 64), ("bhld", 32), ("blhd", 32)))
+@pytest.mark.parametrize("L", (33, 47, 48, 49, 80, 81, 112, 113, 177))
+def test_bigla_bwd_chunkwise_tiles(L, layout, dk):
+    """Lengths around the edges of the 16-token tiles within a chunk: either side of a wave's own tokens, its own pair of
+    tiles, and tiles partly or wholly past the end."""
+    w = wl.Workload("bwdtile", B=2, H=2, Hg=1, Wg=L, dk=dk, dv=64, dtype="bf16", gate_mu=(-2.0, 0.0, 1.0)[L % 3])
+    _say(f"bigla_bwd chunkwise tiles L={L} dk={dk} {layout}")
+    _check_bwd(_bwd_inputs(w, seed=5 * L + dk), "bf16", layout, "auto")
+
+
 @pytest.mark.parametrize("layout,dk", (("bhld", 64), ("blhd", 64), ("blhd", 32)))
 def test_bigla_bwd_slabs_beyond_the_chunkwise_range(layout, dk):
     """Some slabs decay by more than the chunkwise kernels carry (a chunk total beyond 60 nats):
