@@ -120,13 +120,14 @@ struct ChunkRows {
     u32x4 p[2];
 };
 
-__device__ __forceinline__ ChunkRows fetch_rows(const SlabRows &rows, unsigned t0, int w, int lane)
+// wanted: false reads zeros, without going to memory
+__device__ __forceinline__ ChunkRows fetch_rows(const SlabRows &rows, unsigned t0, int w, int lane, bool wanted = true)
 {
     ChunkRows c;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         const unsigned off = (t0 + 16 * w + 8 * h + (lane >> 3)) * rows.pitch + 16u * (lane & 7);
-        c.p[h] = __builtin_amdgcn_raw_buffer_load_b128(rows.rsrc, unsigned(lane & 7) < rows.pieces ? off : kBeyond, 0, 0);
+        c.p[h] = __builtin_amdgcn_raw_buffer_load_b128(rows.rsrc, wanted && unsigned(lane & 7) < rows.pieces ? off : kBeyond, 0, 0);
     }
     return c;
 }
@@ -194,6 +195,7 @@ __device__ __forceinline__ void gate_scan(const Tile &gates, int w, int r, int g
 //     1: forward  A' of the chunk (decayed adjoint from the right)     (pass 1: W)
 //     2: backward state entering the chunk from the right
 //     3: backward A' of the chunk (decayed adjoint from the left)
+//     (0 and 3 of a slab's first chunk and 1 and 2 of its last are zero; the main pass does not read them, the walks do not write them)
 //   log-decays, per (slab, chunk, direction): the chunk's total log-gate per channel, fp32
 //   slab marks: two bytes per slab (walks: one of each direction), not both zero when the slab takes the exact form; with
 //     zeros up to a multiple of kShareSlabs slabs
@@ -399,7 +401,9 @@ __global__ __launch_bounds__(kScanThreads) void bigla_bwd_chunk_scan_kernel(uint
 
 // ---- passes 1 and 2 in one: a workgroup walks a slab for one of its four matrices --------------------
 // The running matrix stays in registers (fp32) and what enters each chunk is written once; a tensor is read by the two
-// walks that need it, mostly from cache the second time.  A chunk is a chain of a gate scan, exponentials and
+// walks that need it, which are at opposite ends of the slab: with the matrices 385 MB at 48 slabs of 4096 tokens, 70 us at the rate of a
+// copy, which is what bounds the walks there (preparing two chunks at a time with eight waves: 156 us a call against 156).  Leaving out
+// the rows of the last chunk and the zero matrices of the first: 75.4 -> 72.4 us a call at 384 slabs of 196 tokens, 158 -> 152 at 192 of 1024.  A chunk is a chain of a gate scan, exponentials and
 // scalings and then the products; four waves do the first half of chunk n + 1 while four do the second half of chunk n, one
 // barrier per chunk, on tiles that alternate.  Rows are requested two chunks before their turn.
 constexpr int kWalkThreads = 2 * kThreads;
@@ -447,7 +451,9 @@ __global__ __launch_bounds__(kWalkThreads, 4) void bigla_bwd_chunk_walk_kernel(
         const SlabRows xs = slab_rows(adjoint ? q_all : k_all, first, L, heads_token_major, dk);
         const SlabRows ys = slab_rows(adjoint ? do_all : v_all, first, L, heads_token_major);
         const SlabRows gs = slab_rows(dir == 0 ? gf_all : gb_all, first, L, heads_token_major, dk);
-        auto fetch = [&](const SlabRows &rows, int n) { return fetch_rows(rows, unsigned(chunk_of(n)) * kC, w, lane); };
+        // (what the last chunk would add to the matrix enters no chunk: its rows are not read, only its gates)
+        auto fetch_gates = [&](int n) { return fetch_rows(gs, unsigned(chunk_of(n)) * kC, w, lane); };
+        auto fetch = [&](const SlabRows &rows, int n) { return fetch_rows(rows, unsigned(chunk_of(n)) * kC, w, lane, n < n_chunks - 1); };
         bf16x8 tri[2];
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) tri[kk] = dir == 0 ? tri_frag<kLe>(kk, g, 16 * w + r) : tri_frag<kGe>(kk, g, 16 * w + r);
@@ -472,13 +478,13 @@ __global__ __launch_bounds__(kWalkThreads, 4) void bigla_bwd_chunk_walk_kernel(
             }
         };
         ChunkRows cg[2], cx[2], cy[2];
-        cg[0] = fetch(gs, 0);
+        cg[0] = fetch_gates(0);
         put_rows<false>(sm.gates[0], cg[0], w, lane);
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             cx[j] = fetch(xs, j);
             cy[j] = fetch(ys, j);
-            cg[j ^ 1] = fetch(gs, j + 1);
+            cg[j ^ 1] = fetch_gates(j + 1);
         }
         // chunk n + 1 into the tiles of parity j ^ 1, the gates of chunk n + 2 into those of parity j, and the next requests
         auto advance = [&](int j, int n) __attribute__((always_inline)) {
@@ -487,7 +493,7 @@ __global__ __launch_bounds__(kWalkThreads, 4) void bigla_bwd_chunk_walk_kernel(
             put_rows<false>(sm.gates[j], cg[j], w, lane);
             cx[j ^ 1] = fetch(xs, n + 3);
             cy[j ^ 1] = fetch(ys, n + 3);
-            cg[j] = fetch(gs, n + 4);
+            cg[j] = fetch_gates(n + 4);
             scale_rows(j ^ 1);
         };
         __syncthreads();
@@ -529,7 +535,7 @@ __global__ __launch_bounds__(kWalkThreads, 4) void bigla_bwd_chunk_walk_kernel(
                 t[e] = d * s[mi][e];
                 o[e] = adjoint ? t[e] : s[mi][e];
             }
-            *reinterpret_cast<uint2 *>(mat + 16 * mt) = pack4(o);
+            if (n > 0) *reinterpret_cast<uint2 *>(mat + 16 * mt) = pack4(o);  // (nothing enters the first chunk, and nobody reads it)
 #pragma unroll
             for (int kk = 0; kk < 2; ++kk) t = mfma(col_frag(sm.y[j], 16 * mt, kk, r, g), xf[kk], t);
             s[mi] = t;
@@ -644,7 +650,7 @@ __global__ __launch_bounds__(kThreads, 2) void bigla_bwd_chunk_main_kernel(
     if (has_chunk && !own_marked) {
         const size_t first = slab_first_row(slab, L, heads_token_major);
         const GradRows io = {q_all, k_all, v_all, gf_all, gb_all, do_all, dq_all, dk_all, dv_all, dgf_all, dgb_all, first, L, heads_token_major};
-        chunk_gradients<kCt>(io, states + size_t(unit) * 4 * kMat, chunk * kC, wave, lane, tid);
+        chunk_gradients<kCt>(io, states + size_t(unit) * 4 * kMat, chunk * kC, chunk == 0, chunk + 1 == unsigned(n_chunks), wave, lane, tid);
     }
     if (marked == 0) return;
     __syncthreads();  // the chunk's LDS is used anew

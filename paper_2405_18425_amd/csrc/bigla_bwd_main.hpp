@@ -108,9 +108,11 @@ struct GradRows {  // the tensors of the whole call; a slab's rows are put behin
     int L, heads_token_major;
 };
 
-// mats: the chunk's four state matrices.  Every wave of the workgroup calls this (barriers).
+// mats: the chunk's four state matrices; nothing enters the first chunk from the left and the last one from the right, and those
+// matrices are not read.  Every wave of the workgroup calls this (barriers).
 template <int kCt>
-__device__ __forceinline__ void chunk_gradients(const GradRows &io, const uint16_t *mats, unsigned t0, int w, int lane, int tid)
+__device__ __forceinline__ void chunk_gradients(const GradRows &io, const uint16_t *mats, unsigned t0, bool first_chunk, bool last_chunk,
+                                                int w, int lane, int tid)
 {
     constexpr int kKs = kCt / 2;         // K-steps of a contraction over channels
     constexpr int kKeyBytes = 32 * kCt;  // row of keys, queries or gates
@@ -142,8 +144,10 @@ __device__ __forceinline__ void chunk_gradients(const GradRows &io, const uint16
     };
     // pieces of a state matrix that this thread carries from memory to LDS: number tid and, of 64 rows, tid + 256
     constexpr int kPieces = kCt / 2;
+    const __amdgpu_buffer_rsrc_t mats_rows = slab_resource(mats, unsigned(4 * kMat * sizeof(uint16_t)));
     auto matrix_piece = [&](int kind, int i) __attribute__((always_inline)) {
-        return reinterpret_cast<const u32x4 *>(mats + size_t(kind) * kMat)[tid + i * kThreads];
+        const bool zeros = kind == 0 || kind == 3 ? first_chunk : last_chunk;
+        return __builtin_amdgcn_raw_buffer_load_b128(mats_rows, zeros ? kBeyond : unsigned(kind * 2 * int(kMat) + (tid + i * kThreads) * 16), 0, 0);
     };
     auto put_matrix_piece = [&](unsigned region, int i, const u32x4 &x) __attribute__((always_inline)) {
         const int row = (tid >> 3) & 15;
@@ -326,7 +330,7 @@ __device__ __forceinline__ void chunk_gradients(const GradRows &io, const uint16
     };
     // The strip of `rows` against `own`, contracted on the side before the own tokens with `below`, into acc_below, which `turn` then takes,
     // and on the side after them with `above`, into acc_above.  The own pair of tiles meets both sides, the other pair one.
-    const int own_pair = w & 2, other_pair = own_pair ^ 2;
+    const int own_pair = w & 2;
     const uint2 mask_before[2] = {before(own_pair), before(own_pair + 1)}, mask_after[2] = {after(own_pair), after(own_pair + 1)};
     auto both_sides = [&](unsigned rows, const u32x4 (&own)[2], unsigned below, unsigned above, f32x4 (&acc_below)[kCt], f32x4 (&acc_above)[kCt],
                           auto turn) __attribute__((always_inline)) {
