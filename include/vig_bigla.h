@@ -105,7 +105,7 @@ int bigla_fwd_layout(const void *q, const void *k, const void *v, const void *g_
 /*
  * bigla_fwd_layout with a choice among the kernels that evaluate the chunkwise form (Section 4.2.1,
  * Eq. (BiGLA); a measurement and testing aid: the result is the same up to operand rounding).
- *   VIG_FWD_AUTO              what bigla_fwd_layout runs: up to 64 tokens, and up to 256 in at least 128
+ *   VIG_FWD_AUTO              what bigla_fwd_layout runs: up to 192 tokens, and up to 256 in at least 128
  *                             slabs, one launch that takes the whole sequence as one chunk; otherwise the
  *                             eight-wave kernels;
  *   VIG_FWD_FOUR_WAVE         workgroups of four waves, each wave walking the whole chain of a chunk

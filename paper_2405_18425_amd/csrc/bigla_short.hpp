@@ -6,7 +6,7 @@
 // chunk.  What the longer products cost in matrix instructions (all 16 x 16 tiles of the L x L score matrix) is what
 // the states of the chunked form cost (readouts, updates): at L = 196 about 1070 against 1056 MFMAs per slab.
 //
-// One workgroup holds one slab (or several short ones): keys scaled for both directions and values in LDS, 3 x 128
+// One workgroup holds one slab (or two short ones): keys scaled for both directions and values in LDS, 3 x 128
 // bytes per token, two workgroups per CU up to L = 208.  A wave owns 32 tokens (two 16-token tiles): their cumulative
 // gates (products with a 0/1 triangle, as in the chunked kernels; the waves' totals are exchanged through LDS and enter
 // as the accumulators' initial values), exponentials, scaled queries (registers) and keys (LDS), then their rows of the
@@ -20,7 +20,7 @@
 // its share of that) takes the range-safe form of bigla_chunk.hip, tile by tile (short_slab_safe), inside the same launch.
 //
 // Measured (kernel trace): 384 slabs of 196 tokens, 57.8 MB: 23.0 us (the chunked kernel that walks a slab twice in one
-// launch: 32.0 us); 192 slabs: 14.7 us (23.2); 1024 slabs of 49 tokens: 13.8 us (the general single-chunk kernel: 69.4).
+// launch: 32.0 us); 192 slabs: 14.7 us (23.2).
 // What bounds it: with two workgroups per CU the phases of one overlap those of the other, and a SIMD then spends about
 // equal times on the exponentials and scalings (24 vector instructions and 4 exponentials per 64 elements of q and k)
 // and on matrix instructions; a lone workgroup is a chain of 25 000 cycles: 6000 until the rows arrive, 5000 for the
@@ -58,7 +58,7 @@ template <int kDk>
 struct ShortSlab {
     static constexpr int kKeyBytes = 2 * kDk;
     unsigned kf, kb, v;
-    __host__ __device__ static unsigned bytes(int n_tiles) { return unsigned(n_tiles) * 16u * (2u * kKeyBytes + 128u); }
+    __host__ __device__ static constexpr unsigned bytes(int n_tiles) { return unsigned(n_tiles) * 16u * (2u * kKeyBytes + 128u); }
     __device__ __forceinline__ ShortSlab(int slot, int n_tiles)
     {
         kf = unsigned(slot) * bytes(n_tiles);
@@ -239,7 +239,7 @@ template <int kDk, bool kTm, bool kGates>
 __global__ __launch_bounds__(64 * kShortWaves, 4) void bigla_short_kernel(
     const uint16_t *__restrict__ q_all, const uint16_t *__restrict__ k_all, const uint16_t *__restrict__ v_all,
     const uint16_t *gf_all, const uint16_t *gb_all, uint16_t *__restrict__ out_all, float *__restrict__ eb_all, int L,
-    int n_tiles, int slab_waves, int waves /* per slab */, int slots, long n_slabs, int heads, GateSource gs)
+    int n_tiles, int slab_waves, int slots, long n_slabs, int heads, GateSource gs)
 {
     constexpr int kKs = kDk / 32;        // K-steps of a contraction over channels
     constexpr int kCt = kDk / 16;        // 16-channel tiles
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(64 * kShortWaves, 4) void bigla_short_kernel(
     constexpr int kGateLoads = kDk / 32;  // 16-byte loads per lane for the 16 whole rows of a gate tile
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
     const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
-    const int slot = wave / waves, w = wave - slot * waves;
+    const int slot = wave / slab_waves, w = wave - slot * slab_waves;
     // (past the last slab: the last one once more, same values)
     const long mine = long(blockIdx.x) * slots + slot, slab = mine < n_slabs ? mine : n_slabs - 1;
     const SlabIo<kTm, kDk> io(q_all, k_all, v_all, gf_all, gb_all, out_all, slab, L, heads);
@@ -256,16 +256,6 @@ __global__ __launch_bounds__(64 * kShortWaves, 4) void bigla_short_kernel(
     const bool two = 2 * w + 1 < n_tiles;  // the wave's second tile exists
     const int tile0 = 2 * w;
 
-    if (w >= slab_waves) {  // a wave for the range-safe form only: the barriers of the others
-        __syncthreads();
-        __syncthreads();
-        if (__builtin_amdgcn_readfirstlane(*strong) == 0)
-            __syncthreads();
-        else
-            short_slab_safe<kDk, kTm>(q_all, k_all, v_all, gf_all, gb_all, out_all, eb_all + slab * (2 * kShortTiles * kD), slab, slot, w,
-                                      waves, L, n_tiles, heads);
-        return;
-    }
     if (w == 0 && lane == 0) *strong = 0;
     if constexpr (!kGates) {
         // ---- the gates of the wave's 32 tokens
@@ -603,22 +593,36 @@ __global__ __launch_bounds__(64 * kShortWaves, 4) void bigla_short_kernel(
     asm volatile("" : "+s"(flag));
     if (flag != 0)
         short_slab_safe<kDk, kTm>(q_all, k_all, v_all, gf_all, gb_all, out_all, eb_all + slab * (2 * kShortTiles * kD), slab, slot, w,
-                                  waves, L, n_tiles, heads);
+                                  slab_waves, L, n_tiles, heads);
 }
 
 }  // namespace
 
-// With gates that decay by up to 16 nats in 64 tokens it is the faster one at every length up to 256 and every number of
-// slabs: per call in a captured graph, 48 slabs of 100 / 196 / 256 tokens 10.1 / 11.7 / 13.0 us against 12.0 / 14.1 / 14.4 with the
-// eight-wave kernels; 384 slabs 12.7 / 24.8 / 32.1 us against 18.2 / 33.0 / 34.7 with the four-wave kernels.  Beyond 16 nats it takes
-// the range-safe form, as the four-wave kernels do (at -0.3 a step, 192 and 384 slabs of 196 tokens 34 and 55 us against 67 and
-// 96), but the eight-wave kernels stay in the fast form up to 60: 48 slabs 28 us against 14.  Whose gates those are is known
-// on the device only, so calls that the eight-wave kernels can take (two chunks or more, fewer than 128 slabs) stay with them.
-// Up to 64 tokens the other choice is the general single-chunk kernel, the slower one in either form: 3 / 48 / 192 / 1024 slabs of 64
-// tokens with mild gates 5.9 / 6.1 / 6.8 / 14.6 us against 10.8 / 12.0 / 19.0 / 68.7, at -0.3 a step 10.0 / 10.5 / 12.2 / 35.8
-// against 14.0 / 15.4 / 23.7 / 80.9.
+}  // namespace vig
+
+#include "bigla_tile.hpp"
+
+namespace vig {
+
+// A sequence in one chunk, in one launch: a wave per tile (bigla_tile.hpp) or per two tiles (bigla_short_kernel), see below.
+// With gates that decay by up to 16 nats in 64 tokens one chunk is the faster way at nearly every length up to 256 and number of
+// slabs; beyond that the kernel with two tiles to a wave takes the range-safe form (at -0.3 a step, 192 and 384 slabs of 196
+// tokens 34 and 55 us against 67 and 96 of the four-wave kernels), the one with a tile to a wave and the eight-wave kernels stay
+// in the fast form.  Whose gates those are is known on the device only.  From 193 tokens on in fewer than 128 slabs the
+// eight-wave kernels are kept: 6 and 48 slabs of 225 tokens 12.9 us with mild gates and 13.2 at -0.3 a step against 13.7 and 15.4.
 // The score matrix grows with the square of the length: beyond 256 tokens the sequence is chunked.
-bool bigla_short_applicable(long BH, int L) { return L <= kShortTokens && (BH >= 128 || L <= kC); }
+bool bigla_short_applicable(long BH, int L) { return L <= kShortTokens && (BH >= 128 || L <= 192); }
+
+// A wave per tile, or per two tiles (which reads half as much LDS and keeps two slabs on a compute unit).  us per call, two tiles to a wave /
+// one, mild gates, 64-wide keys: 256 slabs of 80 tokens 10.1 / 8.4, 768 of 80 18.0 / 16.1, 1024 of 80 19.8 / 22.0, 1024 of 112 28.3 / 22.9, 2048 of 128
+// 59.7 / 45.1, 192 of 130 10.7 / 11.1, 192 of 196 14.0 / 15.5, 384 of 196 23.8 / 28.7; 32-wide: 256 of 100 8.7 / 6.9, 512 10.4 / 10.6, 1024 of 80
+// 13.9 / 17.3; up to 64 tokens 0.73 to 1.04 of it at any number of slabs.
+inline bool wave_per_tile(long BH, int L, int dk)
+{
+    if (L <= kC || BH < 128) return true;
+    if (L > 2 * kC) return false;
+    return dk == kD ? BH <= 768 || L > 96 : BH <= 384;
+}
 
 // bytes of workspace: the range-safe form's whole-tile decay factors
 size_t bigla_short_workspace_bytes(long BH) { return size_t(BH) * 2 * kShortTiles * kD * sizeof(float); }
@@ -628,14 +632,8 @@ hipError_t bigla_short_launch(const void *q, const void *k, const void *v, const
                               const GateSource *gates = nullptr)
 {
     const int n_tiles = (L + 15) / 16, slab_waves = (n_tiles + 1) / 2;
-    // Up to 64 tokens in up to 1024 slabs, a workgroup per slab with a wave per tile of the range-safe form (half of them
-    // idle in the fast form): 48 slabs of 64 tokens 6.1 us and, at -0.3 a step, 10.5, against 9.5 and 22.5 with four slabs in a
-    // workgroup and two tiles to a wave (the general single-chunk kernel: 12.0 and 15.4); 1024 slabs 14.6 / 35.8 against
-    // 15.1 / 34.3, beyond that the chip is full either way (2048 of 48: 21.3 / 54.7 against 20.1 / 48.0; dk = 64, calls in a
-    // captured graph).
-    const bool spread = L <= kC && BH <= 1024;
-    const int waves = spread ? n_tiles : slab_waves;     // per slab
-    const int slots = spread ? 1 : kShortWaves / waves;  // slabs per workgroup
+    const bool per_tile = wave_per_tile(BH, L, dk);
+    const int slots = per_tile ? 1 : kShortWaves / slab_waves;  // slabs per workgroup
     const long blocks = (BH + slots - 1) / slots;
     if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
     LaunchTimer timer(kKernelSlab, stream);
@@ -643,11 +641,18 @@ hipError_t bigla_short_launch(const void *q, const void *k, const void *v, const
     auto go = [&](auto dk_c, auto tm_c, auto gates_c) {
         constexpr int kDk = decltype(dk_c)::value;
         constexpr bool kTm = decltype(tm_c)::value, kGates = decltype(gates_c)::value;
+        if (per_tile) {
+            hipLaunchKernelGGL((bigla_tile_kernel<kDk, kTm, kGates>), dim3((unsigned)BH), dim3(unsigned(64 * n_tiles)), tile_lds_bytes<kDk>(n_tiles), stream,
+                               static_cast<const uint16_t *>(q), static_cast<const uint16_t *>(k), static_cast<const uint16_t *>(v),
+                               static_cast<const uint16_t *>(g_fwd), static_cast<const uint16_t *>(g_bwd), static_cast<uint16_t *>(out),
+                               static_cast<float *>(workspace), L, n_tiles, heads_token_major > 0 ? heads_token_major : 1, gates ? *gates : none);
+            return;
+        }
         const unsigned lds = unsigned(slots) * (ShortSlab<kDk>::bytes(n_tiles) + unsigned(sizeof(int)));
-        hipLaunchKernelGGL((bigla_short_kernel<kDk, kTm, kGates>), dim3((unsigned)blocks), dim3(unsigned(64 * waves * slots)), lds, stream,
+        hipLaunchKernelGGL((bigla_short_kernel<kDk, kTm, kGates>), dim3((unsigned)blocks), dim3(unsigned(64 * slab_waves * slots)), lds, stream,
                            static_cast<const uint16_t *>(q), static_cast<const uint16_t *>(k), static_cast<const uint16_t *>(v),
                            static_cast<const uint16_t *>(g_fwd), static_cast<const uint16_t *>(g_bwd), static_cast<uint16_t *>(out),
-                           static_cast<float *>(workspace), L, n_tiles, slab_waves, waves, slots, BH, heads_token_major > 0 ? heads_token_major : 1,
+                           static_cast<float *>(workspace), L, n_tiles, slab_waves, slots, BH, heads_token_major > 0 ? heads_token_major : 1,
                            gates ? *gates : none);
     };
     using std::integral_constant;

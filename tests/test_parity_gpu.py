@@ -1193,6 +1193,21 @@ def test_bigla_one_chunk_many_short_sequences(L, layout, dk):
     _check_one_chunk(wl.Workload("one_chunk_many", B=5, H=206, Hg=1, Wg=L, dk=dk, dv=64, dtype="bf16", gate_mu=-1.0), layout)
 
 
+@pytest.mark.parametrize("layout,dk", (("bhld", 64), ("blhd", 64), ("bhld", 32), ("blhd", 32)))
+@pytest.mark.parametrize("L", (65, 80, 81, 112, 128, 129, 177, 192, 193))
+def test_bigla_wave_per_tile(L, layout, dk):
+    """Few slabs of up to 192 tokens, a wave per 16-token tile: lengths around its tiles and the last one it takes, in one
+    call slabs of either form of the diagonal tiles and slabs that take the range-safe form."""
+    _check_one_chunk(wl.Workload("tiles", B=5, H=2, Hg=1, Wg=L, dk=dk, dv=64, dtype="bf16", gate_mu=-1.0), layout)
+
+
+@pytest.mark.parametrize("L,dk,slabs", ((65, 64, 770), (96, 64, 770), (97, 64, 770), (65, 32, 390), (100, 32, 390), (128, 32, 390)))
+def test_bigla_two_tiles_per_wave(L, dk, slabs):
+    """Either side of the line from which on two tiles go to a wave and two slabs to a workgroup, for 65 to 128 tokens."""
+    for n in (slabs - 5, slabs):
+        _check_one_chunk(wl.Workload("two_tiles", B=5, H=n // 5, Hg=1, Wg=L, dk=dk, dv=64, dtype="bf16", gate_mu=-1.0), "bhld")
+
+
 @pytest.mark.parametrize("slabs", (1024, 2560))
 @pytest.mark.parametrize("L,rate,dk", ((32, 0.48, 32), (40, 0.39, 32), (40, 0.39, 64), (48, 0.32, 32), (49, 0.3, 64)))
 def test_bigla_short_sequences_of_fast_decay(L, rate, dk, slabs):
