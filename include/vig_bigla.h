@@ -106,7 +106,8 @@ int bigla_fwd_layout(const void *q, const void *k, const void *v, const void *g_
  * bigla_fwd_layout with a choice among the kernels that evaluate the chunkwise form (Section 4.2.1,
  * Eq. (BiGLA); a measurement and testing aid: the result is the same up to operand rounding).
  *   VIG_FWD_AUTO              what bigla_fwd_layout runs: up to 192 tokens, and up to 256 in at least 128
- *                             slabs, one launch that takes the whole sequence as one chunk; otherwise the
+ *                             slabs, one launch that takes the whole sequence as one chunk; otherwise, in more
+ *                             than 256 slabs, one launch with a four-wave workgroup per slab, else the
  *                             eight-wave kernels;
  *   VIG_FWD_FOUR_WAVE         workgroups of four waves, each wave walking the whole chain of a chunk
  *                             step for its 16 tokens;
@@ -295,8 +296,9 @@ int gate_producer_fwd(const void *x, const void *w1, const void *w2, const void 
  *                            Same arithmetic as gate_producer_fwd, bit for bit.  VIG_BF16, dv = 64,
  *                            where bigla_fwd_plan admits VIG_FWD_WAVE_SPECIALISED (VIG_ERR_UNSUPPORTED
  *                            otherwise, and while vig_measure_alias_slabs is on);
- *   VIG_GATES_AUTO           VIG_GATES_IN_STATE_PASS where it applies (bf16, dv = 64: also wherever the mixer is
- *                            one launch, which makes the gates in the same way), else VIG_GATES_SEPARATE.
+ *   VIG_GATES_AUTO           VIG_GATES_IN_STATE_PASS where it applies (bf16, dv = 64: also wherever the mixer takes a
+ *                            sequence as one chunk, and makes the gates in the same way), else, and in more than 256
+ *                            longer slabs, VIG_GATES_SEPARATE.
  * workspace: at least gated_bigla_workspace_bytes(B, H, L, dk, dv, dtype) bytes (0 for invalid or unsupported
  * arguments; it covers every plan).
  */

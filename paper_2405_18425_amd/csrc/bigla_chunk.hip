@@ -270,7 +270,9 @@ __device__ __forceinline__ void finish_chunk(OutLds &sm, const uint16_t (*ktile)
 template <int kKs = 2>
 __device__ __forceinline__ void score_tiles(OutLds &sm, const int w, const int r, const int g, const bf16x8 qf0,
                                             const bf16x8 qf1, const bf16x8 qb0, const bf16x8 qb1, const bf16x8 kf0,
-                                            const bf16x8 kf1, const bf16x8 kb0, const bf16x8 kb1, ChunkOperands &op)
+                                            const bf16x8 kf1, const bf16x8 kb0, const bf16x8 kb1, const f32x4 pf_low,
+                                            const f32x4 pb_low /* what the low halves of split operands add to the diagonal */,
+                                            ChunkOperands &op)
 {
     // merged score tile, transposed: P^T[i][t]; key sub-block I < w forward, I > w backward,
     // I = w the masked sum of both (own token counted by both directions)
@@ -278,7 +280,7 @@ __device__ __forceinline__ void score_tiles(OutLds &sm, const int w, const int r
     for (int I = 0; I < 4; ++I) {
         const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
         if (I == w) {
-            f32x4 pf = mfma(kf0, qf0, zero), pb = mfma(kb0, qb0, zero);
+            f32x4 pf = mfma(kf0, qf0, pf_low), pb = mfma(kb0, qb0, pb_low);
             if (kKs > 1) {
                 pf = mfma(kf1, qf1, pf);
                 pb = mfma(kb1, qb1, pb);
@@ -339,7 +341,8 @@ __device__ __forceinline__ void out_chunk_fast(OutLds &sm, const int w, const in
     __syncthreads();  // kf, kb, tot visible
     prefetch_first();
 
-    score_tiles(sm, w, r, g, qf0, qf1, qb0, qb1, kf0, kf1, kb0, kb1, op);
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    score_tiles(sm, w, r, g, qf0, qf1, qb0, qb1, kf0, kf1, kb0, kb1, zero, zero, op);
 }
 
 // FAST form with the gate scans folded in, for the kernel that runs nothing else: per 16-channel
@@ -348,7 +351,8 @@ __device__ __forceinline__ void out_chunk_fast(OutLds &sm, const int w, const in
 // of one tile can overlap the LDS reads and MFMAs of the next (one basic block, no branch
 // between the scan and its use).  The forward chunk totals are the cumulative gates of the
 // chunk's last token (wave 3, r = 15).
-template <int kKs, class Prefetch>
+// kSplit: the operands of the diagonal tiles as bf16 pairs, hi.lo + lo.hi + hi.hi (fast decay, see kMildRange).
+template <int kKs, bool kSplit, class Prefetch>
 __device__ __forceinline__ void out_chunk_fast_fused(OutLds &sm, const bf16x8 (&tri_f)[2], const bf16x8 (&tri_b)[2],
                                                      const int w, const int r, const int g, const Row16 &qraw,
                                                      const Row16 &kraw, ChunkOperands &op, Prefetch &&prefetch_first)
@@ -378,8 +382,25 @@ __device__ __forceinline__ void out_chunk_fast_fused(OutLds &sm, const bf16x8 (&
             kf[n] *= fast_exp2(-xf);              // k * exp(-b_i)
         }
     }
-    const bf16x8 qf0 = pack8(qf), qf1 = pack8(qf + 8), qb0 = pack8(qb), qb1 = pack8(qb + 8);
-    const bf16x8 kf0 = pack8(kf), kf1 = pack8(kf + 8), kb0 = pack8(kb), kb1 = pack8(kb + 8);
+    bf16x8 qf0, qf1 = {}, qb0, qb1 = {}, kf0, kf1 = {}, kb0, kb1 = {};
+    f32x4 pf = {0.f, 0.f, 0.f, 0.f}, pb = pf;
+    if constexpr (kSplit) {
+        auto pair = [](const float *k8, const float *q8, bf16x8 &kh, bf16x8 &qh, f32x4 &p) __attribute__((always_inline)) {
+            bf16x8 kl, ql;
+            pack8_split(k8, kh, kl);
+            pack8_split(q8, qh, ql);
+            p = mfma(kl, qh, mfma(kh, ql, p));
+        };
+        pair(kf, qf, kf0, qf0, pf);
+        pair(kb, qb, kb0, qb0, pb);
+        if (kKs > 1) {
+            pair(kf + 8, qf + 8, kf1, qf1, pf);
+            pair(kb + 8, qb + 8, kb1, qb1, pb);
+        }
+    } else {
+        qf0 = pack8(qf); qf1 = pack8(qf + 8); qb0 = pack8(qb); qb1 = pack8(qb + 8);
+        kf0 = pack8(kf); kf1 = pack8(kf + 8); kb0 = pack8(kb); kb1 = pack8(kb + 8);
+    }
     *reinterpret_cast<bf16x8 *>(&sm.kf[row][8 * g]) = kf0;
     *reinterpret_cast<bf16x8 *>(&sm.kb[row][8 * g]) = kb0;
     if (kKs > 1) {  // the upper K-step of the key tiles is never read otherwise
@@ -390,7 +411,7 @@ __device__ __forceinline__ void out_chunk_fast_fused(OutLds &sm, const bf16x8 (&
 
     __syncthreads();  // kf, kb, tot visible
     prefetch_first();
-    score_tiles<kKs>(sm, w, r, g, qf0, qf1, qb0, qb1, kf0, kf1, kb0, kb1, op);
+    score_tiles<kKs>(sm, w, r, g, qf0, qf1, qb0, qb1, kf0, kf1, kb0, kb1, pf, pb, op);
 }
 
 // RANGE-SAFE form of one chunk, both directions (see the header); scans the sub-block-local,
@@ -563,7 +584,7 @@ __device__ __forceinline__ PathLds &path_lds<false>()
 
 // kLoc: the 2D gating locality injection of `lf` is applied to every chunk's rows before they are
 // written, so that `out_all` receives the block output instead of the token mixer's.
-template <bool kFastOnly, int kDk, bool kTm, bool kLoc, bool kInWs = false>
+template <bool kFastOnly, int kDk, bool kTm, bool kLoc, bool kInWs = false, bool kSplit = false>
 __device__ __forceinline__ void out_unit(
     const uint16_t *__restrict__ q_all, const uint16_t *__restrict__ k_all, const uint16_t *__restrict__ v_all,
     const uint16_t *__restrict__ gf_all, const uint16_t *__restrict__ gb_all, uint16_t *__restrict__ out_all,
@@ -766,7 +787,7 @@ __device__ __forceinline__ void out_unit(
             }
         };
         if (kFastOnly) {
-            out_chunk_fast_fused<kKs>(sm, tri_f, tri_b, w, r, g, q_row, k_row, op, prefetch_first);
+            out_chunk_fast_fused<kKs, kSplit>(sm, tri_f, tri_b, w, r, g, q_row, k_row, op, prefetch_first);
         } else {
             f32x4 Tb[4];
             chunk_gate_scan(sm.gf, tri_f, r, g, Bf, Tf);
@@ -826,8 +847,10 @@ __global__ __launch_bounds__(kThreads, 2) void bigla_segment_out_kernel(
 // kFwd = false (only with seg_states == nullptr): nothing reads the forward end state, so the fast
 // form skips the forward direction altogether (its cumulative gates, scaled keys and K^T V); the
 // forward chunk totals are still formed, for the choice of the form.
-template <int kDk, bool kTm, bool kFwd = true, bool kInWs = false>
-__device__ __forceinline__ bool state_unit(
+// kToFastRange: chunks are taken in the fast form up to kFastRange, not kMildRange; then 2 is returned where all of them were, but
+// some are beyond kMildRange.
+template <int kDk, bool kTm, bool kFwd = true, bool kInWs = false, bool kToFastRange = false>
+__device__ __forceinline__ int state_unit(
     const uint16_t *__restrict__ k_all, const uint16_t *__restrict__ v_all, const uint16_t *__restrict__ gf_all,
     const uint16_t *__restrict__ gb_all, float *__restrict__ seg_states, unsigned char *__restrict__ stash, int L,
     int n_chunks, int seg_chunks, int n_seg, const long unit, int heads)
@@ -865,7 +888,7 @@ __device__ __forceinline__ bool state_unit(
         Sb[jt] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     float4 rf = make_float4(1.f, 1.f, 1.f, 1.f), rb = rf;
-    bool all_fast = true;  // every chunk of the segment within the fast form's range
+    bool all_fast = true, all_mild = true;  // every chunk of the segment within the range
 
     struct ChunkRows {
         StagedRows k, v, gf, gb;
@@ -947,8 +970,9 @@ __device__ __forceinline__ bool state_unit(
             for (int n = 0; n < 16; ++n) t[n] = T[n >> 2][n & 3];
             if (r == 0) store_chan16(sm.tot[1], g, t);
         }
-        const bool fast = fmaxf(max_f, max_b) <= kMildRange;  // uniform over the workgroup
+        const bool fast = fmaxf(max_f, max_b) <= (kToFastRange ? kFastRange : kMildRange);  // uniform over the workgroup
         all_fast = all_fast && fast;
+        all_mild = all_mild && fmaxf(max_f, max_b) <= kMildRange;
         next.gf = load_rows(g_fwd, kr, far_token0);
         float4 df, db;  // this chunk's decay, rows at LDS positions 16w + 4g + e
         float tmp[16];
@@ -1076,7 +1100,7 @@ __device__ __forceinline__ bool state_unit(
             *reinterpret_cast<float4 *>(dst + kSegStateFloats + kD + 16 * w + 4 * g) = rb;
         }
     }
-    return all_fast;
+    return all_fast ? (all_mild ? 1 : 2) : 0;
 }
 
 template <int kDk, bool kTm>
@@ -1086,9 +1110,9 @@ __global__ __launch_bounds__(kThreads, 2) void bigla_segment_state_kernel(
     unsigned char *__restrict__ stash, int L, int n_chunks, int seg_chunks, int n_seg,
     int heads /* used when kTm: activations are [B,L,H,d] */)
 {
-    const bool all_fast =
+    const int all_fast =
         state_unit<kDk, kTm>(k, v, g_fwd, g_bwd, seg_states, stash, L, n_chunks, seg_chunks, n_seg, blockIdx.x, heads);
-    if (threadIdx.x == 0) seg_mild[blockIdx.x] = all_fast ? 1 : 0;
+    if (threadIdx.x == 0) seg_mild[blockIdx.x] = all_fast;
 }
 
 // One-segment plans (a workgroup per slab): state pass and output pass in ONE launch.  The stash
@@ -1102,12 +1126,15 @@ __global__ __launch_bounds__(kThreads, 2) void bigla_slab_kernel(
     unsigned char *__restrict__ stash, int L, int n_chunks, int heads, const LocalityFusion lf)
 {
     const long unit = blockIdx.x;
-    const bool all_fast =
-        state_unit<kDk, kTm, false>(k, v, g_fwd, g_bwd, nullptr, stash, L, n_chunks, n_chunks, 1, unit, heads);
+    const int form =
+        state_unit<kDk, kTm, false, false, !kLoc>(k, v, g_fwd, g_bwd, nullptr, stash, L, n_chunks, n_chunks, 1, unit, heads);
     __syncthreads();  // stash written (and complete), the state pass's LDS no longer read
-    if (all_fast)     // uniform over the workgroup
+    if (form == 1)    // uniform over the workgroup
         out_unit<true, kDk, kTm, kLoc>(q, k, v, g_fwd, g_bwd, out, nullptr, stash, L, n_chunks, n_chunks, 1, unit,
                                        heads, lf);
+    else if (!kLoc && form == 2)  // (with the epilogue of wide grids, which has no registers to spare, the general code)
+        out_unit<true, kDk, kTm, kLoc, false, true>(q, k, v, g_fwd, g_bwd, out, nullptr, stash, L, n_chunks, n_chunks, 1,
+                                                    unit, heads, lf);
     else
         out_unit_general<kDk, kTm, kLoc>(q, k, v, g_fwd, g_bwd, out, nullptr, stash, L, n_chunks, n_chunks, 1, unit,
                                          heads, lf);
@@ -1211,6 +1238,17 @@ hipError_t bigla_chunk_set_alias(int on)
     return hipMemcpyToSymbol(HIP_SYMBOL(g_alias_inputs), &on, sizeof(int));
 }
 
+// More slabs than compute units: a four-wave workgroup per slab, two of which share a compute unit, in one launch.  The
+// eight-wave kernels, one workgroup a compute unit, take a second round of it.  us per call, eight-wave kernels / workgroup per slab,
+// mild gates and -0.3 a step: 257 slabs of 300 tokens 48.5 / 36.0 and 51.5 / 39.0, 270 of 363 57.0 / 43.4, 300 of 600 89.8 / 70.6 and 94.8 /
+// 76.4, 512 of 300 57.9 / 41.5, 513 of 300 74.8 / 59.5, 1024 of 300 112.6 / 84.4, 400 of 300 with 32-wide keys 42.3 / 29.4; 232 of 405
+// 35.3 / 36.3, 144 of 460 36.9 / 40.1.
+static bool bigla_chunk_slab_preferred(long BH) { return BH > 256; }
+
+// The gates made by the state pass need the eight-wave kernels: 258 slabs of 300 tokens 61 us against 50 with the gates first, 300
+// of 600 112 / 92, 1020 of 300 136 / 118.
+bool bigla_chunk_gates_apart(long BH, int L) { return !bigla_short_applicable(BH, L) && bigla_chunk_slab_preferred(BH); }
+
 bool bigla_chunk_gated_selectable(long BH, int L, int dk)
 {
     return !g_alias_on && (bigla_short_applicable(BH, L) ? (dk == kD || dk == kD / 2) : bigla_chunk_ws_applicable(BH, L, dk));
@@ -1254,7 +1292,7 @@ hipError_t bigla_chunk_launch(const void *q, const void *k, const void *v, const
         return bigla_short_launch(q, k, v, g_fwd, g_bwd, out, BH, L, dk, heads_token_major, workspace, stream);
     const bool ws_ok = bigla_chunk_ws_applicable(BH, L, dk) && (!fusion || (fusion->Wg < kXHalo && L < (1 << 22)));
     if (kernels == 2 && !ws_ok) return hipErrorInvalidValue;
-    if (kernels == 2 || (kernels == 0 && ws_ok)) {
+    if (kernels == 2 || (kernels == 0 && ws_ok && (fusion || !bigla_chunk_slab_preferred(BH)))) {
         return bigla_chunk_ws_launch(q, k, v, g_fwd, g_bwd, out, BH, L, dk, heads_token_major, workspace, stream,
                                      nullptr, fusion);
     }

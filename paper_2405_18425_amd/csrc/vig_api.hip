@@ -370,7 +370,8 @@ int gated_bigla_fwd(const void *x, const void *w1, const void *w2, const void *b
     // (asked for by name the plan keeps to the shapes of the eight-wave kernels; short sequences beyond those get it from AUTO)
     if (plan == VIG_GATES_IN_STATE_PASS && !(fusable && vig::bigla_chunk_ws_selectable(BH, L, dk))) return VIG_ERR_UNSUPPORTED;
     const size_t mixer_bytes = round256(bigla_workspace_bytes(B, H, L, dk, dv, dtype));
-    if (plan == VIG_GATES_SEPARATE || !fusable) {
+    const bool apart = plan == VIG_GATES_SEPARATE || (plan == VIG_GATES_AUTO && fusable && vig::bigla_chunk_gates_apart(BH, L));
+    if (apart || !fusable) {
         const int st = gate_producer_fwd(x, w1, w2, bias, g_fwd, g_bwd, B, H, L, D, dk, tau, dtype, layout, stream);
         if (st != VIG_OK) return st;
         return bigla_fwd_layout(q, k, v, g_fwd, g_bwd, out, B, H, L, dk, dv, dtype, layout, workspace, mixer_bytes, stream);

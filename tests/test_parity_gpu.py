@@ -1201,6 +1201,27 @@ def test_bigla_wave_per_tile(L, layout, dk):
     _check_one_chunk(wl.Workload("tiles", B=5, H=2, Hg=1, Wg=L, dk=dk, dv=64, dtype="bf16", gate_mu=-1.0), layout)
 
 
+@pytest.mark.parametrize("layout,dk", (("bhld", 64), ("blhd", 64), ("blhd", 32)))
+@pytest.mark.parametrize("L", (257, 320, 390))
+def test_bigla_workgroup_per_slab(L, layout, dk):
+    """More slabs than compute units, longer than one chunk: a four-wave workgroup per slab, with mild gates, beyond the limit of bf16
+    operands in the fast form, and beyond that form, in one call; the gated call makes the gates first."""
+    import torch
+    from paper_2405_18425_amd import binding as vb
+
+    _check_one_chunk(wl.Workload("slabs", B=5, H=52, Hg=1, Wg=L, dk=dk, dv=64, dtype="bf16", gate_mu=-1.0), layout)
+    H = 52
+    st = wl.generate_gate_inputs(5, L, 384, H, dk, "bf16", seed=L, bias_mu=0.0)
+    t = {n: wl.to_torch(a, "bf16", "cuda:0") for n, a in st.items()}
+    w1, w2 = t["w1"].t().contiguous(), t["w2"].t().contiguous()
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    shape = (5, H, L) if layout == "bhld" else (5, L, H)
+    q, k, v = (torch.randn(*shape, d, device="cuda", generator=gen).bfloat16() for d in (dk, dk, 64))
+    call = lambda plan: vb.gated_bigla_fwd(t["x"], w1, w2, q, k, v, bias=t["bias"], layout=layout, plan=plan)
+    for a, b in zip(call("auto"), call("separate")):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("L,dk,slabs", ((65, 64, 770), (96, 64, 770), (97, 64, 770), (65, 32, 390), (100, 32, 390), (128, 32, 390)))
 def test_bigla_two_tiles_per_wave(L, dk, slabs):
     """Either side of the line from which on two tiles go to a wave and two slabs to a workgroup, for 65 to 128 tokens."""
