@@ -844,11 +844,12 @@ __device__ __forceinline__ void ws_out_unit(
             rz0 = load_z(0, 0);
         }
 
+        __syncthreads();  // (the producers' prologue barrier)
+        // (while the producers scale the first chunk)
         if (seg_states != nullptr && owns_rows) {
             fold(S, 0, 0, seg, 1);
             fold(Sseg, 1, n_seg - 1, n_seg - 1 - seg, -1);
         }
-        __syncthreads();  // (the producers' prologue barrier)
         for (int m = 0; m <= nch; ++m) {
             const int c = m - 1, b = c & 1;
             WS_MARK(0);
