@@ -268,10 +268,11 @@ __global__ __launch_bounds__(kWsThreads) void bigla_ws_state_kernel(
         bf16x8 tri_f[2], tri_b[2];
         scan_triangle<0>(w, r, g, tri_f);
         scan_triangle<1>(w, r, g, tri_b);
-        StagedRows rk = load_keys(io.k, nch - 1);
-        StagedRows rgf, rgb;
+        StagedRows rk, rgf, rgb;
+        if (kGates) rk = load_keys(io.k, nch - 1);
         if (!kGates) {
             StagedRows gf = load_keys(io.gf, nch - 1), gb = load_keys(io.gb, nch - 1);
+            rk = load_keys(io.k, nch - 1);
             zero_widened_half<kDk>(gf, lane);
             zero_widened_half<kDk>(gb, lane);
             stage_gates(sm.g[0][0], w, lane, gf);
@@ -597,9 +598,13 @@ __device__ __forceinline__ void ws_out_unit(
         bf16x8 tri_f[2], tri_b[2];
         scan_triangle<0>(w, r, g, tri_f);
         scan_triangle<1>(w, r, g, tri_b);
-        StagedRows rq = load_rows(io.q, lrk, token0(0)), rk = load_rows(io.k, lrk, token0(0)), rv = load_rows(io.v, lr, token0(0));
+        StagedRows rq, rk, rv;
         {
+            // (gates first: they are waited for first)
             StagedRows gf = load_rows(io.gf, lrk, token0(0)), gb = load_rows(io.gb, lrk, token0(0));
+            rq = load_rows(io.q, lrk, token0(0));
+            rk = load_rows(io.k, lrk, token0(0));
+            rv = load_rows(io.v, lr, token0(0));
             zero_widened_half<kDk>(gf, lane);
             zero_widened_half<kDk>(gb, lane);
             stage_gates(sm.g[0], w, lane, gf);
@@ -765,29 +770,41 @@ __device__ __forceinline__ void ws_out_unit(
         f32x4 S[4], Sseg[4];
 #pragma unroll
         for (int jt = 0; jt < 4; ++jt) S[jt] = Sseg[jt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        auto fold = [&](f32x4 (&E)[4], int dir, int first, int count, int step) {
+        // (Both directions' loads of up to four segments are in flight together: with one direction after the other, 6 slabs of 4096 tokens
+        // 29.3 us for 26.4, 2 of 2000 22.4 / 19.3, 15 of 1026 24.0 / 23.0.)
+        auto fold = [&](f32x4 (&Ef)[4], int count_f, f32x4 (&Eb)[4], int count_b) {
             const float *slab_states = seg_states + slab * n_seg * kSegFloats;
-            constexpr int kBatch = 4;
-            for (int i0 = 0; i0 < count; i0 += kBatch) {
-                f32x4 local[kBatch][4];
-                float4 decay[kBatch];
+            constexpr int kBatch = kLoc ? 2 : 4;  // (the locality epilogue has no registers to spare)
+            for (int i0 = 0; i0 < max(count_f, count_b); i0 += kBatch) {
+                f32x4 local[2][kBatch][4];
+                float4 decay[2][kBatch];
 #pragma unroll
-                for (int u = 0; u < kBatch; ++u) {
-                    const float *sp = slab_states + size_t(first + step * min(i0 + u, count - 1)) * kSegFloats;
+                for (int dir = 0; dir < 2; ++dir) {
+                    const int count = dir == 0 ? count_f : count_b;
+                    if (i0 >= count) continue;
 #pragma unroll
-                    for (int jt = 0; jt < 4; ++jt)
-                        local[u][jt] = reinterpret_cast<const f32x4 *>(sp + dir * kD * kD)[256 * jt + tid4];
-                    decay[u] = *reinterpret_cast<const float4 *>(sp + kSegStateFloats + dir * kD + 16 * w + 4 * g);
+                    for (int u = 0; u < kBatch; ++u) {
+                        const int i = min(i0 + u, count - 1);
+                        const float *sp = slab_states + size_t(dir == 0 ? i : n_seg - 1 - i) * kSegFloats;
+#pragma unroll
+                        for (int jt = 0; jt < 4; ++jt)
+                            local[dir][u][jt] = reinterpret_cast<const f32x4 *>(sp + dir * kD * kD)[256 * jt + tid4];
+                        decay[dir][u] = *reinterpret_cast<const float4 *>(sp + kSegStateFloats + dir * kD + 16 * w + 4 * g);
+                    }
                 }
 #pragma unroll
-                for (int u = 0; u < kBatch; ++u) {
-                    if (i0 + u < count) {
+                for (int dir = 0; dir < 2; ++dir) {
+                    f32x4(&E)[4] = dir == 0 ? Ef : Eb;
 #pragma unroll
-                        for (int jt = 0; jt < 4; ++jt) {
-                            E[jt][0] = fmaf(E[jt][0], decay[u].x, local[u][jt][0]);
-                            E[jt][1] = fmaf(E[jt][1], decay[u].y, local[u][jt][1]);
-                            E[jt][2] = fmaf(E[jt][2], decay[u].z, local[u][jt][2]);
-                            E[jt][3] = fmaf(E[jt][3], decay[u].w, local[u][jt][3]);
+                    for (int u = 0; u < kBatch; ++u) {
+                        if (i0 + u < (dir == 0 ? count_f : count_b)) {
+#pragma unroll
+                            for (int jt = 0; jt < 4; ++jt) {
+                                E[jt][0] = fmaf(E[jt][0], decay[dir][u].x, local[dir][u][jt][0]);
+                                E[jt][1] = fmaf(E[jt][1], decay[dir][u].y, local[dir][u][jt][1]);
+                                E[jt][2] = fmaf(E[jt][2], decay[dir][u].z, local[dir][u][jt][2]);
+                                E[jt][3] = fmaf(E[jt][3], decay[dir][u].w, local[dir][u][jt][3]);
+                            }
                         }
                     }
                 }
@@ -845,10 +862,9 @@ __device__ __forceinline__ void ws_out_unit(
         }
 
         __syncthreads();  // (the producers' prologue barrier)
-        // (while the producers scale the first chunk)
+        // (while the producers scale the first chunk; before the barrier: 24 slabs of 300 tokens 13.2 us for 12.2, 54 of 945 28.3 / 27.2)
         if (seg_states != nullptr && owns_rows) {
-            fold(S, 0, 0, seg, 1);
-            fold(Sseg, 1, n_seg - 1, n_seg - 1 - seg, -1);
+            fold(S, seg, Sseg, n_seg - 1 - seg);
         }
         for (int m = 0; m <= nch; ++m) {
             const int c = m - 1, b = c & 1;
