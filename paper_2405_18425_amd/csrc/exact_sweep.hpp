@@ -217,6 +217,12 @@ struct PartStage {
 template <>
 struct PartStage<1> {};
 
+// A decay over several tokens, as a product of their factors that is zero only where a factor is: an infinite element of the
+// matrix then stays infinite over a part, as it does from token to token.  (The smallest positive number for a product below
+// it: the largest finite element adds less than 5e-7.)
+constexpr float kLeastFactor = 1.401298464324817e-45f;
+__device__ __forceinline__ float joint_factor(float a, float b) { return fmaxf(a * b, fminf(fminf(a, b), kLeastFactor)); }
+
 // M: what enters the wave's part, from what the parts before it on its way leave
 template <int kParts>
 __device__ __forceinline__ void enter_part(const PartStage<kParts> &ex, int matrix, bool descending, int part, int lane, float (&M)[kStrip])
@@ -312,14 +318,19 @@ __device__ __forceinline__ void column_sweep(const T *u_rows, const T *r_rows, c
     };
     if constexpr (kParts > 1) {
         if (part != (descending ? 0 : kParts - 1)) {  // (nobody enters anything after the last part)
-            float total = 1.f;
+            float total = 1.f, least = 1.f;  // joint_factor of the part's factors, their minimum taken apart
             auto fetch = [&](Operands &o, int n) __attribute__((always_inline)) { fetch_rows(o, min(n, way.tiles - 1), std::false_type{}); };
             auto walk = [&](Operands &o, int n) __attribute__((always_inline)) {
                 clear_past_end(o, n);
 #pragma unroll
-                for (int i = 0; i < kTile; ++i) total *= advance(o, i);
+                for (int i = 0; i < kTile; ++i) {
+                    const float alpha = advance(o, i);
+                    total *= alpha;
+                    least = fminf(least, alpha);
+                }
             };
             over_tiles<Operands, kDepth<Off, kParts>>(0, way.tiles, fetch, walk);
+            total = fmaxf(total, fminf(least, kLeastFactor));
             const float f = kDelayed ? before : 1.f;
             parts.end[descending][part][0][lane] = make_float4(f * M[0], f * M[1], f * M[2], f * M[3]);
             parts.decay[descending][part][0][lane] = make_float4(total, total, total, total);
@@ -502,7 +513,7 @@ __device__ __forceinline__ void row_sweep(const T *q_rows, const T *k_rows, cons
             auto walk = [&](Operands &o, int n) __attribute__((always_inline)) {
                 put_stage(o, n);
 #pragma unroll
-                for (int j = 0; j < kLoads / 2; ++j) total[j] *= o.s[j];
+                for (int j = 0; j < kLoads / 2; ++j) total[j] = joint_factor(total[j], o.s[j]);
 #pragma unroll
                 for (int i = 0; i < kTile; ++i) advance(o.v[i], 0.5f * o.d[i], i);
                 lds_order();
@@ -526,7 +537,7 @@ __device__ __forceinline__ void row_sweep(const T *q_rows, const T *k_rows, cons
                     float f[kStrip];
                     load_strip(&stage.x[i][m][kStrip * grp], f);
 #pragma unroll
-                    for (int c = 0; c < kStrip; ++c) decay[m][c] *= f[c];
+                    for (int c = 0; c < kStrip; ++c) decay[m][c] = joint_factor(decay[m][c], f[c]);
                 }
                 parts.decay[descending][part][m][lane] = make_float4(decay[m][0], decay[m][1], decay[m][2], decay[m][3]);
             }

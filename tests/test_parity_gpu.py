@@ -1313,6 +1313,32 @@ def test_exact_kernels_parts(B, H, L, dk, dv, layout):
     _check_exact(B, H, L, dk, dv, layout)
 
 
+@pytest.mark.parametrize("B,H,L,dk,dv", ((1, 2, 64, 64, 64), (3, 4, 64, 64, 64), (1, 3, 72, 16, 32), (2, 5, 64, 32, 16)))
+def test_exact_kernels_parts_keep_an_infinite_element(B, H, L, dk, dv):
+    """An element of the state that is infinite stays so under any decay that is not zero, also across parts of a strip whose
+    joint decay (e^-128 and less) is below the range of fp32: with positive inputs every output that it reaches is infinite and
+    none is NaN."""
+    import torch
+    from paper_2405_18425_amd import binding as vb
+
+    _say(f"exact kernels, an infinite element {B}x{H} L{L} dk{dk} dv{dv}")
+    gen = torch.Generator(device="cuda").manual_seed(L + dk)
+    rand = lambda d: torch.rand(B, H, L, d, device="cuda", generator=gen) + 0.5
+    q, k, v, d_out = rand(dk), rand(dk), rand(dv), rand(dv)
+    gate = torch.full((B, H, L, dk), -8.0, device="cuda")
+    inf = lambda a: bool(torch.isposinf(a[0, 0]).all()) and bool(torch.isfinite(a[0, 1:]).all())
+    for t0 in (1, L - 2):
+        x = v.clone()
+        x[0, 0, t0, 3] = float("inf")
+        out = vb.bigla_fwd(q, k, x, gate, gate)
+        assert inf(out[..., 3]) and bool(torch.isfinite(out[..., :3]).all()), f"out {t0}"
+        assert inf(vb.bigla_bwd(q, k, x, gate, gate, d_out)[0]), f"dq {t0}"
+        x = d_out.clone()
+        x[0, 0, t0, 3] = float("inf")
+        _, dk_, dv_, _, _ = vb.bigla_bwd(q, k, v, gate, gate, x)
+        assert inf(dk_) and inf(dv_[..., 3]) and bool(torch.isfinite(dv_[..., :3]).all()), f"dk, dv {t0}"
+
+
 def _check_exact(B, H, L, dk, dv, layout):
     import oracle
     import torch
