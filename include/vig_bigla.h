@@ -296,9 +296,9 @@ int gate_producer_fwd(const void *x, const void *w1, const void *w2, const void 
  *                            Same arithmetic as gate_producer_fwd, bit for bit.  VIG_BF16, dv = 64,
  *                            where bigla_fwd_plan admits VIG_FWD_WAVE_SPECIALISED (VIG_ERR_UNSUPPORTED
  *                            otherwise, and while vig_measure_alias_slabs is on);
- *   VIG_GATES_AUTO           VIG_GATES_IN_STATE_PASS where it applies (bf16, dv = 64: also wherever the mixer takes a
- *                            sequence as one chunk, and makes the gates in the same way), else, and in more than 256
- *                            longer slabs, VIG_GATES_SEPARATE.
+ *   VIG_GATES_AUTO           where the mixer takes a sequence as one chunk (bf16, dv = 64; see bigla_fwd_plan), its one launch
+ *                            makes the gates in the same way; else VIG_GATES_IN_STATE_PASS where it applies and is the
+ *                            faster one (up to 256 slabs); else VIG_GATES_SEPARATE.
  * workspace: at least gated_bigla_workspace_bytes(B, H, L, dk, dv, dtype) bytes (0 for invalid or unsupported
  * arguments; it covers every plan).
  */

@@ -1255,13 +1255,14 @@ bool bigla_chunk_gated_selectable(long BH, int L, int dk)
 }
 
 // bigla_chunk_launch with the first pass over the keys (the state pass of the eight-wave kernels, or the one pass of
-// the kernel for short sequences) making the gates from the gate producer's low-rank half, and writing them to g_fwd
-// and g_bwd.
+// the kernel for short sequences, which takes the shapes of both unless state_pass) making the gates from the gate producer's
+// low-rank half, and writing them to g_fwd and g_bwd.
 hipError_t bigla_chunk_gated_launch(const void *q, const void *k, const void *v, void *g_fwd, void *g_bwd, void *out,
                                     long BH, int L, int dk, int n_heads, int heads_token_major, const void *lowrank,
-                                    const void *w2, const void *bias, float tau, void *workspace, hipStream_t stream)
+                                    const void *w2, const void *bias, float tau, bool state_pass, void *workspace, hipStream_t stream)
 {
     if (!bigla_chunk_gated_selectable(BH, L, dk) || n_heads <= 0 || BH % n_heads != 0) return hipErrorInvalidValue;
+    if (state_pass && !bigla_chunk_ws_applicable(BH, L, dk)) return hipErrorInvalidValue;
     if (g_alias_on) return hipErrorInvalidValue;  // aliased slabs would all write the first slab's gates
     GateSource gs;
     gs.lowrank = static_cast<const uint16_t *>(lowrank);
@@ -1269,7 +1270,7 @@ hipError_t bigla_chunk_gated_launch(const void *q, const void *k, const void *v,
     gs.bias = static_cast<const uint16_t *>(bias);
     gs.inv_tau = 1.f / tau;
     gs.n_heads = n_heads;
-    if (bigla_short_applicable(BH, L))
+    if (!state_pass && bigla_short_applicable(BH, L))
         return bigla_short_launch(q, k, v, g_fwd, g_bwd, out, BH, L, dk, heads_token_major, workspace, stream, &gs);
     return bigla_chunk_ws_launch(q, k, v, g_fwd, g_bwd, out, BH, L, dk, heads_token_major, workspace, stream, &gs);
 }

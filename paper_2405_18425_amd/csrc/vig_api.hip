@@ -367,8 +367,9 @@ int gated_bigla_fwd(const void *x, const void *w1, const void *w2, const void *b
     const long BH = long(B) * H;
     const bool fusable = chunkwise_fwd(L, dk, dv, bf16) && vig::bigla_chunk_gated_selectable(BH, L, dk) &&
                          chunk_offsets_ok(L, H, layout);
-    // (asked for by name the plan keeps to the shapes of the eight-wave kernels; short sequences beyond those get it from AUTO)
-    if (plan == VIG_GATES_IN_STATE_PASS && !(fusable && vig::bigla_chunk_ws_selectable(BH, L, dk))) return VIG_ERR_UNSUPPORTED;
+    // (by name the state pass of the eight-wave kernels, at every shape that they take; AUTO prefers the one-chunk kernel where it applies)
+    const bool by_name = plan == VIG_GATES_IN_STATE_PASS;
+    if (by_name && !(fusable && vig::bigla_chunk_ws_selectable(BH, L, dk))) return VIG_ERR_UNSUPPORTED;
     const size_t mixer_bytes = round256(bigla_workspace_bytes(B, H, L, dk, dv, dtype));
     const bool apart = plan == VIG_GATES_SEPARATE || (plan == VIG_GATES_AUTO && fusable && vig::bigla_chunk_gates_apart(BH, L));
     if (apart || !fusable) {
@@ -389,7 +390,7 @@ int gated_bigla_fwd(const void *x, const void *w1, const void *w2, const void *b
     const hipError_t e = vig::gate_lowrank_launch(x, w1, lowrank, B, L, D, s);
     if (e != hipSuccess) return hip_status(e);
     return hip_status(vig::bigla_chunk_gated_launch(q, k, v, g_fwd, g_bwd, out, BH, L, dk, H,
-                                                    layout == VIG_LAYOUT_BLHD ? H : 0, lowrank, w2, bias, tau, workspace, s));
+                                                    layout == VIG_LAYOUT_BLHD ? H : 0, lowrank, w2, bias, tau, by_name, workspace, s));
 }
 
 const char *vig_status_str(int status)

@@ -38,13 +38,14 @@ hipError_t bigla_chunk_launch(const void *q, const void *k, const void *v, const
                               int kernels, void *workspace, hipStream_t stream);
 
 // The eight-wave kernels with the state pass making the gates from the gate producer's low-rank half
-// (lowrank [B][L][16] bf16); g_fwd, g_bwd are written.  bf16, dv = 64, dk = 64 or 32; not while slabs are aliased.
+// (lowrank [B][L][16] bf16); g_fwd, g_bwd are written.  bf16, dv = 64, dk = 64 or 32; not while slabs are aliased.  Unless
+// state_pass (then bigla_chunk_ws_selectable), sequences taken as one chunk: the one launch does the same.
 bool bigla_chunk_gated_selectable(long BH, int L, int dk);
 // where it applies, but the gates in a launch of their own are faster
 bool bigla_chunk_gates_apart(long BH, int L);
 hipError_t bigla_chunk_gated_launch(const void *q, const void *k, const void *v, void *g_fwd, void *g_bwd, void *out,
                                     long BH, int L, int dk, int n_heads, int heads_token_major, const void *lowrank,
-                                    const void *w2, const void *bias, float tau, void *workspace, hipStream_t stream);
+                                    const void *w2, const void *bias, float tau, bool state_pass, void *workspace, hipStream_t stream);
 
 // ---- gradient of the token mixer -----------------------------------------------------------------
 // Exact fp32 recurrences for any supported head shape and both dtypes; for bf16 with dv = 64 and dk = 64 or 32 the

@@ -748,7 +748,7 @@ def test_gate_producer_into_bigla_chain():
 @pytest.mark.parametrize("B,L,D,H,layout,bias_mu,with_bias,dk", [
     (2, 1024, 384, 6, "bhld", -2.0, True, 64),     # several segments per slab
     (3, 300, 192, 3, "blhd", 0.0, True, 64),       # ragged last chunk, token-major
-    (2, 130, 64, 2, "bhld", 1.0, False, 64),       # three chunks, no bias
+    (2, 130, 64, 2, "bhld", 1.0, False, 64),       # three chunks, no bias (by default one launch takes them as one)
     (1, 4096, 384, 2, "bhld", -1.0, True, 64),     # two slabs cut into many segments
     (2, 700, 128, 4, "blhd", -16.0, True, 64),     # gates of -1 per step: every unit leaves the fast form
     (2, 640, 128, 3, "bhld", -12.0, True, 64),     # around the fast form's limit: some units inside, some outside
@@ -758,7 +758,8 @@ def test_gate_producer_into_bigla_chain():
 ])
 def test_gated_bigla_plans(B, L, D, H, layout, bias_mu, with_bias, dk):
     """Gate producer + token mixer as one call (Section 3 gate into Eq. (BiGLA)): the plan whose state pass makes
-    the gates itself against the oracle's chain, and bit for bit against the two separate launches."""
+    the gates itself against the oracle's chain, and bit for bit against the gate producer followed by the eight-wave
+    kernels; the default plan bit for bit against the two separate launches."""
     import torch
     import oracle
     from paper_2405_18425_amd import binding as vb
@@ -779,8 +780,10 @@ def test_gated_bigla_plans(B, L, D, H, layout, bias_mu, with_bias, dk):
         out, gf, gb = vb.gated_bigla_fwd(t["x"], w1, w2, t["q"], t["k"], t["v"], bias=bias, layout=layout, plan=plan)
         torch.cuda.synchronize()
         res[plan] = (out, gf, gb)
+    eight_wave = vb.bigla_fwd(t["q"], t["k"], t["v"], *res["separate"][1:], layout=layout, plan="wave_specialised")
     for i, name in enumerate(("out", "g_fwd", "g_bwd")):
-        assert torch.equal(res["in_state_pass"][i], res["separate"][i]), f"{name}: fused != separate"
+        want = res["separate"][i] if i > 0 else eight_wave
+        assert torch.equal(res["in_state_pass"][i], want), f"{name}: in_state_pass != separate"
         assert torch.equal(res["auto"][i], res["separate"][i]), f"{name}: auto != separate"
     back = (lambda a: a.transpose(1, 2).contiguous()) if layout == "blhd" else (lambda a: a)
     out, gf, gb = (wl.widen(wl.from_torch(back(a), "bf16"), "bf16") for a in res["in_state_pass"])
@@ -792,6 +795,35 @@ def test_gated_bigla_plans(B, L, D, H, layout, bias_mu, with_bias, dk):
     assert_close(out, oracle.bigla(wd["q"], wd["k"], wd["v"], gf, gb), TOL["bf16"], "mixer on the stored gates")
     rel = assert_close(out, oracle.bigla(wd["q"], wd["k"], wd["v"], rf, rb), TOL["bf16"], "chain")
     _say(f"  chain: max|err|/max|ref| = {rel:.3e}")
+
+
+@pytest.mark.parametrize("layout,dk", (("bhld", 64), ("blhd", 32)))
+@pytest.mark.parametrize("L", (65, 130, 192, 193))
+def test_gates_in_state_pass_by_name_runs_the_state_pass(L, layout, dk):
+    """VIG_GATES_IN_STATE_PASS asked for by name runs the eight-wave kernels at every shape that VIG_FWD_WAVE_SPECIALISED
+    admits, also where the default plan takes the sequence as one chunk."""
+    import torch
+    from paper_2405_18425_amd import binding as vb
+
+    B, H, D = 2, 3, 192
+    _say(f"gates in the state pass L{L} {layout} dk{dk}")
+    st = wl.generate_gate_inputs(B, L, D, H, dk, "bf16", seed=L, bias_mu=0.0)
+    t = {n: wl.to_torch(a, "bf16", "cuda:0") for n, a in st.items()}
+    w1, w2 = t["w1"].t().contiguous(), t["w2"].t().contiguous()
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    shape = (B, H, L) if layout == "bhld" else (B, L, H)
+    q, k, v = (torch.randn(*shape, d, device="cuda", generator=gen).bfloat16() for d in (dk, dk, 64))
+    vb.timing_enable(True)
+    try:
+        got = vb.gated_bigla_fwd(t["x"], w1, w2, q, k, v, bias=t["bias"], layout=layout, plan="in_state_pass")
+        launches = {n: vb.timing_collect(n)[1] for n in ("gate_lowrank", "segment_state", "segment_out", "slab", "gate_producer")}
+    finally:
+        vb.timing_enable(False)
+    assert launches == {"gate_lowrank": 1, "segment_state": 1, "segment_out": 1, "slab": 0, "gate_producer": 0}, launches
+    gf, gb = vb.gate_producer_fwd(t["x"], w1, w2, H, dk, bias=t["bias"], layout=layout)
+    want = vb.bigla_fwd(q, k, v, gf, gb, layout=layout, plan="wave_specialised")
+    for a, b, name in zip(got, (want, gf, gb), ("out", "g_fwd", "g_bwd")):
+        assert torch.equal(a, b), name
 
 
 def test_path_captured_in_a_hip_graph():
