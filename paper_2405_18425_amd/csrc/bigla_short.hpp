@@ -635,17 +635,22 @@ hipError_t bigla_short_launch(const void *q, const void *k, const void *v, const
     const bool per_tile = wave_per_tile(BH, L, dk);
     const int slots = per_tile ? 1 : kShortWaves / slab_waves;  // slabs per workgroup
     const long blocks = (BH + slots - 1) / slots;
-    if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
+    if (blocks > 0x7fffffffL || (per_tile && n_tiles > kTileMost)) return hipErrorInvalidValue;
     LaunchTimer timer(kKernelSlab, stream);
     const GateSource none = {};
     auto go = [&](auto dk_c, auto tm_c, auto gates_c) {
         constexpr int kDk = decltype(dk_c)::value;
         constexpr bool kTm = decltype(tm_c)::value, kGates = decltype(gates_c)::value;
-        if (per_tile) {
-            hipLaunchKernelGGL((bigla_tile_kernel<kDk, kTm, kGates>), dim3((unsigned)BH), dim3(unsigned(64 * n_tiles)), tile_lds_bytes<kDk>(n_tiles), stream,
+        auto tile_launch = [&](auto halves_c) {
+            constexpr bool kHalves = decltype(halves_c)::value;
+            const unsigned lds = tile_lds_bytes<kDk, kHalves>(n_tiles);
+            hipLaunchKernelGGL((bigla_tile_kernel<kDk, kTm, kGates, kHalves>), dim3((unsigned)BH), dim3(unsigned(64 * n_tiles)), lds, stream,
                                static_cast<const uint16_t *>(q), static_cast<const uint16_t *>(k), static_cast<const uint16_t *>(v),
                                static_cast<const uint16_t *>(g_fwd), static_cast<const uint16_t *>(g_bwd), static_cast<uint16_t *>(out),
                                static_cast<float *>(workspace), L, n_tiles, heads_token_major > 0 ? heads_token_major : 1, gates ? *gates : none);
+        };
+        if (per_tile) {
+            if (tile_halves(n_tiles)) tile_launch(std::true_type{}); else tile_launch(std::false_type{});
             return;
         }
         const unsigned lds = unsigned(slots) * (ShortSlab<kDk>::bytes(n_tiles) + unsigned(sizeof(int)));

@@ -7,8 +7,13 @@
 // registers.  Three barriers.
 //
 // A slab in which some 64-token stretch decays by more than kMildRange has the operands of the diagonal tiles split into bf16 pairs,
-// as in the eight-wave kernels; where half the sequence decays by more than kFastRange the slab takes the range-safe form
-// (short_slab_safe), a tile a wave.
+// as in the eight-wave kernels.  All exponents are referred to one point in the middle of the sequence as long as neither half decays
+// by more than kFastRange.  Up to 128 tokens a slab beyond that takes the range-safe form (short_slab_safe), a tile a wave; there
+// that is the limit of the eight-wave kernels, 60 nats in 64 tokens.  From 129 tokens on (kHalves) each half is then referred to
+// its own middle, with a second set of scaled queries for the keys of the other half, and the range-safe form is left to
+// slabs with a quarter beyond kFastRange.  At -0.8 a step, 64-wide keys, one point and the range-safe form / two points / the eight-wave
+// kernels: 6 slabs of 144 tokens 19.3 / 11.2 / 11.2 us, of 192 22.5 / 12.3 / 11.1, 127 slabs of 192 26.2 / 12.8 / 16.9; at -0.3 one point holds
+// and two would take 0.6 us more.
 //
 // Per call in a captured graph, us, 64-wide keys, mild gates and -0.3 a step (the kernels before it: up to 64 tokens and from 128 slabs on
 // bigla_short_kernel, else the eight-wave kernels): 6 slabs of 65 tokens 6.7 / 7.4 (11.7 / 12.0), 48 of 100 7.5 / 8.3 (12.2 / 12.5), 48
@@ -23,14 +28,18 @@ namespace vig {
 
 namespace {
 
-template <int kDk>
+constexpr int kTileMost = 12;  // tiles of the longest sequence (192 tokens)
+constexpr int kTileWhole = 8;  // up to so many, halves of at most 64 tokens: one reference point
+inline bool tile_halves(int n_tiles) { return n_tiles > kTileWhole; }
+
+template <int kDk, bool kHalves>
 constexpr unsigned tile_lds_bytes(int n_tiles)
 {
-    return ShortSlab<kDk>::bytes(n_tiles) + 4 * unsigned(sizeof(int)) + unsigned(n_tiles) * 4 * kDk * unsigned(sizeof(float));
+    return ShortSlab<kDk>::bytes(n_tiles) + 4 * unsigned(sizeof(int)) + unsigned(n_tiles) * (kHalves ? 5 : 4) * kDk * unsigned(sizeof(float));
 }
 
-template <int kDk, bool kTm, bool kGates>
-__global__ __launch_bounds__(64 * kShortTiles, 4) void bigla_tile_kernel(
+template <int kDk, bool kTm, bool kGates, bool kHalves /* 9 to 12 tiles */>
+__global__ __launch_bounds__(64 * (kHalves ? kTileMost : kTileWhole), kHalves ? 3 : 4) void bigla_tile_kernel(
     const uint16_t *__restrict__ q_all, const uint16_t *__restrict__ k_all, const uint16_t *__restrict__ v_all,
     const uint16_t *gf_all, const uint16_t *gb_all, uint16_t *__restrict__ out_all, float *__restrict__ eb_all, int L,
     int n_tiles, int heads, GateSource gs)
@@ -44,12 +53,12 @@ __global__ __launch_bounds__(64 * kShortTiles, 4) void bigla_tile_kernel(
     const long slab = blockIdx.x;
     const SlabIo<kTm, kDk> io(q_all, k_all, v_all, gf_all, gb_all, out_all, slab, L, heads);
     const ShortSlab<kDk> at(0, n_tiles);
-    // strong: some 64-token stretch beyond kMildRange; far: half the sequence beyond kFastRange
-    int *strong = reinterpret_cast<int *>(g_short_lds + ShortSlab<kDk>::bytes(n_tiles)), *far = strong + 1;
+    // strong: some 64-token stretch beyond kMildRange; far: half the sequence beyond kFastRange; beyond: a quarter of it
+    int *strong = reinterpret_cast<int *>(g_short_lds + ShortSlab<kDk>::bytes(n_tiles)), *far = strong + 1, *beyond = kHalves ? strong + 2 : far;
     float *tot = reinterpret_cast<float *>(strong + 4);  // totals [direction][tile][channel], then what enters each tile, likewise
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
     const unsigned own_keys = unsigned(w) * kKeyTile;
-    if (w == 0 && lane == 0) *strong = *far = 0;
+    if (w == 0 && lane == 0) *strong = *far = *beyond = 0;
 
     // ---- rows of the tile; its gates into its rows of the key tiles
     Row16 rq, rk;
@@ -151,21 +160,24 @@ __global__ __launch_bounds__(64 * kShortTiles, 4) void bigla_tile_kernel(
     __syncthreads();  // totals visible
 
     // ---- what enters the tile's scans, referred to the first token of tile `mid`; lane = channel
-    const int mid = n_tiles >> 1;
-    float *own_offs = tot + (2 * n_tiles + 2 * w) * kDk;
-    {
-        const int c = lane & (kDk - 1);
-        auto sum = [&](int dir, int first, int last) __attribute__((always_inline)) {  // of the totals of tiles first .. last - 1, eight at most
-            float s = 0.f;
+    const int mid = kHalves ? (n_tiles + 2) / 4 * 2 : n_tiles >> 1;  // (halves of whole pairs of tiles)
+    const bool low = w < mid;
+    float *own_offs = tot + (2 * n_tiles + (kHalves ? 3 : 2) * w) * kDk;
+    const int c = lane & (kDk - 1);
+    auto sum = [&](auto most, int dir, int first, int last) __attribute__((always_inline)) {  // of the totals of tiles first .. last - 1
+        float s = 0.f;
 #pragma unroll
-            for (int i = 0; i < kShortTiles / 2; ++i) {
-                const float t = tot[(dir * n_tiles + min(first + i, n_tiles - 1)) * kDk + c];
-                s += __int_as_float(__float_as_int(t) & (first + i < last ? -1 : 0));
-            }
-            return s;
-        };
-        const bool low = w < mid;
-        const float of = sum(0, low ? w : mid, low ? mid : w), ob = sum(1, low ? w + 1 : mid, low ? mid : w + 1);
+        for (int i = 0; i < decltype(most)::value; ++i) {
+            const float t = tot[(dir * n_tiles + min(first + i, n_tiles - 1)) * kDk + c];
+            s += __int_as_float(__float_as_int(t) & (first + i < last ? -1 : 0));
+        }
+        return s;
+    };
+    const std::integral_constant<int, (kHalves ? kTileMost : kTileWhole) / 2> half;
+    const std::integral_constant<int, kTileMost / 4> quarter;
+    const int ref[2] = {mid / 2, (mid + n_tiles) / 2};  // kHalves: the halves' own reference points, likewise
+    {
+        const float of = sum(half, 0, low ? w : mid, low ? mid : w), ob = sum(half, 1, low ? w + 1 : mid, low ? mid : w + 1);
         const float xf = low ? -of : of, xb = low ? ob : -ob;
         own_offs[c] = xf * kLog2e;
         own_offs[kDk + c] = xb * kLog2e;
@@ -179,9 +191,18 @@ __global__ __launch_bounds__(64 * kShortTiles, 4) void bigla_tile_kernel(
             const float range = kMildRange / kC * float(min(L, kC));
             if (!(s[0] >= -range && s[1] >= -range)) *strong = 1;
         }
-        // exponents reach furthest at the two ends
-        if (w == 0 && !(xf <= kFastRange && xb + tot[n_tiles * kDk + c] >= -kFastRange)) *far = 1;
-        if (w == n_tiles - 1 && !(xb <= kFastRange && xf + tot[w * kDk + c] >= -kFastRange)) *far = 1;
+        // exponents reach furthest at the two ends; with a reference point to each half, at the ends of the quarters
+        auto is_far = [&](bool upper) __attribute__((always_inline)) {
+            *far = 1;
+            if constexpr (kHalves) {
+                const int first = upper ? mid : 0, own = ref[upper], last = upper ? n_tiles : mid;
+                const bool near = sum(quarter, 0, first, own) >= -kFastRange && sum(quarter, 0, own, last) >= -kFastRange &&
+                                  sum(quarter, 1, first, own) >= -kFastRange && sum(quarter, 1, own, last) >= -kFastRange;
+                if (!near) *beyond = 1;
+            }
+        };
+        if (w == 0 && !(xf <= kFastRange && xb + tot[n_tiles * kDk + c] >= -kFastRange)) is_far(false);
+        if (w == n_tiles - 1 && !(xb <= kFastRange && xf + tot[w * kDk + c] >= -kFastRange)) is_far(true);
         wave_lds_fence();
     }
     // exponents (of 2) of the lane's token
@@ -195,11 +216,13 @@ __global__ __launch_bounds__(64 * kShortTiles, 4) void bigla_tile_kernel(
         }
     __syncthreads();  // the slab's flags are visible
     const bool split = __builtin_amdgcn_readfirstlane(*strong) != 0;
-    int safe = __builtin_amdgcn_readfirstlane(*strong & *far);
+    const bool apart = kHalves && split && __builtin_amdgcn_readfirstlane(*far) != 0;  // each half has a reference point of its own
+    int safe = __builtin_amdgcn_readfirstlane(*strong & *beyond);
     if (safe == 0) {
         // ---- scaled queries (kept; they carry the 1/2 of the average) and keys (into the rows the gates were in), and the own
         // diagonal tile of the scores
         bf16x8 qx[2][kKs];
+        bf16x8 qc[kHalves ? kKs : 1] = {};  // the queries for the other half's keys, referred to that half's point
         f32x4 diag[2] = {zero, zero};
         auto scale = [&](auto split_c) __attribute__((always_inline)) {
             constexpr bool kSplit = decltype(split_c)::value;
@@ -207,6 +230,34 @@ __global__ __launch_bounds__(64 * kShortTiles, 4) void bigla_tile_kernel(
             if constexpr (kSplit) {
 #pragma unroll
                 for (int ct = 0; ct < kCt; ++ct) asm volatile("" : "+v"(B[0][ct]), "+v"(B[1][ct]));
+            }
+            if constexpr (kSplit && kHalves) {
+                if (apart) {
+                    // from the middle to the own half's reference point, and for the queries that meet the other half's keys to
+                    // that half's (those are the backward direction's in the lower half, the forward one's in the upper)
+                    const int h0 = low ? ref[0] : mid, h1 = low ? mid : ref[1], o0 = low ? mid : ref[0], o1 = low ? ref[1] : mid;
+                    const float sf = sum(quarter, 0, h0, h1), sb = sum(quarter, 1, h0, h1), so = sum(quarter, low ? 1 : 0, o0, o1);
+                    own_offs[c] = (low ? sf : -sf) * kLog2e;
+                    own_offs[kDk + c] = (low ? -sb : sb) * kLog2e;
+                    own_offs[2 * kDk + c] = so * kLog2e;
+                    wave_lds_fence();
+#pragma unroll
+                    for (int kk = 0; kk < kKs; ++kk) {
+                        float qv[8];
+                        unpack8(rq.p[kk], qv);
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            const int ct = 2 * kk + h;
+                            const float *off = &own_offs[32 * kk + 8 * g + 4 * h];
+                            const f32x4 x = (low ? B[1][ct] : B[0][ct]) + *reinterpret_cast<const f32x4 *>(off + 2 * kDk);
+                            B[0][ct] += *reinterpret_cast<const f32x4 *>(off);
+                            B[1][ct] += *reinterpret_cast<const f32x4 *>(off + kDk);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) qv[4 * h + e] *= fast_exp2(x[e] - 1.f);
+                        }
+                        qc[kk] = pack8(qv);
+                    }
+                }
             }
 #pragma unroll
             for (int kk = 0; kk < kKs; ++kk) {
@@ -260,9 +311,9 @@ __global__ __launch_bounds__(64 * kShortTiles, 4) void bigla_tile_kernel(
             for (int kk = 0; kk < kKs; ++kk) k.a[kk] = short_b128((region + unsigned(tile) * kKeyTile + koff) ^ (64u * unsigned(kk)));
             return k;
         };
-        auto scores = [&](const Keys &k, int dir) __attribute__((always_inline)) {
-            f32x4 p = mfma(k.a[0], qx[dir][0], zero);
-            if (kKs > 1) p = mfma(k.a[kKs - 1], qx[dir][kKs - 1], p);
+        auto scores = [&](const Keys &k, const bf16x8 *q) __attribute__((always_inline)) {
+            f32x4 p = mfma(k.a[0], q[0], zero);
+            if (kKs > 1) p = mfma(k.a[kKs - 1], q[kKs - 1], p);
             return p;
         };
         auto add_pair = [&](int t0, int t1, const f32x4 &p0, const f32x4 &p1) __attribute__((always_inline)) {
@@ -280,31 +331,41 @@ __global__ __launch_bounds__(64 * kShortTiles, 4) void bigla_tile_kernel(
         const int own_pair = w >> 1, pairs = (n_tiles + 1) >> 1, sibling = min(w ^ 1, n_tiles - 1);
         const bool odd = (w & 1) != 0;
         Keys k0 = key_rows(at.kf, 0), k1 = key_rows(at.kf, min(1, n_tiles - 1));
-        for (int p = 0; p < own_pair; ++p) {
-            const f32x4 p0 = scores(k0, 0), p1 = scores(k1, 0);
-            k0 = key_rows(at.kf, 2 * p + 2);
-            k1 = key_rows(at.kf, min(2 * p + 3, n_tiles - 1));
-            add_pair(2 * p, 2 * p + 1, p0, p1);
-        }
+        auto forward = [&](int first, int last, const bf16x8 *q) __attribute__((always_inline)) {
+            for (int p = first; p < last; ++p) {
+                const f32x4 p0 = scores(k0, q), p1 = scores(k1, q);
+                k0 = key_rows(at.kf, 2 * p + 2);
+                k1 = key_rows(at.kf, min(2 * p + 3, n_tiles - 1));
+                add_pair(2 * p, 2 * p + 1, p0, p1);
+            }
+        };
+        auto backward = [&](int first, int last, const bf16x8 *q) __attribute__((always_inline)) {
+            for (int p = first; p < last; ++p) {
+                const f32x4 p0 = scores(k0, q);
+                f32x4 p1 = scores(k1, q);
+                const int second = min(2 * p + 1, n_tiles - 1);
+                if (second == 2 * p) p1 = zero;
+                k0 = key_rows(at.kb, min(2 * p + 2, n_tiles - 1));
+                k1 = key_rows(at.kb, min(2 * p + 3, n_tiles - 1));
+                add_pair(2 * p, second, p0, p1);
+            }
+        };
+        // (apart: the pairs of the other half, before the upper one and after the lower one)
+        const int other_before = apart && !low ? mid >> 1 : 0, own_last = apart && low ? mid >> 1 : pairs;
+        if constexpr (kHalves) forward(0, other_before, qc);
+        forward(other_before, own_pair, qx[0]);
         {
             // the own tile, and beside it the one before it (forward) or after it (backward; there may be none)
             const Keys c = key_rows(at.kb, sibling);
             const int next = 2 * min(own_pair + 1, pairs - 1);
-            f32x4 other = odd ? scores(k0, 0) : scores(c, 1);
+            f32x4 other = odd ? scores(k0, qx[0]) : scores(c, qx[1]);
             if (sibling == w) other = zero;
             k0 = key_rows(at.kb, next);
             k1 = key_rows(at.kb, min(next + 1, n_tiles - 1));
             add_pair(w, sibling, own, other);
         }
-        for (int p = own_pair + 1; p < pairs; ++p) {
-            const f32x4 p0 = scores(k0, 1);
-            f32x4 p1 = scores(k1, 1);
-            const int second = min(2 * p + 1, n_tiles - 1);
-            if (second == 2 * p) p1 = zero;
-            k0 = key_rows(at.kb, min(2 * p + 2, n_tiles - 1));
-            k1 = key_rows(at.kb, min(2 * p + 3, n_tiles - 1));
-            add_pair(2 * p, second, p0, p1);
-        }
+        backward(own_pair + 1, own_last, qx[1]);
+        if constexpr (kHalves) backward(own_last, pairs, qc);
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
             const uint2 a = pack4(O[2 * kk]), b = pack4(O[2 * kk + 1]);

@@ -1233,6 +1233,62 @@ def test_bigla_wave_per_tile(L, layout, dk):
     _check_one_chunk(wl.Workload("tiles", B=5, H=2, Hg=1, Wg=L, dk=dk, dv=64, dtype="bf16", gate_mu=-1.0), layout)
 
 
+@pytest.mark.parametrize("layout,dk", (("bhld", 64), ("blhd", 32)))
+@pytest.mark.parametrize("L,rate", ((129, 0.9), (144, 0.85), (145, 0.8), (161, 0.75), (177, 0.7), (192, 0.65), (192, 0.92)))
+def test_bigla_wave_per_tile_fast_gates(L, rate, layout, dk):
+    """129 to 192 tokens whose halves decay by more than 60 nats and their 64-token chunks by less: 126 slabs, both directions,
+    either one alone, and every eighth channel alone, within half the element bound (the diagonal tiles are split)."""
+    import oracle
+    import torch
+    from paper_2405_18425_amd import binding as vb
+
+    _say(f"wave per tile, fast gates L{L} {rate} {layout} dk{dk}")
+    g = torch.Generator().manual_seed(L + dk)
+    q, k, v = (torch.randn(42, 3, L, d, generator=g).bfloat16() for d in (dk, dk, 64))
+    gf, gb = (-rate * (0.98 + 0.04 * torch.rand(42, 3, L, dk, generator=g)) for _ in range(2))
+    gf[10:20] *= 0.3
+    gb[20:30] *= 0.3
+    for a in (gf, gb):
+        a[30:, :, :, torch.arange(dk) % 8 != 3] *= 0.5
+    t = [q, k, v, gf.bfloat16(), gb.bfloat16()]
+    d = [(a if layout == "bhld" else a.transpose(1, 2).contiguous()).cuda() for a in t]
+    out = vb.bigla_fwd(*d, layout=layout)
+    torch.cuda.synchronize()
+    if layout == "blhd":
+        out = out.transpose(1, 2)
+    assert_close(out.double().cpu().numpy(), oracle.bigla(*(a.double().numpy() for a in t)), 0.5 * TOL["bf16"], f"L{L} {rate}")
+
+
+@pytest.mark.parametrize("mirrored", (False, True))
+@pytest.mark.parametrize("layout,dk", (("bhld", 64), ("blhd", 32)))
+def test_bigla_wave_per_tile_keeps_the_fast_form(layout, dk, mirrored):
+    """192 tokens with resets of 15 nats, five to a half of the sequence and three to a 64-token chunk: within the range of
+    the fast form, which carries them as they are; the range-safe form would let 1e4 times e^-8 of the first token past the
+    first one.  Mirrored: the backward direction, and the last token."""
+    import torch
+    from paper_2405_18425_amd import binding as vb
+
+    L = 192
+    w = wl.Workload("resets", B=1, H=3, Hg=1, Wg=L, dk=dk, dv=64, dtype="bf16", gate_mu=0.0)
+    _say(f"wave per tile, resets {layout} dk{dk} mirrored={mirrored}")
+    s = wl.generate(w, seed=5, tensors=("q", "k", "v", "g_fwd", "g_bwd"))
+    g = {n: np.full_like(wl.widen(s[n], "bf16"), -0.2) for n in ("g_fwd", "g_bwd")}
+    k = wl.widen(s["k"], "bf16")
+    order = slice(None, None, -1) if mirrored else slice(None)
+    resets = [t + 20 * i for t in (10, 74, 138) for i in range(3)]
+    g["g_bwd" if mirrored else "g_fwd"][:, :, order][:, :, resets] = -15.0
+    k[:, :, order][:, :, 0] *= 1e4
+    s.update({n: wl.store(a, "bf16") for n, a in {**g, "k": k}.items()})
+    t = {n: wl.to_torch(a, "bf16", "cuda:0") for n, a in s.items()}
+    if layout == "blhd":
+        t = {n: a.transpose(1, 2).contiguous() for n, a in t.items()}
+    out = vb.bigla_fwd(t["q"], t["k"], t["v"], t["g_fwd"], t["g_bwd"], layout=layout)
+    torch.cuda.synchronize()
+    out = wl.widen(wl.from_torch((out.transpose(1, 2) if layout == "blhd" else out).contiguous(), "bf16"), "bf16")
+    # the rows past the first reset, against the scale of their own values
+    assert_close(out[:, :, order][:, :, 10:], run_bigla_oracle(s, "bf16")[:, :, order][:, :, 10:], TOL["bf16"], "past the reset")
+
+
 @pytest.mark.parametrize("layout,dk", (("bhld", 64), ("blhd", 64), ("blhd", 32)))
 @pytest.mark.parametrize("L", (257, 320, 390))
 def test_bigla_workgroup_per_slab(L, layout, dk):
