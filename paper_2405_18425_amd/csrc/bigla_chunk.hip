@@ -1242,12 +1242,15 @@ hipError_t bigla_chunk_set_alias(int on)
 // eight-wave kernels, one workgroup a compute unit, take a second round of it.  us per call, eight-wave kernels / workgroup per slab,
 // mild gates and -0.3 a step: 257 slabs of 300 tokens 48.5 / 36.0 and 51.5 / 39.0, 270 of 363 57.0 / 43.4, 300 of 600 89.8 / 70.6 and 94.8 /
 // 76.4, 512 of 300 57.9 / 41.5, 513 of 300 74.8 / 59.5, 1024 of 300 112.6 / 84.4, 400 of 300 with 32-wide keys 42.3 / 29.4; 232 of 405
-// 35.3 / 36.3, 144 of 460 36.9 / 40.1.
-static bool bigla_chunk_slab_preferred(long BH) { return BH > 256; }
+// 35.3 / 36.3, 144 of 460 36.9 / 40.1.  Long sequences: 260 of 4096 525 / 424, 384 of 6400 885 / 790, 512 of 4096 658 / 626, 1024 of 4096
+// 1282 / 1278.  Between 513 and 768 slabs, two rounds of the slab kernel against three of the eight-wave kernels, the gain shrinks with the
+// length and is gone at 3072 tokens: 600 slabs of 1024 226 / 209, of 2048 444 / 443, of 3136 678 / 700, of 4096 888 / 919, of 6400 1391 /
+// 1465, 700 of 6400 with 32-wide keys 998 / 1028.
+static bool bigla_chunk_slab_preferred(long BH, int L) { return BH > 256 && !(BH > 512 && BH <= 768 && L > 48 * kC); }
 
 // The gates made by the state pass need the eight-wave kernels: 258 slabs of 300 tokens 61 us against 50 with the gates first, 300
-// of 600 112 / 92, 1020 of 300 136 / 118.
-bool bigla_chunk_gates_apart(long BH, int L) { return !bigla_short_applicable(BH, L) && bigla_chunk_slab_preferred(BH); }
+// of 600 112 / 92, 1020 of 300 136 / 118, 384 of 4096 763 / 660; 700 of 3136 942 / 950, of 6400 1866 / 1933.
+bool bigla_chunk_gates_apart(long BH, int L) { return !bigla_short_applicable(BH, L) && bigla_chunk_slab_preferred(BH, L); }
 
 bool bigla_chunk_gated_selectable(long BH, int L, int dk)
 {
@@ -1293,7 +1296,7 @@ hipError_t bigla_chunk_launch(const void *q, const void *k, const void *v, const
         return bigla_short_launch(q, k, v, g_fwd, g_bwd, out, BH, L, dk, heads_token_major, workspace, stream);
     const bool ws_ok = bigla_chunk_ws_applicable(BH, L, dk) && (!fusion || (fusion->Wg < kXHalo && L < (1 << 22)));
     if (kernels == 2 && !ws_ok) return hipErrorInvalidValue;
-    if (kernels == 2 || (kernels == 0 && ws_ok && (fusion || !bigla_chunk_slab_preferred(BH)))) {
+    if (kernels == 2 || (kernels == 0 && ws_ok && (fusion || !bigla_chunk_slab_preferred(BH, L)))) {
         return bigla_chunk_ws_launch(q, k, v, g_fwd, g_bwd, out, BH, L, dk, heads_token_major, workspace, stream,
                                      nullptr, fusion);
     }

@@ -1310,6 +1310,36 @@ def test_bigla_workgroup_per_slab(L, layout, dk):
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("slabs,L,one_launch", ((512, 3136, True), (516, 3072, True), (516, 3073, False), (768, 3136, False), (772, 3136, True)))
+def test_bigla_many_long_slabs(slabs, L, one_launch):
+    """More slabs than compute units: one launch or the eight-wave kernels, either side of the lines between them, bit for bit what
+    the plan asked for by name gives; the gates in a launch of their own, or in the state pass, accordingly."""
+    import torch
+    from paper_2405_18425_amd import binding as vb
+
+    B, H, D, dk = slabs // 4, 4, 64, 32
+    _say(f"many long slabs {slabs} x {L}")
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    q, k = (torch.randn(B, H, L, dk, device="cuda", generator=gen).bfloat16() for _ in range(2))
+    v = torch.randn(B, H, L, 64, device="cuda", generator=gen).bfloat16()
+    x = torch.randn(B, L, D, device="cuda", generator=gen).bfloat16()
+    w1, w2 = ((torch.randn(n, m, device="cuda", generator=gen) / m ** 0.5).bfloat16() for n, m in ((16, D), (2 * H * dk, 16)))
+    names = ("segment_state", "slab", "gate_producer", "gate_lowrank")
+    vb.timing_enable(True)
+    try:
+        out, gf, gb = vb.gated_bigla_fwd(x, w1, w2, q, k, v)
+        gated = [vb.timing_collect(n)[1] for n in names]
+        vb.timing_enable(True)
+        plain = vb.bigla_fwd(q, k, v, gf, gb)
+        fwd = [vb.timing_collect(n)[1] for n in names]
+    finally:
+        vb.timing_enable(False)
+    assert gated == ([0, 1, 1, 0] if one_launch else [1, 0, 0, 1]), gated
+    assert fwd == ([0, 1, 0, 0] if one_launch else [1, 0, 0, 0]), fwd
+    want = vb.bigla_fwd(q, k, v, gf, gb, plan="slab_sweep" if one_launch else "wave_specialised")
+    assert torch.equal(plain, want) and torch.equal(out, want)
+
+
 @pytest.mark.parametrize("L,dk,slabs", ((65, 64, 770), (96, 64, 770), (97, 64, 770), (65, 32, 390), (100, 32, 390), (128, 32, 390)))
 def test_bigla_two_tiles_per_wave(L, dk, slabs):
     """Either side of the line from which on two tiles go to a wave and two slabs to a workgroup, for 65 to 128 tokens."""
