@@ -103,22 +103,23 @@ def test_bigla_ragged_lengths(dtype, dk, dv):
     (3, 3, 700, 64, "bhld"),     # 9 slabs: the plain (slab, segment) order
     (16, 1, 330, 32, "bhld"),    # 16 slabs, 32-wide keys (only two waves own state rows)
     (1, 1, 4096, 64, "bhld"),    # a single slab cut into 64 segments
-    (5, 8, 130, 64, "blhd"),     # 40 slabs, three chunks in two or three segments
+    (5, 8, 130, 64, "blhd"),     # 40 slabs, three chunks in two or three segments (by name: one launch takes them as one chunk)
 ])
 def test_bigla_segment_plans(B, H, L, dk, layout):
     """Plans with several segments per slab: the output pass folds the other segments' end states
     itself, and the workgroup -> (slab, segment) assignment depends on the slab count."""
+    plan = "auto" if L > 192 else "wave_specialised"
     w = wl.Workload("plan", B=B, H=H, Hg=1, Wg=L, dk=dk, dv=64, dtype="bf16", gate_mu=1.0)
     _say(f"bigla plan {w} {layout}")
     s = wl.generate(w, seed=B * 100 + H, tensors=("q", "k", "v", "g_fwd", "g_bwd"))
     ref = run_bigla_oracle(s, "bf16")
     if layout == "bhld":
-        got = run_bigla_gpu(s, "bf16")
+        got = run_bigla_gpu(s, "bf16", plan=plan)
     else:
         import torch
         from paper_2405_18425_amd import binding as vb
         t = {n: wl.to_torch(s[n], "bf16", "cuda:0").transpose(1, 2).contiguous() for n in s}
-        out = vb.bigla_fwd(t["q"], t["k"], t["v"], t["g_fwd"], t["g_bwd"], layout="blhd")
+        out = vb.bigla_fwd(t["q"], t["k"], t["v"], t["g_fwd"], t["g_bwd"], layout="blhd", plan=plan)
         torch.cuda.synchronize()
         got = wl.widen(wl.from_torch(out.transpose(1, 2).contiguous(), "bf16"), "bf16")
     assert_close(got, ref, TOL["bf16"], "segment plan")
@@ -330,6 +331,17 @@ def test_bigla_fwd_plans(plan, B, H, L, dk, mu):
 def test_bigla_fwd_plans_short_sequences(plan, layout, dk, B, H, L):
     """The four-wave kernels on one to four chunks, few slabs and many (one workgroup per slab), which bigla_fwd takes as one
     chunk or with the eight-wave kernels: reached by name only.  One slab of fast decay and one with a stretch of it."""
+    _check_fwd_plan_short(plan, layout, dk, B, H, L)
+
+
+@pytest.mark.parametrize("layout,dk", (("bhld", 64), ("blhd", 64), ("blhd", 32)))
+@pytest.mark.parametrize("L", (65, 128, 129, 130, 192, 193, 250))
+def test_bigla_fwd_eight_wave_short_sequences(layout, dk, L):
+    """The eight-wave kernels on two to four chunks of few slabs; up to 192 tokens reached by name only."""
+    _check_fwd_plan_short("wave_specialised", layout, dk, 2, 3, L)
+
+
+def _check_fwd_plan_short(plan, layout, dk, B, H, L):
     import torch
     from paper_2405_18425_amd import binding as vb
 
@@ -499,8 +511,10 @@ def test_path_end_to_end_hierarchical_stage_shapes(grid, H):
     (1, 3, 20, 13, 32, "blhd", -40.0, True),    # strong decay: range-safe form
     (1, 2, 5, 100, 64, "bhld", 0.0, True),      # grid rows longer than a chunk
     (1, 2, 100, 3, 64, "bhld", 0.0, True),      # many grid rows per chunk
-    (1, 1, 1, 70, 64, "bhld", 0.0, True),       # degenerate grids: a single row, a single column
+    (1, 1, 1, 70, 64, "bhld", 0.0, True),       # degenerate grids: a single row, a single column (taken as one chunk)
     (1, 1, 70, 1, 64, "bhld", 0.0, True),
+    (1, 1, 1, 300, 64, "bhld", 0.0, True),      # the same in the epilogues: the four-wave one for the row, the eight-wave
+    (1, 1, 300, 1, 64, "bhld", 0.0, True),      # one for the column
     (2, 6, 64, 64, 64, "bhld", -2.0, True),     # the benchmark grid: the widest the eight-wave epilogue takes
     (3, 2, 64, 64, 64, "blhd", 0.0, False),
     (2, 2, 30, 47, 64, "bhld", 1.0, True),      # grid rows that straddle chunks, ragged final chunk
@@ -543,10 +557,10 @@ def test_bigla_locality_plans(B, H, Hg, Wg, dk, layout, mu, with_bias):
     for plan in ("two_launches", "auto"):
         o = outs[plan]
         assert torch.equal(o, separate), f"{plan}: {(o != separate).sum().item()} elements differ from the separate calls"
-    # up to 64 tokens, and up to 256 in at least 128 slabs, bigla_fwd takes the sequence as one chunk and the
+    # up to 192 tokens, and up to 256 in at least 128 slabs, bigla_fwd takes the sequence as one chunk and the
     # fused plan does too, with the locality kernel after it; elsewhere bigla_fwd runs the eight-wave kernels
     # and the plan those or, for wide grids, the four-wave ones (the eight-wave epilogue sums the taps in pairs)
-    one_chunk = Hg * Wg <= 64 or (B * H >= 128 and Hg * Wg <= 256)
+    one_chunk = Hg * Wg <= 192 or (B * H >= 128 and Hg * Wg <= 256)
     o = outs["fused_epilogue"]
     if one_chunk:
         assert torch.equal(o, separate), f"fused: {(o != separate).sum().item()} elements differ from the separate calls"
@@ -1220,8 +1234,7 @@ def test_bigla_one_chunk_sequences(L, layout, dk):
 @pytest.mark.parametrize("layout,dk", (("bhld", 64), ("blhd", 64), ("bhld", 32)))
 @pytest.mark.parametrize("L", (32, 33, 48, 49, 64))
 def test_bigla_one_chunk_many_short_sequences(L, layout, dk):
-    """The same beyond 1024 slabs, where up to 64 tokens share a workgroup with other slabs and a wave takes two tiles
-    in the range-safe form; 1030 slabs, the last workgroup not full."""
+    """The same in 1030 slabs, more workgroups of one to four waves than the chip holds at once."""
     _check_one_chunk(wl.Workload("one_chunk_many", B=5, H=206, Hg=1, Wg=L, dk=dk, dv=64, dtype="bf16", gate_mu=-1.0), layout)
 
 
@@ -1293,7 +1306,8 @@ def test_bigla_wave_per_tile_keeps_the_fast_form(layout, dk, mirrored):
 @pytest.mark.parametrize("L", (257, 320, 390))
 def test_bigla_workgroup_per_slab(L, layout, dk):
     """More slabs than compute units, longer than one chunk: a four-wave workgroup per slab, with mild gates, beyond the limit of bf16
-    operands in the fast form, and beyond that form, in one call; the gated call makes the gates first."""
+    operands in the fast form, and beyond that form, in one call; the gated call makes the gates first: the same gates as in the
+    state pass of the eight-wave kernels, and the same output up to operand rounding."""
     import torch
     from paper_2405_18425_amd import binding as vb
 
@@ -1305,9 +1319,10 @@ def test_bigla_workgroup_per_slab(L, layout, dk):
     gen = torch.Generator(device="cuda").manual_seed(L)
     shape = (5, H, L) if layout == "bhld" else (5, L, H)
     q, k, v = (torch.randn(*shape, d, device="cuda", generator=gen).bfloat16() for d in (dk, dk, 64))
-    call = lambda plan: vb.gated_bigla_fwd(t["x"], w1, w2, q, k, v, bias=t["bias"], layout=layout, plan=plan)
-    for a, b in zip(call("auto"), call("separate")):
-        assert torch.equal(a, b)
+    got, want = (vb.gated_bigla_fwd(t["x"], w1, w2, q, k, v, bias=t["bias"], layout=layout, plan=plan) for plan in ("auto", "in_state_pass"))
+    assert torch.equal(got[1], want[1]) and torch.equal(got[2], want[2])
+    out, ref = ((a[0] if layout == "bhld" else a[0].transpose(1, 2)).double().cpu().numpy() for a in (got, want))
+    assert_close(out, ref, TOL["bf16"], f"gated L{L}")
 
 
 @pytest.mark.parametrize("slabs,L,one_launch", ((512, 3136, True), (516, 3072, True), (516, 3073, False), (768, 3136, False), (772, 3136, True)))
@@ -1340,11 +1355,14 @@ def test_bigla_many_long_slabs(slabs, L, one_launch):
     assert torch.equal(plain, want) and torch.equal(out, want)
 
 
-@pytest.mark.parametrize("L,dk,slabs", ((65, 64, 770), (96, 64, 770), (97, 64, 770), (65, 32, 390), (100, 32, 390), (128, 32, 390)))
-def test_bigla_two_tiles_per_wave(L, dk, slabs):
-    """Either side of the line from which on two tiles go to a wave and two slabs to a workgroup, for 65 to 128 tokens."""
-    for n in (slabs - 5, slabs):
-        _check_one_chunk(wl.Workload("two_tiles", B=5, H=n // 5, Hg=1, Wg=L, dk=dk, dv=64, dtype="bf16", gate_mu=-1.0), "bhld")
+@pytest.mark.parametrize("layout", ("bhld", "blhd"))
+@pytest.mark.parametrize("L,dk,slabs", ((65, 64, (765, 775)), (96, 64, (765, 775)), (97, 64, (775,)), (65, 32, (380, 385)),
+                                        (100, 32, (380, 385)), (128, 32, (380, 385)), (129, 64, (125, 130))))
+def test_bigla_two_tiles_per_wave(L, dk, slabs, layout):
+    """Either side of the lines from which on two tiles go to a wave (and up to 128 tokens two slabs to a workgroup, here with one left
+    over): more than 768 slabs of 65 to 96 tokens, 384 of 65 to 128 with 32-wide keys, 127 of more than 128."""
+    for n in slabs:
+        _check_one_chunk(wl.Workload("two_tiles", B=5, H=n // 5, Hg=1, Wg=L, dk=dk, dv=64, dtype="bf16", gate_mu=-1.0), layout)
 
 
 @pytest.mark.parametrize("slabs", (1024, 2560))
@@ -1399,8 +1417,16 @@ def test_gated_bigla_one_chunk_sequences(L, layout, dk, bias_mu):
 @pytest.mark.parametrize("layout,dk,bias_mu", (("bhld", 64, 0.0), ("blhd", 64, -40.0), ("blhd", 32, -40.0)))
 @pytest.mark.parametrize("L,B", ((33, 3), (64, 3), (33, 343), (64, 343)))
 def test_gated_bigla_one_chunk_short_sequences(L, B, layout, dk, bias_mu):
-    """The same with a workgroup per slab and, beyond 1024 slabs, with several; in the range-safe form a wave reads gates
-    that another wave of its workgroup has made."""
+    """The same for up to 64 tokens, few slabs and 1029: a wave per tile, in the fast form and the range-safe one."""
+    _check_gated_one_chunk(L, B, layout, dk, bias_mu)
+
+
+@pytest.mark.parametrize("layout,dk,bias_mu", (("bhld", 64, 0.0), ("blhd", 64, -11.0), ("blhd", 32, -11.0), ("bhld", 64, -40.0)))
+@pytest.mark.parametrize("L,B", ((65, 3), (100, 3), (128, 3), (129, 3), (192, 3), (80, 259)))
+def test_gated_bigla_wave_per_tile(L, B, layout, dk, bias_mu):
+    """The same for 65 to 192 tokens in nine slabs, a wave per tile: mild gates, -0.7 a step (at 192 tokens a reference point to
+    each half), and the range-safe form; and in 777 slabs of 80 tokens, two tiles to a wave and two slabs to a workgroup,
+    where the range-safe form's waves read gates that others of the workgroup have made."""
     _check_gated_one_chunk(L, B, layout, dk, bias_mu)
 
 
