@@ -92,10 +92,12 @@ hipError_t launch(const void *q, const void *k, const void *v, const void *gf, c
     // Parts of a strip's tokens (exact_sweep.hpp) while a compute unit has one strip, or two of two parts each.  fp32, us for 1 / 2 /
     // 4 parts: 8 slabs (256 strips, 64 x 64) of 196 tokens 37.8 / 32.9 / 25.8, of 98 22.0 / 20.1 / 15.6, of 56 13.7 / 12.6 / 10.0, of 32
     // 8.4 / 8.0 / 8.3; 12 slabs of 196 39.7 / 34.8 / 44.8, of 17 8.7 / 8.4 / 12.7; 20 (640 strips) of 196 41.9 / 54.7 / 63.5; 128 slabs of
-    // 196, 16 x 16, 54.6 / 48.9 / 36.1.
+    // 196, 16 x 16, 54.6 / 48.9 / 36.1.  A second part starts to pay at three tiles, 0.90 to 0.98 of one part's time for 17 to 48 tokens (two
+    // tiles: 1.04 to 1.25); with 64-wide values, whose sums over the lanes are the longest, at seven (17 to 24 tokens 0.96 to 0.99, 25 to
+    // 48 0.96 to 1.04, 49 to 80 0.92 to 1.00).
     const long strips = BH * (kRowStrips + kColStrips);
     if (strips <= 256 && L >= 40) return run(integral_constant<int, 1>{}, 0u, integral_constant<int, 4>{});
-    if (strips <= 512 && L > kTile) return run(integral_constant<int, 1>{}, 0u, integral_constant<int, 2>{});
+    if (strips <= 512 && L > (DV == 64 ? 6 : 2) * kTile) return run(integral_constant<int, 1>{}, 0u, integral_constant<int, 2>{});
     // as in the forward: one pair per workgroup until every compute unit has one
     if constexpr (kRowStrips % 2 == 0 && kColStrips % 2 == 0)
         if (BH * (kRowStrips + kColStrips) > 512) return run(integral_constant<int, 2>{}, 0u, integral_constant<int, 1>{});

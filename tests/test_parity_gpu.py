@@ -1450,10 +1450,11 @@ def test_exact_kernels_tile_edges(L, dk, dv, layout):
 
 @pytest.mark.parametrize("B,H,L,dk,dv,layout", ((2, 2, 39, 64, 64, "bhld"), (2, 2, 40, 64, 64, "blhd"), (1, 3, 41, 32, 32, "bhld"),
                                                 (2, 4, 57, 16, 16, "blhd"), (3, 4, 9, 64, 64, "bhld"), (3, 4, 16, 64, 64, "blhd"),
-                                                (4, 4, 50, 64, 64, "bhld"), (4, 17, 50, 32, 16, "blhd")))
+                                                (4, 4, 50, 64, 64, "bhld"), (4, 17, 50, 32, 16, "blhd"), (3, 4, 48, 64, 64, "bhld"),
+                                                (3, 4, 49, 64, 64, "blhd"), (3, 4, 17, 64, 32, "bhld"), (2, 4, 17, 16, 16, "blhd")))
 def test_exact_kernels_parts(B, H, L, dk, dv, layout):
-    """Strips cut into four and into two parts of tokens, and the line between (256 and 512 strips, 40 and 9 tokens): parts of
-    unequal length, of a tile, and without one."""
+    """Strips cut into four and into two parts of tokens, and the lines between (256 and 512 strips; 40 tokens, and 17 or, with
+    64-wide values, 49): parts of unequal length, of a tile, and without one."""
     _check_exact(B, H, L, dk, dv, layout)
 
 
@@ -1481,6 +1482,25 @@ def test_exact_kernels_parts_keep_an_infinite_element(B, H, L, dk, dv):
         x[0, 0, t0, 3] = float("inf")
         _, dk_, dv_, _, _ = vb.bigla_bwd(q, k, v, gate, gate, x)
         assert inf(dk_) and inf(dv_[..., 3]) and bool(torch.isfinite(dv_[..., :3]).all()), f"dk, dv {t0}"
+
+
+@pytest.mark.parametrize("L,dk,dv", ((9, 64, 64), (16, 64, 64), (16, 16, 16), (16, 32, 32), (24, 64, 64), (33, 16, 64), (48, 64, 64)))
+def test_exact_gradient_of_short_sequences_in_one_part(L, dk, dv):
+    """Where a strip's tokens stay in one part, a slab's gradients have the same bits in a call of 288 strips or more (in two
+    parts, a sum of the part's own products and of what enters it) as in one of more than 512, which is never cut."""
+    import torch
+    from paper_2405_18425_amd import binding as vb
+
+    per_slab = 2 * dk * dv // 256
+    few, many = 288 // per_slab + 1, 520 // per_slab + 1
+    _say(f"exact gradient in one part L{L} dk{dk} dv{dv}")
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    rn = lambda d: torch.randn(many, 1, L, d, device="cuda", generator=gen)
+    t = [rn(dk), rn(dk), rn(dv), -rn(dk).abs(), -rn(dk).abs(), rn(dv)]
+    want = vb.bigla_bwd(*t)
+    got = vb.bigla_bwd(*(a[:few].contiguous() for a in t))
+    for a, b, name in zip(got, want, ("dq", "dk", "dv", "dg_fwd", "dg_bwd")):
+        assert torch.equal(a, b[:few]), name
 
 
 def _check_exact(B, H, L, dk, dv, layout):
