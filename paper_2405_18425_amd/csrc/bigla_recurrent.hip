@@ -167,8 +167,9 @@ hipError_t launch(const void *q, const void *k, const void *v, const void *gf, c
     // finds what enters it: four parts.  The walks are bound by the instructions their SIMD can issue, so with two strips on
     // a compute unit the extra ones cost more than the shorter way gains.  fp32, us for 1 / 2 / 4 parts: 12 slabs (192 strips, 64 x 64) of
     // 196 tokens 23.3 / 23.2 / 20.5, of 98 14.3 / 14.6 / 13.3, of 56 9.7 / 9.5 / 8.1, of 32 5.8 / 6.0 / 6.1; 20 slabs (320 strips) of 196
-    // 26.2 / 30.9 / 37.5; one slab of 1024 104 / 88 / 68.
-    if (long(BH) * kBlocks <= 256 && L >= 40) return run(integral_constant<int, 1>{}, integral_constant<int, 4>{});
+    // 26.2 / 30.9 / 37.5; one slab of 1024 104 / 88 / 68.  Not for ten tiles, which are parts of two, three, two and three: 15
+    // slabs of 72 / 80 / 88 tokens 11.0 / 11.2 / 12.6 in one part, 10.4 / 12.0 / 12.1 in four.
+    if (long(BH) * kBlocks <= 256 && L >= 40 && (L + kTile - 1) / kTile != 10) return run(integral_constant<int, 1>{}, integral_constant<int, 4>{});
     // Few strips: one pair per workgroup, so that they spread over the compute units.  More than one pair
     // for every unit: two per workgroup, which read the slab's rows from memory once.
     if constexpr (kBlocks % 2 == 0)

@@ -1503,6 +1503,19 @@ def test_exact_gradient_of_short_sequences_in_one_part(L, dk, dv):
         assert torch.equal(a, b[:few]), name
 
 
+@pytest.mark.parametrize("L", (39, 73, 80))
+def test_exact_forward_of_ten_tiles_in_one_part(L):
+    """The same for the forward below 40 tokens and at ten tiles: 192 strips have the bits of 320, which are never cut."""
+    import torch
+    from paper_2405_18425_amd import binding as vb
+
+    _say(f"exact forward in one part L{L}")
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    rn = lambda: torch.randn(20, 1, L, 64, device="cuda", generator=gen)
+    t = [rn(), rn(), rn(), -rn().abs(), -rn().abs()]
+    assert torch.equal(vb.bigla_fwd(*(a[:12].contiguous() for a in t)), vb.bigla_fwd(*t)[:12])
+
+
 def _check_exact(B, H, L, dk, dv, layout):
     import oracle
     import torch
