@@ -1,5 +1,6 @@
 // BiGLA forward (Section 4.2.1, Eq. (BiGLA)) for sequences of up to 256 tokens, bf16, dv = 64, dk = 64 or 32: the
-// whole sequence is one chunk.  With b_t (c_t) the forward (backward) cumulative log-gate of the sequence, referred to
+// whole sequence is one chunk.  The kernel with two 16-token tiles to a wave, which is given 65 to 256 tokens in at least 128 slabs
+// (bigla_tile.hpp has the one with a tile to a wave; wave_per_tile says which runs).  With b_t (c_t) the forward (backward) cumulative log-gate of the sequence, referred to
 // the middle of the sequence,
 //   out_t = 1/2 sum_{i <= t} (q_t exp(b_t) . k_i exp(-b_i)) v_i + 1/2 sum_{i >= t} (q_t exp(c_t) . k_i exp(-c_i)) v_i ,
 // so there are no states at all: no second pass over k, v and the gates, no workspace traffic, no walk from chunk to
@@ -16,8 +17,8 @@
 // of its token, and nothing is bounced through LDS.  LDS rows are 128 (64) bytes without padding, their 16-byte pieces
 // permuted by row so that the accesses of 16 lanes fall into different banks.
 //
-// A slab in which some 64-token stretch decays by more than kMildRange in a channel (a sequence of fewer tokens: by more than
-// its share of that) takes the range-safe form of bigla_chunk.hip, tile by tile (short_slab_safe), inside the same launch.
+// A slab in which some 64-token stretch decays by more than kMildRange in a channel takes the range-safe form of
+// bigla_chunk.hip, tile by tile (short_slab_safe), inside the same launch.
 //
 // Measured (kernel trace): 384 slabs of 196 tokens, 57.8 MB: 23.0 us (the chunked kernel that walks a slab twice in one
 // launch: 32.0 us); 192 slabs: 14.7 us (23.2).
@@ -409,11 +410,8 @@ __global__ __launch_bounds__(64 * kShortWaves, 4) void bigla_short_kernel(
         }
         own_offs[c] = w < mid ? -of : of;
         own_offs[kDk + c] = w < mid ? ob : -ob;
-        // (a NaN counts as too fast; a sequence of under 64 tokens has its share of the range: the decay per token is what
-        // leaves an output few tokens to sum over.  A last stretch of a few tokens keeps all of it: the slab's scale is that of
-        // the others, and few gates of such a stretch are an ordinary draw away from a share.)
-        const float range = kMildRange / kC * float(min(L, kC));
-        if (!(stretch[0] >= -range && stretch[1] >= -range)) *strong = 1;
+        // (a NaN counts as too fast; a last stretch of a few tokens has the whole range: see bigla_tile.hpp)
+        if (!(stretch[0] >= -kMildRange && stretch[1] >= -kMildRange)) *strong = 1;
         wave_lds_fence();
     }
     f32x4 offs[2][kCt];

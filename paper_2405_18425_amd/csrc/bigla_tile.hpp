@@ -1,12 +1,12 @@
-// BiGLA forward (Section 4.2.1, Eq. (BiGLA)) for sequences of up to 256 tokens in one chunk, as in bigla_short.hpp (the algebra is
-// there), with a wave per 16-token tile and a slab per workgroup: the form for few slabs, where the chain of one workgroup is
-// what takes the time and most of the chip's wave slots are empty.
+// BiGLA forward (Section 4.2.1, Eq. (BiGLA)) for sequences of up to 192 tokens (12 tiles) in one chunk, as in bigla_short.hpp (the
+// algebra is there), with a wave per 16-token tile and a slab per workgroup: for few slabs, where the chain of one workgroup is what takes
+// the time and most of the chip's wave slots are empty, and for up to 64 tokens in any number of slabs.
 //
 // A wave scans the gates of its own tile only (its rows never leave it, so there is no barrier before the scan); the tiles'
 // totals are exchanged through LDS and enter as offsets of the exponents.  Its own diagonal tile of the scores comes from its
 // registers.  Three barriers.
 //
-// A slab in which some 64-token stretch decays by more than kMildRange has the operands of the diagonal tiles split into bf16 pairs,
+// A slab in which some 64-token stretch decays by more than kMildRange (a sequence of fewer tokens: by more than its share of that) has the operands of the diagonal tiles split into bf16 pairs,
 // as in the eight-wave kernels.  All exponents are referred to one point in the middle of the sequence as long as neither half decays
 // by more than kFastRange.  Up to 128 tokens a slab beyond that takes the range-safe form (short_slab_safe), a tile a wave; there
 // that is the limit of the eight-wave kernels, 60 nats in 64 tokens.  From 129 tokens on (kHalves) each half is then referred to
@@ -181,7 +181,10 @@ __global__ __launch_bounds__(64 * (kHalves ? kTileMost : kTileWhole), kHalves ? 
         const float xf = low ? -of : of, xb = low ? ob : -ob;
         own_offs[c] = xf * kLog2e;
         own_offs[kDk + c] = xb * kLog2e;
-        if ((w & 3) == 0) {  // the 64-token stretch that begins here (a NaN counts as too fast; shorter sequences: see bigla_short_kernel)
+        // The 64-token stretch that begins here.  (A NaN counts as too fast; a sequence of under 64 tokens has its share of the range: the
+        // decay per token is what leaves an output few tokens to sum over.  A last stretch of a few tokens keeps all of it: the slab's
+        // scale is that of the others, and few gates of such a stretch are an ordinary draw away from a share.)
+        if ((w & 3) == 0) {
             float s[2] = {0.f, 0.f};
 #pragma unroll
             for (int dir = 0; dir < 2; ++dir)
