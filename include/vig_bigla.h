@@ -84,9 +84,11 @@ size_t bigla_workspace_bytes(int B, int H, int L, int dk, int dv, int dtype);
  * operands, fp32 accumulation, fp32 carried state; dk = 32 is widened to 64 key channels with zeros
  * inside the kernels).  Where some channel of a 64-token chunk decays by more than 16 nats (a quarter
  * of a nat per step), the operands of every token's nearest products are kept to 16 bits: at full
- * speed up to 60 nats per chunk where the eight-wave kernels run (see bigla_fwd_plan),
- * otherwise in a range-safe form, several times slower, that treats per-step log gates below -8
- * as -8 (alpha < 3.4e-4 acts as a hard reset either way; the difference is far below the bf16
+ * speed up to 60 nats per chunk where the eight-wave kernels or the one launch for more than 256 slabs
+ * run (see bigla_fwd_plan), and up to 60 nats per half (a quarter beyond 128 tokens) of a
+ * sequence of up to 192 tokens, except where 65 to 192 tokens come in so many slabs that a wave takes two
+ * 16-token tiles; otherwise in a range-safe form, several times slower, that treats per-step log gates
+ * below -8 as -8 (alpha < 3.4e-4 acts as a hard reset either way; the difference is far below the bf16
  * tolerance).  Every other case runs the exact recurrence in fp32 arithmetic.
  */
 int bigla_fwd(const void *q, const void *k, const void *v, const void *g_fwd, const void *g_bwd,
@@ -107,8 +109,8 @@ int bigla_fwd_layout(const void *q, const void *k, const void *v, const void *g_
  * Eq. (BiGLA); a measurement and testing aid: the result is the same up to operand rounding).
  *   VIG_FWD_AUTO              what bigla_fwd_layout runs: up to 192 tokens, and up to 256 in at least 128
  *                             slabs, one launch that takes the whole sequence as one chunk; otherwise, in more
- *                             than 256 slabs, one launch with a four-wave workgroup per slab, else the
- *                             eight-wave kernels;
+ *                             than 256 slabs (not in 513 to 768 of more than 3072 tokens), one launch with a
+ *                             four-wave workgroup per slab, else the eight-wave kernels;
  *   VIG_FWD_FOUR_WAVE         workgroups of four waves, each wave walking the whole chain of a chunk
  *                             step for its 16 tokens;
  *   VIG_FWD_WAVE_SPECIALISED  workgroups of eight waves: producer waves (gate scans, exponentials, scaled
@@ -234,9 +236,9 @@ int locality_gate_fwd_layout(const void *x, const void *w, const void *bias, con
  *                             as bigla_fwd would store it) never goes through memory: a sixth fewer
  *                             bytes per step and no intermediate tensor, at about the speed of two
  *                             launches where the eight-wave kernels carry it (grids under 65 columns,
- *                             the shapes of VIG_FWD_WAVE_SPECIALISED) and slower elsewhere.
- *                             Where the token mixer is one launch (see bigla_fwd_plan) that launch writes `out` and the
- *                             locality kernel blends it in place (no intermediate tensor either).
+ *                             the shapes of VIG_FWD_WAVE_SPECIALISED, up to 256 slabs) and slower elsewhere.
+ *                             Where the token mixer takes a sequence as one chunk (see bigla_fwd_plan) its launch writes
+ *                             `out` and the locality kernel blends it in place (no intermediate tensor either).
  *                             VIG_BF16 with dv = 64, dk = 64 or 32 and at least 32 tokens only,
  *                             the cases in which bigla_fwd runs the chunkwise path
  *                             (VIG_ERR_UNSUPPORTED otherwise);
@@ -297,8 +299,8 @@ int gate_producer_fwd(const void *x, const void *w1, const void *w2, const void 
  *                            where bigla_fwd_plan admits VIG_FWD_WAVE_SPECIALISED (VIG_ERR_UNSUPPORTED
  *                            otherwise, and while vig_measure_alias_slabs is on);
  *   VIG_GATES_AUTO           where the mixer takes a sequence as one chunk (bf16, dv = 64; see bigla_fwd_plan), its one launch
- *                            makes the gates in the same way; else VIG_GATES_IN_STATE_PASS where it applies and is the
- *                            faster one (up to 256 slabs); else VIG_GATES_SEPARATE.
+ *                            makes the gates in the same way; else VIG_GATES_IN_STATE_PASS where the mixer takes the
+ *                            eight-wave kernels (see bigla_fwd_plan); else VIG_GATES_SEPARATE.
  * workspace: at least gated_bigla_workspace_bytes(B, H, L, dk, dv, dtype) bytes (0 for invalid or unsupported
  * arguments; it covers every plan).
  */

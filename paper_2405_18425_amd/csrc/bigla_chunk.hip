@@ -21,9 +21,10 @@
 //   per-channel sub-block total is checked): far inside fp32's range, and slow enough a decay
 //   that an output sums over enough tokens for the rounding of the scaled operands to stay
 //   within the stated tolerance.  Gates of the paper's form, sigmoid(z)^(1/16), stay inside:
-//   64 steps reach 16 nats only for z < -4 throughout.  (The eight-wave kernels of
-//   bigla_chunk_ws.hpp keep the fast form up to 60 nats, with split operands for the diagonal
-//   score tiles beyond 16.)
+//   64 steps reach 16 nats only for z < -4 throughout.  (bigla_slab_kernel without the locality
+//   epilogue, and the eight-wave kernels of bigla_chunk_ws.hpp, keep the fast form up to 60 nats,
+//   with split operands for the diagonal score tiles beyond 16; so does the one-chunk kernel of
+//   bigla_tile.hpp, over stretches that it states.)
 //   RANGE-SAFE.  Otherwise cumulative gates stay local to a sub-block: off-diagonal 16x16 tiles
 //   scale keys by the decay to the END of the key's own sub-block and queries by the decay from
 //   the START of the query's sub-block times the whole-sub-block factors in between, so every
@@ -1289,13 +1290,16 @@ hipError_t bigla_chunk_launch(const void *q, const void *k, const void *v, const
     if (dk != kD && dk != kD / 2) return hipErrorInvalidValue;
     const LocalityFusion none = {};
     // (key width, layout, fused epilogue) pick the instantiation
-    // kernels: 0 = the faster set for the shape (the eight-wave kernels where they apply), 1 = four-wave,
+    // kernels: 0 = the faster set for the shape (one chunk, one launch for many slabs, else the eight-wave kernels), 1 = four-wave,
     // 2 = eight-wave (an error where they do not apply), 3 = four-wave with one workgroup per slab
     // (with a fusion: grids narrow enough for the eight-wave epilogue's ring of conv-input rows)
     if (kernels == 0 && !fusion && bigla_short_applicable(BH, L))
         return bigla_short_launch(q, k, v, g_fwd, g_bwd, out, BH, L, dk, heads_token_major, workspace, stream);
     const bool ws_ok = bigla_chunk_ws_applicable(BH, L, dk) && (!fusion || (fusion->Wg < kXHalo && L < (1 << 22)));
     if (kernels == 2 && !ws_ok) return hipErrorInvalidValue;
+    // (The locality epilogue stays with the eight-wave kernels in more than 256 slabs: it is there so that no intermediate tensor is needed, and
+    // the slab kernel has a slower one.  us per bigla_locality_fwd, epilogue / two launches: 257 slabs of 289 tokens 64.9 / 46.6, 300 of 600
+    // 110.6 / 84.6, 600 of 1024 297 / 269, 1024 of 306 142.9 / 115.6, 300 of 4096 711 / 576, 600 of 4096 1119 / 1100.)
     if (kernels == 2 || (kernels == 0 && ws_ok && (fusion || !bigla_chunk_slab_preferred(BH, L)))) {
         return bigla_chunk_ws_launch(q, k, v, g_fwd, g_bwd, out, BH, L, dk, heads_token_major, workspace, stream,
                                      nullptr, fusion);

@@ -25,10 +25,10 @@ constexpr float kGateFloorLog2 = -8.0f * kLog2e;  // per-step floor of the log-g
 //     from 0.2 to 0.5 nats per step the worst element of 400 000 sits at 0.55-0.8 of a bound of 2 % of
 //     |value| + slab rms with bf16 operands and at 0.2-0.4 with the diagonal tile exact; a random case at
 //     0.48 nats per step reached 1.13).  Beyond a quarter of a nat per step the operands of the diagonal score
-//     tile are split into two bf16 terms: the eight-wave kernels do that inside the fast form, the four-wave
-//     kernels and the one-chunk kernel (bigla_short.hpp; there a sequence of under 64 tokens by its share of the limit)
-//     take the range-safe form (which splits them always).  Gates of the paper's form at the
-//     benchmark's statistics stay under 11 nats per chunk.
+//     tile are split into two bf16 terms: the eight-wave kernels, the slab kernel (without the locality epilogue) and the
+//     one-chunk kernel of bigla_tile.hpp (a sequence of under 64 tokens by its share of the limit) do that inside the fast
+//     form, the other four-wave kernels and the one-chunk kernel of bigla_short.hpp take the range-safe form (which splits
+//     them always).  Gates of the paper's form at the benchmark's statistics stay under 11 nats per chunk.
 constexpr float kFastRange = 60.0f;
 constexpr float kMildRange = 16.0f;
 
