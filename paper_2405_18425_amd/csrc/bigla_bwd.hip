@@ -42,7 +42,7 @@ __global__ __launch_bounds__(128 * kPairs * kParts, 1) void bigla_bwd_exact_kern
     constexpr int kRowWork = DK / (kStrip * (64 / DV)) / kPairs;  // workgroups of a slab that take rows
     static_assert(kPairs == 1 || kParts == 1, "one strip's parts per workgroup");
     __shared__ RowStage<DV> stage[2 * kPairs * kParts];
-    __shared__ PartStage<kParts> parts;
+    __shared__ PartStage<kParts, 2> parts;
     const unsigned slab = first_slab + blockIdx.x % n_slabs;
     const int work = int(blockIdx.x / n_slabs);
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x)) >> 6, lane = int(threadIdx.x) & 63;

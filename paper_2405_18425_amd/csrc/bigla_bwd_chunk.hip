@@ -598,7 +598,7 @@ __device__ __forceinline__ void exact_strips(const ExactArgs &a, RowStage<kD> (&
     const bool descending = (wave & 1) != 0;
     const size_t step = a.heads_token_major ? a.heads_token_major : 1, keys = size_t(a.L) * DK, all_keys = keys * a.n_slabs;
     const unsigned n_marked = unsigned(__popc(marked));
-    PartStage<1> whole;
+    PartStage<1, 2> whole;
 #pragma unroll 1
     for (unsigned i = worker; i < n_marked * (kRowItems + kColItems); i += workers) {
         // (what depends on the lane is formed anew for every strip: hoisted out of this loop, the offsets of both kinds of

@@ -112,7 +112,7 @@ __global__ __launch_bounds__(128 * kPairs * kParts, 1) void bigla_recurrent_kern
 {
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x)) >> 6, lane = int(threadIdx.x) & 63;
     static_assert(kPairs == 1 || kParts == 1, "one strip's parts per workgroup");
-    __shared__ PartStage<kParts> parts;
+    __shared__ PartStage<kParts, 1> parts;
     const unsigned slab = blockIdx.x % n_slabs;
     const int col_block = int(blockIdx.x / n_slabs) * kPairs + (kPairs > 1 ? wave >> 1 : 0);
     const bool descending = (wave & 1) != 0;

@@ -216,13 +216,13 @@ __device__ __forceinline__ void over_tiles(int first, int last, Fetch fetch, Wal
 }
 
 // What the waves of a strip exchange between its parts: a lane's elements of the matrices a part leaves when nothing enters
-// it, and the decay over the part, per direction and part.  (A column sweep has one matrix, a row sweep two.)
-template <int kParts>
+// it, and the decay over the part, per direction and part.  kMatrices: 1 for column sweeps alone, 2 where row sweeps use it too.
+template <int kParts, int kMatrices>
 struct PartStage {
-    float4 end[2][kParts][2][64], decay[2][kParts][2][64];
+    float4 end[2][kParts][kMatrices][64], decay[2][kParts][kMatrices][64];
 };
-template <>
-struct PartStage<1> {};
+template <int kMatrices>
+struct PartStage<1, kMatrices> {};
 
 // A decay over several tokens, as a product of their factors that is zero only where a factor is: an infinite element of the
 // matrix then stays infinite over a part, as it does from token to token.  (The smallest positive number for a product below
@@ -231,8 +231,8 @@ constexpr float kLeastFactor = 1.401298464324817e-45f;
 __device__ __forceinline__ float joint_factor(float a, float b) { return fmaxf(a * b, fminf(fminf(a, b), kLeastFactor)); }
 
 // M: what enters the wave's part, from what the parts before it on its way leave
-template <int kParts>
-__device__ __forceinline__ void enter_part(const PartStage<kParts> &ex, int matrix, bool descending, int part, int lane, float (&M)[kStrip])
+template <int kParts, int kMatrices>
+__device__ __forceinline__ void enter_part(const PartStage<kParts, kMatrices> &ex, int matrix, bool descending, int part, int lane, float (&M)[kStrip])
 {
     const int before = descending ? kParts - 1 - part : part;
     for (int u = 0; u < before; ++u) {
@@ -251,10 +251,10 @@ __device__ __forceinline__ void enter_part(const PartStage<kParts> &ex, int matr
 // b = d_out, r = k).  `park`: fp32, dense or strided like the result; result = result_scale * (own + parked).
 // One barrier, and one more with several parts, executed by every wave that calls this.  `park` and `result` may be one
 // buffer (fp32).
-template <typename T, int DK, int DV, bool kDelayed, typename Off = unsigned, int kParts = 1>
+template <typename T, int DK, int DV, bool kDelayed, typename Off = unsigned, int kParts = 1, int kMatrices>
 __device__ __forceinline__ void column_sweep(const T *u_rows, const T *r_rows, const T *g_rows, const T *b_rows,
                                              float *park, T *result, size_t step, size_t park_step, int L,
-                                             bool descending, int part, PartStage<kParts> &parts, int col_block,
+                                             bool descending, int part, PartStage<kParts, kMatrices> &parts, int col_block,
                                              float b_scale, float result_scale, int lane)
 {
     constexpr int kGroups = 64 / DK;
@@ -419,7 +419,7 @@ template <typename T, int DK, int DV, typename Off = unsigned, int kParts = 1>
 __device__ __forceinline__ void row_sweep(const T *q_rows, const T *k_rows, const T *v_rows, const T *gf_rows,
                                           const T *gb_rows, const T *do_rows, T *dq_rows, T *dk_rows, T *dgf_rows,
                                           T *dgb_rows, float *part_f, float *part_b, RowStage<DV> &stage, size_t step,
-                                          int L, bool descending, int part, PartStage<kParts> &parts, int row_block, int lane)
+                                          int L, bool descending, int part, PartStage<kParts, 2> &parts, int row_block, int lane)
 {
     constexpr int kGroups = 64 / DV;
     constexpr int kRows = kStrip * kGroups;   // rows of the wave
